@@ -104,7 +104,8 @@ typedef struct {
 /* Launch and search knobs; a zeroed struct (or NULL) means "choose automatically". */
 typedef struct {
   int32_t wg_size;      /* threads per workgroup, a multiple of 64 up to 1024; 0 = auto
-                           (the occupancy rule of §IV-E) */
+                           (the occupancy rule of §IV-E). Bitset kernels: 0 (teams of up to 16
+                           wavefronts, one node each) or 64 (one wavefront) */
   int32_t num_wg;       /* workgroups in the persistent grid; 0 = as many as are co-resident;
                            larger values are clamped to the co-resident maximum */
   int32_t wl_capacity;  /* global worklist entries (rounded up to a power of two); 0 = auto */
@@ -166,7 +167,8 @@ typedef struct {
                              bitset launches, the span from its start to the last one's end) */
   double greedy_ms;       /* greedy kernel time (MVC) */
   double total_ms;        /* wall clock of the whole call */
-  /* With VC_OPT_PROFILE, shader-clock cycles summed over the workgroups (paper §V-D):
+  /* With VC_OPT_PROFILE, shader-clock cycles summed over the workgroups, with the bitset kernels
+   * over every wavefront of them (paper §V-D):
    * [0] taking nodes (stack pops, worklist dequeues, waiting for work), [1] reduction rules,
    * [2] branching (max-degree pass, stopping test, removing v_max or N(v_max)),
    * [3] deferring children (stack pushes, worklist enqueues), [4] other (flags, bound,

@@ -9,7 +9,7 @@
 // self-contained, given the read-only adjacency, and W*8 + 8 bytes instead of 4(n+2). A degree
 // is recomputed as popcount(adj[v] & L).
 //
-// One wavefront per workgroup. Lane l holds vertices l, 64+l, ..., (W-1)*64+l and their W
+// One wavefront per node. Lane l holds vertices l, 64+l, ..., (W-1)*64+l and their W
 // adjacency words each in vector registers; the whole adjacency matrix also sits in LDS for
 // random access (the triangle test). A rule pass is a handful of ballots and bit operations;
 // the main loop has no barriers except inside the worklist protocol.
@@ -398,16 +398,24 @@ constexpr int bits_stride() {
 constexpr int kPendingBits = 10;
 
 template <int W>
+__device__ __forceinline__ void bits_pack(uint32_t (&x)[2 * W + 2], const Live<W>& L, int pending,
+                                          int inst) {
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    x[2 * w] = static_cast<uint32_t>(L.bits[w]);
+    x[2 * w + 1] = static_cast<uint32_t>(L.bits[w] >> 32);
+  }
+  x[2 * W] = static_cast<uint32_t>(L.s);
+  x[2 * W + 1] = static_cast<uint32_t>(pending + 1) | (static_cast<uint32_t>(inst) << kPendingBits);
+}
+
+template <int W>
 __device__ __forceinline__ void bits_store(int32_t* dst, const Live<W>& L, int pending, int inst) {
   if (lane_id() == 0) {
+    uint32_t x[2 * W + 2];
+    bits_pack<W>(x, L, pending, inst);
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-      dst[2 * w] = static_cast<int32_t>(static_cast<uint32_t>(L.bits[w]));
-      dst[2 * w + 1] = static_cast<int32_t>(static_cast<uint32_t>(L.bits[w] >> 32));
-    }
-    dst[2 * W] = L.s;
-    dst[2 * W + 1] = static_cast<int32_t>(static_cast<uint32_t>(pending + 1) |
-                                          (static_cast<uint32_t>(inst) << kPendingBits));
+    for (int i = 0; i < 2 * W + 2; ++i) dst[i] = static_cast<int32_t>(x[i]);
   }
 }
 
@@ -486,73 +494,201 @@ __device__ __forceinline__ void write_cover(uint8_t* cov, const Live<W>& L, int 
   }
 }
 
-// ---- worklist protocol for a one-wavefront workgroup ----------------------------------------
-// Lane 0 runs the whole protocol (reservation, the node copy, the release / acquire of the slot
+// ---- worklist protocol -----------------------------------------------------------------------
+// One lane runs the whole protocol (reservation, the node copy, the release / acquire of the slot
 // ticket), so one agent-scope release store orders the node's words before the ticket and one
-// acquire load orders them after it; the result reaches the other lanes by readfirstlane.
+// acquire load orders them after it.
 
-// Donate a deferred child of instance `inst` to the worklist; true if the worklist took it.
-// The child is the stored node at `oldest` (the bottom of this workgroup's stack) when that is
-// not null, else node L with `pending` as its branch vertex.
-template <int W>
-__device__ __forceinline__ bool bits_enqueue(const Params& p, Ctrl& c, const Live<W>& L,
-                                             int pending, const int32_t* oldest, int inst) {
-  int ok = 0;
-  if (lane_id() == 0) {
-    ok = enqueue_reserve(p, c, inst) == 1;
-    if (ok) {
-      int32_t* dst = p.payload + static_cast<size_t>(c.slot) * p.stride;
-      if (oldest) {
-#pragma unroll
-        for (int i = 0; i < 2 * W + 2; ++i) dst[i] = oldest[i];
-      } else {
-        bits_store<W>(dst, L, pending, inst);
-      }
-      store_release(p.seq + c.slot, 2u * c.lap + 1u);
-    }
-  }
-  return __builtin_amdgcn_readfirstlane(ok);
+// Ring slot `at` entries after `from` in a ring of `cap` (at <= cap).
+__device__ __forceinline__ int ring_slot(int from, int at, int cap) {
+  const int x = from + at;
+  return x >= cap ? x - cap : x;
 }
 
-// Take work. Returns 1 with L / pending / inst set from a worklist node, 2 with inst set to an
-// unstarted instance (its root), 0 when the launch is over, -1 when it is being stopped. Queued
-// nodes go first, then roots in instance order; idle polling as in dequeue_begin.
+// Word i of stack entry `slot`: from the ring in LDS or in device memory.
 template <int W>
-__device__ __forceinline__ int bits_dequeue(const Params& p, Ctrl& c, Live<W>& L, int& pending,
-                                            int& inst) {
-  int status = 3;
-  uint32_t words[2 * W + 2];
-  int root = 0;
-  if (lane_id() == 0) {
-    int polls = 0;
-    while (status == 3) {
-      uint32_t slot = 0, lap = 0;
-      status = worklist_take(p, c, (polls & 3) == 0, &slot, &lap, &root);
-      if (status == 1) {
-        int wait = 0;
-        while (load_acquire(p.seq + slot) != 2u * lap + 1u) {
-          if (search_stopped(p, c)) {
-            status = -1;
-            break;
-          }
-          backoff(wait);
-        }
-        if (status == 1) {
-          const int32_t* src = p.payload + static_cast<size_t>(slot) * p.stride;
+__device__ __forceinline__ void bits_copy_entry(int32_t* __restrict__ dst, const int32_t* lstack,
+                                                const int32_t* gstack, bool stack_lds, int slot) {
+  constexpr int kStride = bits_stride<W>();
+  uint32_t x[2 * W + 2];
+  if (stack_lds) {
 #pragma unroll
-          for (int i = 0; i < 2 * W + 2; ++i) words[i] = static_cast<uint32_t>(src[i]);
-          store_release(p.seq + slot, 2u * (lap + 1u));
-        }
-      } else if (status == 3) {
-        const int units = 1 << (polls < 5 ? polls : 5);
-        for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(16);
-        ++polls;
-      }
+    for (int i = 0; i < 2 * W + 2; ++i) x[i] = static_cast<uint32_t>(lstack[slot * kStride + i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2 * W + 2; ++i)
+      x[i] = static_cast<uint32_t>(gstack[static_cast<size_t>(slot) * kStride + i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2 * W + 2; ++i) dst[i] = static_cast<int32_t>(x[i]);
+}
+
+// Donate the `m` (at most 64) oldest entries of this wavefront's stack, nodes of instance `inst`,
+// to the worklist; false if the worklist is at its threshold. Whole wavefront: lane 0 reserves m
+// consecutive tickets with one set of atomics, lane i copies entry i into ticket i's slot.
+template <int W>
+__device__ __forceinline__ bool bits_enqueue(const Params& p, Ctrl& c, int inst, int m,
+                                             const int32_t* lstack, const int32_t* gstack,
+                                             bool stack_lds, int bot_slot) {
+  const int lane = lane_id();
+  uint32_t t_lo = 0, t_hi = 0;
+  int ok = 0;
+  if (lane == 0) {
+    int32_t* count = ctr_i32(p, kQCount);
+    if (load_relaxed(count) < static_cast<int32_t>(p.q_threshold)) {
+      fetch_add(p.work + inst, m);
+      fetch_add(ctr_i32(p, kWork), m);
+      fetch_add(count, m);  // stays below cap: threshold + producers * (kDonateMost + 1) <= cap
+      const unsigned long long t =
+          fetch_add(ctr_u64(p, kQTail), static_cast<unsigned long long>(m));
+      t_lo = static_cast<uint32_t>(t);
+      t_hi = static_cast<uint32_t>(t >> 32);
+      ok = 1;
     }
   }
-  status = __builtin_amdgcn_readfirstlane(status);
-  if (status == 1) bits_unpack<W>(words, L, pending, inst);
-  else if (status == 2) inst = __builtin_amdgcn_readfirstlane(root);
+  if (!__builtin_amdgcn_readfirstlane(ok)) return false;
+  const uint64_t t = ((static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(t_hi)) << 32) |
+                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(t_lo))) + lane;
+  if (lane < m) {
+    const uint32_t slot = static_cast<uint32_t>(t) & (p.q_cap - 1);
+    const uint32_t lap = static_cast<uint32_t>(t / p.q_cap);
+    int spins = 0;
+    bool lost = false;
+    while (load_acquire(p.seq + slot) != 2u * lap) {
+      if (search_stopped(p, c)) {  // the launch is ending: the node no longer matters
+        lost = true;
+        break;
+      }
+      backoff(spins);
+    }
+    if (!lost) {
+      bits_copy_entry<W>(p.payload + static_cast<size_t>(slot) * p.stride, lstack, gstack,
+                         stack_lds, ring_slot(bot_slot, lane, p.depth_cap));
+      store_release(p.seq + slot, 2u * lap + 1u);
+    }
+  }
+  return true;
+}
+
+// What the wavefronts of one workgroup (a team) share, in LDS. They all work on one instance, the
+// one whose adjacency matrix the workgroup holds, and pass sub-trees to each other through one
+// mailbox per wavefront:
+//  - a wavefront that has finished its sub-tree lowers `active` and sets its bit of `idle`;
+//  - one that has a deferred child and sees an idle bit clears it (the claim), raises `active`,
+//    writes the child into that wavefront's box and sets its mail flag.
+// `active` counts the sub-trees the team holds, handed-over ones included, so it reaches zero
+// only when the team has finished everything it took; thread 0 then looks for more work in the
+// worklist. A handover costs a few LDS operations, where a donation through the worklist is a
+// chain of six device-scope memory operations (several microseconds, and far more when thousands
+// of workgroups contend for its counters).
+template <int W>
+struct Team {
+  int32_t active;
+  uint32_t idle;
+  uint32_t best;   // MVC: smallest cover size any wavefront of the team has seen
+  int32_t status;  // thread 0's look for work: 1 a node in words, 2 the root of `inst`, <= 0 end
+  int32_t inst;
+  uint32_t nodes;  // nodes not yet reported to the instance, gathered when it is left
+  uint32_t words[2 * W + 2];
+  int32_t mail[bitset_max_team(W)];
+  alignas(16) int32_t box[bitset_max_team(W)][bits_stride<W>()];
+};
+
+__device__ __forceinline__ int32_t team_load(int32_t* a) {
+  return __hip_atomic_load(a, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint32_t team_load(uint32_t* a) {
+  return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// This wavefront has no work: wait for a sub-tree from another wavefront of the team. True with
+// its box filled, false once the whole team has finished. `held`: it has just finished a sub-tree.
+template <int W>
+__device__ __forceinline__ bool team_wait(Team<W>& t, int wave, bool held) {
+  int got = 0;
+  if (lane_id() == 0) {
+    const bool last =
+        held && __hip_atomic_fetch_add(&t.active, -1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP) == 1;
+    if (!last) {
+      // (release: the last box's flag is lowered before the bit shows)
+      __hip_atomic_fetch_or(&t.idle, 1u << wave, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      for (;;) {
+        // the flag first: `active` stays positive from before the flag is set until the sub-tree
+        // in the box is finished, so reading it as zero means that no box is being filled
+        if (team_load(&t.mail[wave])) {
+          got = 1;
+          break;
+        }
+        if (team_load(&t.active) == 0) break;
+        __builtin_amdgcn_s_sleep(2);
+      }
+      if (got) t.mail[wave] = 0;
+    }
+  }
+  return __builtin_amdgcn_readfirstlane(got);
+}
+
+// Hand the oldest entries of this wavefront's stack (`avail` of them) to idle wavefronts of the
+// team, one each; returns how many were handed over. Lane i serves wavefront i.
+template <int W>
+__device__ __forceinline__ int team_give(Team<W>& t, uint32_t idle, int avail,
+                                         const int32_t* lstack, const int32_t* gstack,
+                                         bool stack_lds, int bot_slot, int cap) {
+  const int lane = lane_id();
+  const uint32_t bit = lane < 32 ? 1u << lane : 0u;
+  bool claim = (idle & bit) && __popc(idle & (bit - 1u)) < avail;
+  if (claim)
+    claim = __hip_atomic_fetch_and(&t.idle, ~bit, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP) & bit;
+  const uint64_t mask = ballot(claim);
+  const int given = __popcll(mask);
+  if (given == 0) return 0;
+  if (lane == 0)
+    __hip_atomic_fetch_add(&t.active, given, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  if (claim) {
+    const int e = __popc(static_cast<uint32_t>(mask) & (bit - 1u));
+    bits_copy_entry<W>(t.box[lane], lstack, gstack, stack_lds, ring_slot(bot_slot, e, cap));
+    __hip_atomic_store(&t.mail[lane], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  return given;
+}
+
+// Thread 0: take work for the team. Returns 1 with the node's words in `words`, 2 with *root set
+// to an unstarted instance (its root), 0 when the launch is over, -1 when it is being stopped.
+// Queued nodes go first, then roots in instance order; an idle team looks again with exponential
+// back-off (`cap`: its longest, as a power of two of 1,024-cycle sleeps).
+template <int W>
+__device__ __forceinline__ int bits_dequeue(const Params& p, Ctrl& c, bool first, int cap,
+                                            uint32_t* words, int* root) {
+  int status = 3;
+  int polls = 0;
+  while (status == 3) {
+    uint32_t slot = 0, lap = 0;
+    status = first ? first_take(p, root)
+                   : worklist_take(p, c, (polls & 3) == 0, &slot, &lap, root);
+    if (status == 1) {
+      int wait = 0;
+      while (load_acquire(p.seq + slot) != 2u * lap + 1u) {
+        if (search_stopped(p, c)) {
+          status = -1;
+          break;
+        }
+        backoff(wait);
+      }
+      if (status == 1) {
+        const int32_t* src = p.payload + static_cast<size_t>(slot) * p.stride;
+#pragma unroll
+        for (int i = 0; i < 2 * W + 2; ++i) words[i] = static_cast<uint32_t>(src[i]);
+        store_release(p.seq + slot, 2u * (lap + 1u));
+      }
+    } else if (status == 3) {
+      const int units = 1 << (polls < cap ? polls : cap);
+      for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(16);
+      if (!first) ++polls;
+      first = false;
+    }
+  }
   return status;
 }
 
@@ -626,44 +762,68 @@ __device__ __forceinline__ int bits_report_nodes(const Params& p, int j, uint32_
 
 // Nodes between two reads of the node header (a power of two).
 constexpr uint32_t kPollNodes = 16;
+// In a team of more than one, nodes a wavefront visits between two donations to the worklist:
+// the team's own idle wavefronts are served first (team_give), and a donation costs the donor the
+// time of a few nodes. Up to kDonateMost entries go out at once, so that a tree whose side
+// branches are small still spreads. Measured (one 5-regular graph of 120 vertices / a G(200, 0.5)
+// search of 85,000 nodes), entries x interval: 1 x 8: 5.4 / 5.1 ms, 2 x 8: 4.4 / 3.7,
+// 4 x 8: 3.9 / 2.4, 4 x 2: 4.1 / 3.9, 4 x 32: 4.2 / 4.0.
+constexpr uint32_t kDonateNodes = 8;
 
 // The hybrid traversal (§IV-A, Fig. 4; termination §IV-C) on bitset nodes, over every instance
-// of the launch (as traverse_kernel).
+// of the launch (as traverse_kernel). Each wavefront of a workgroup walks its own sub-trees with
+// its own stack; the wavefronts of a workgroup (a team) share the instance's adjacency matrix and
+// pass sub-trees to each other in LDS, and the workgroup as a whole takes nodes and roots from
+// the launch's worklist when all of its wavefronts have run out.
 template <int W, bool PVC, bool PROF, bool SO>
-__global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
+__global__ void __launch_bounds__(64 * bitset_max_team(W)) bitset_traverse_kernel(Params p) {
   extern __shared__ uint64_t adj_lds[];
   __shared__ Ctrl c;
-  // 64-bit statistics, kept by lane 0 in LDS: the loop's scalar registers hold only the 32-bit
-  // counts since the last flush
+  __shared__ Team<W> team;
+  // 64-bit statistics in LDS: the loop's scalar registers hold only the 32-bit counts since the
+  // last flush
   __shared__ WgStats tally;
   const int wg = blockIdx.x;
   const int tid = threadIdx.x;
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+  const int waves = p.team;
   Rows<W> r;
   ActivityClock<PROF> clk;
   clk.begin();
   if (tid == 0) {
     watch_begin(c);
     tally = WgStats{};
+    team.nodes = 0;
   }
+  if (lane == 0) team.mail[wave] = 0;
+  auto add_tally = [](int64_t* dst, int64_t x) {
+    __hip_atomic_fetch_add(dst, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
 
   constexpr int kStride = bits_stride<W>();
-  // Lane 0 alone writes and reads stack entries, in program order, so the ring needs no
-  // barrier in LDS either.
-  // The ring lives in LDS after the adjacency matrix (stack_lds) or in device memory. The two
+  // Lane 0 alone writes and reads a wavefront's stack entries, in program order, so the ring
+  // needs no barrier in LDS either.
+  // The rings live in LDS after the adjacency matrix (stack_lds) or in device memory. The two
   // are addressed through separate pointers, each access under a uniform branch, so that LDS
   // entries are read and written with LDS instructions rather than flat ones (a flat access
   // waits for every outstanding memory operation, the node header's load included).
   const bool stack_lds = p.stack_lds != 0;
-  int32_t* const lstack = reinterpret_cast<int32_t*>(adj_lds + static_cast<size_t>(p.n_max) * W);
-  int32_t* const gstack = p.stacks + static_cast<size_t>(wg) * p.depth_cap * kStride;
-  // The stack is a ring of depth_cap entries holding [bot, top): pops take the top, donations
-  // take the bottom (the oldest deferred child, nearest its sub-tree root). Every entry belongs
-  // to the instance of the sub-tree being walked.
+  int32_t* const lstack = reinterpret_cast<int32_t*>(adj_lds + static_cast<size_t>(p.n_max) * W) +
+                          static_cast<size_t>(wave) * p.depth_cap * kStride;
+  int32_t* const gstack =
+      p.stacks + (static_cast<size_t>(wg) * waves + wave) * p.depth_cap * kStride;
+  // The stack is a ring of depth_cap entries holding [bot, top): pops take the top, handovers and
+  // donations take the bottom (the oldest deferred child, nearest its sub-tree root). Every entry
+  // belongs to the team's instance.
   int top = 0, bot = 0;
   // ring slots of top and bot, kept reduced modulo depth_cap (no division per push or pop)
   int top_slot = 0, bot_slot = 0;
   const int cap = p.depth_cap;
-  bool have = false, holding = false;
+  bool have = false;
+  bool held = false;     // this wavefront holds a sub-tree (counted in team.active)
+  bool holding = false;  // thread 0: the team holds a sub-tree of the launch (a root, a queued node)
+  bool first = true;     // the team has not looked for work yet
   int cur = -1, cur_n = 0;
   int32_t cur_k = 0, cur_vtx = 0;
   // Statistics: nodes and stack traffic are counted in 32 bits since the last flush (instance
@@ -671,10 +831,10 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
   uint32_t unreported = 0, pushes32 = 0, pops32 = 0;  // since the last flush
   const uint32_t flush_at = p.node_budget > 0 ? static_cast<uint32_t>(p.budget_chunk) : (1u << 30);
   int max_depth = 0;
-  uint32_t headers = 0;  // node headers read so far
+  uint32_t headers = 0;  // nodes since the last header, and so on (see kPollNodes)
   uint32_t so_path = 0;  // StackOnly: the current path index
-  int seen_inst = -1;    // the instance whose header was last read, and what it showed:
-  int32_t seen_best = 0; // MVC: its best (lowered by this workgroup's own covers)
+  uint32_t quiet = 0;    // nodes since this wavefront's last donation to the worklist
+  int32_t seen_best = 0; // MVC: the instance's best as this wavefront last saw it
   bool inst_done = false;  // it is answered (PVC) or out of budget
   int32_t seen_count = 0;  // worklist count at the last header
   int stop = 0;            // the launch is being stopped
@@ -692,18 +852,22 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
         ++pops32;
         clk.charge(kActAcquire);
       } else if constexpr (SO) {
-        // StackOnly (the comparison method of §V-A): no worklist. This workgroup's sub-trees
-        // are the paths wg, wg + num_wg, ... < 2^start_depth (bit d: which child at depth d);
-        // it walks each path down from the root, then walks the sub-tree with its stack. A node
-        // above the start depth counts for the instance only on the path whose remaining bits
-        // are zero, so the instance's node count is the tree's.
+        // StackOnly (the comparison method of §V-A): no worklist, one wavefront per workgroup.
+        // This workgroup's sub-trees are the paths wg, wg + num_wg, ... < 2^start_depth (bit d:
+        // which child at depth d); it walks each path down from the root, then walks the sub-tree
+        // with its stack. A node above the start depth counts for the instance only on the path
+        // whose remaining bits are zero, so the instance's node count is the tree's.
         if (cur < 0) {
           cur_n = load_adjacency<W>(p, 0, adj_lds, r);
           const Instance in = p.inst[0];
           cur = 0;
           cur_k = min(in.k, cur_n);  // a k beyond n acts as n (see reduce_bits)
           cur_vtx = in.vtx_off;
-          if (tid == 0) ++tally.instances;
+          seen_best = 0x7FFFFFFF;
+          if (tid == 0) {
+            ++tally.instances;
+            team.best = 0x7FFFFFFF;
+          }
           so_path = static_cast<uint32_t>(wg);
         } else {
           so_path += static_cast<uint32_t>(p.num_wg);
@@ -726,6 +890,7 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
             reached = false;
             break;
           }
+          if (!PVC) seen_best = min(seen_best, static_cast<int32_t>(h));
           const int32_t bound = PVC ? cur_k : static_cast<int32_t>(h) - 1;
           if (owner) ++unreported;  // counted for the instance (and the workgroup) at the flush
           else if (tid == 0) ++tally.nodes;  // a walk through a node another path owns
@@ -757,19 +922,37 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
         }
         clk.charge(kActAcquire);
         if (!reached) continue;
-      } else {
-        if (holding) {
-          if (tid == 0) release_work(p, cur);
-          holding = false;
-        }
-        const int got = bits_dequeue<W>(p, c, L, pending, inst);
-        if (got != 1 && got != 2) {
-          clk.charge(kActAcquire);
-          break;
-        }
-        holding = true;
-        if (got == 1 && tid == 0) ++tally.dequeues;
+      } else if (waves > 1 && !first && team_wait<W>(team, wave, held)) {
+        // a sub-tree from another wavefront of the team
+        held = true;
+        bits_load_lds<W>(team.box[wave], L, pending, inst);
         clk.charge(kActAcquire);
+      } else {
+        // the whole team is out of work: every wavefront of the workgroup comes here
+        held = false;
+        __syncthreads();
+        if (tid == 0) {
+          if (holding) release_work(p, cur);
+          uint32_t words[2 * W + 2];
+          int root = 0;
+          const int got = bits_dequeue<W>(p, c, first, waves > 1 ? 3 : 5, words, &root);
+          holding = got > 0;
+          team.status = got;
+          team.inst = got == 1 ? static_cast<int32_t>(words[2 * W + 1] >> kPendingBits) : root;
+          if (got == 1) {
+            ++tally.dequeues;
+#pragma unroll
+            for (int i = 0; i < 2 * W + 2; ++i) team.words[i] = words[i];
+          }
+          team.active = 1;
+          team.idle = 0;
+        }
+        __syncthreads();
+        first = false;
+        const int got = __builtin_amdgcn_readfirstlane(team.status);
+        inst = __builtin_amdgcn_readfirstlane(team.inst);
+        clk.charge(kActAcquire);
+        if (got != 1 && got != 2) break;
         if (inst < 0 || inst >= p.num_inst) {  // cannot happen: every stored node names its instance
           if (tid == 0) {
             atomicMax(ctr_i32(p, kError), 2);
@@ -777,23 +960,49 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
           }
           break;
         }
-        // a root's input check is loaded now, while the instance is being staged
+        // a root's input check and the instance's header are loaded now, while the instance is
+        // being staged
         const int32_t err_row = got == 2 ? load_relaxed(&p.ist[inst].err_row) : kNoRow;
+        const uint64_t hraw = inst_header(p, inst);
         if (inst != cur) {
-          if (tid == 0) {
-            if (cur >= 0) bits_report_nodes(p, cur, unreported);
-            tally.nodes += unreported;
-            tally.pushes += pushes32;
-            tally.pops += pops32;
-            ++tally.instances;
+          if (lane == 0) {
+            if (unreported) {
+              __hip_atomic_fetch_add(&team.nodes, unreported, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+              add_tally(&tally.nodes, unreported);
+              add_tally(&tally.pushes, pushes32);
+              add_tally(&tally.pops, pops32);
+            }
           }
           unreported = pushes32 = pops32 = 0;
-          cur_n = load_adjacency<W>(p, inst, adj_lds, r);
+          const int left = cur;
+          cur_n = load_adjacency<W>(p, inst, adj_lds, r);  // begins and ends with a barrier
+          if (tid == 0) {
+            if (left >= 0) bits_report_nodes(p, left, team.nodes);
+            team.nodes = 0;
+            ++tally.instances;
+          }
           const Instance in = p.inst[inst];
           cur = inst;
           cur_k = min(in.k, cur_n);  // a k beyond n acts as n (see reduce_bits)
           cur_vtx = in.vtx_off;
+          seen_best = 0x7FFFFFFF;
+          inst_done = false;
+          if (!PVC) {
+            if (tid == 0) team.best = 0x7FFFFFFF;
+            __syncthreads();
+          }
         }
+        const uint64_t h = uniform64(hraw);
+        const int32_t state = static_cast<int32_t>(h >> 32);
+        if ((state & kInstOutOfBudget) || (PVC && (state & kInstFound))) inst_done = true;
+        if (!PVC) seen_best = min(seen_best, static_cast<int32_t>(static_cast<uint32_t>(h)));
+        headers = 1;
+        if (wave != 0) {  // the other wavefronts wait for sub-trees of this one
+          clk.charge(kActOther);
+          continue;
+        }
+        held = true;
         if (got == 2) {
           const int rejected = __builtin_amdgcn_readfirstlane(err_row != kNoRow);
           if (rejected) {  // rejected input: no search (PVC: the instance is settled)
@@ -802,6 +1011,11 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
           }
           root_bits<W>(L, cur_n);
           pending = -1;
+        } else {
+          uint32_t words[2 * W + 2];
+#pragma unroll
+          for (int i = 0; i < 2 * W + 2; ++i) words[i] = team.words[i];
+          bits_unpack<W>(words, L, pending, inst);
         }
         clk.charge(kActOther);
       }
@@ -810,17 +1024,16 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
       have = true;
     }
 
-    // Node header, read every kPollNodes nodes (and at the first node after a switch of
-    // instance): the instance's flags and current best (one load), the worklist count for the
-    // donation test, and the launch-wide stop. These are agent-scope loads of lines every
-    // workgroup reads, so they are kept off most nodes: a stale best is only a weaker bound
-    // (MVC), a stale count only a stale filter (the reservation re-reads it), and a workgroup
-    // that answers its instance or exhausts its budget knows it at once (inst_done). The loads
-    // are issued here and waited for after the reduction, which runs meanwhile with the bound
-    // known before them: k (PVC), or the best this workgroup saw last, lowered by the covers it
-    // found since (MVC); it then continues under the fresh best. With one workgroup the two
-    // bounds always agree.
-    const bool poll = (headers++ & (kPollNodes - 1)) == 0 || seen_inst != cur;
+    // Node header, read every kPollNodes nodes (and when the team takes work): the instance's
+    // flags and current best (one load), the worklist count for the donation test, and the
+    // launch-wide stop. These are agent-scope loads of lines every workgroup reads, so they are
+    // kept off most nodes: a stale best is only a weaker bound (MVC), a stale count only a stale
+    // filter (the reservation re-reads it), and a wavefront that answers its instance or exhausts
+    // its budget knows it at once (inst_done). The loads are issued here and waited for after the
+    // reduction, which runs meanwhile with the bound known before them: k (PVC), or the best the
+    // team saw last, lowered by the covers it found since (MVC); it then continues under the
+    // fresh best. With one wavefront in the grid the two bounds always agree.
+    const bool poll = (headers++ & (kPollNodes - 1)) == 0;
     uint64_t hraw = 0;
     int32_t qraw = 0, abort_raw = 0, open_raw = 1;
     if (poll) {
@@ -828,13 +1041,15 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
       if (p.q_threshold > 0) qraw = load_relaxed(ctr_i32(p, kQCount));
       abort_raw = load_relaxed(ctr_i32(p, kAbort));
       if (PVC) open_raw = load_relaxed(ctr_i32(p, kOpen));
-      if (tid == 0 && watchdog(p, c)) abort_raw = 1;
+      if (lane == 0 && watchdog(p, c)) abort_raw = 1;
     }
-    if (seen_inst != cur) {
-      // a new instance: wait for its header before the reduction
-      seen_best = static_cast<int32_t>(static_cast<uint32_t>(uniform64(hraw)));
-      seen_inst = cur;
-      inst_done = false;
+    // the team's idle wavefronts and its best, read from LDS while the reduction runs
+    uint32_t idle_raw = 0;
+    if (waves > 1) {
+      idle_raw = team_load(&team.idle);
+      if (!PVC)
+        seen_best = min(seen_best, __builtin_amdgcn_readfirstlane(
+                                       static_cast<int>(team_load(&team.best))));
     }
     const int32_t early = PVC ? cur_k : seen_best - 1;
     reduce_bits<W>(r, L, D, adj_lds, early, p.rules);
@@ -845,11 +1060,16 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
       if ((state & kInstOutOfBudget) || (PVC && (state & kInstFound))) inst_done = true;
       if (!PVC) seen_best = min(seen_best, static_cast<int32_t>(static_cast<uint32_t>(h)));
       seen_count = __builtin_amdgcn_readfirstlane(qraw);
-      stop = __builtin_amdgcn_readfirstlane((abort_raw != 0 || open_raw == 0) ? 1 : 0);
+      stop |= __builtin_amdgcn_readfirstlane((abort_raw != 0 || open_raw == 0) ? 1 : 0);
     }
     clk.charge(kActReduce);
-    if (stop) break;
-    if (inst_done) {  // answered or out of budget: drop this node and the rest of the sub-tree
+    if (stop | static_cast<int>(inst_done)) {
+      // stopped, answered or out of budget: drop this node and the rest of the sub-tree (a
+      // stopped team ends in its next look for work, once all of its wavefronts have dropped
+      // theirs)
+      if constexpr (SO) {
+        if (stop) break;
+      }
       have = false;
       top = bot;
       top_slot = bot_slot;
@@ -858,11 +1078,13 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
 
     if (++unreported >= flush_at) {
       int spent = 0;
-      if (tid == 0) {
+      if (lane == 0) {
         if (p.node_budget > 0) spent = bits_report_nodes(p, cur, unreported);
-        tally.nodes += unreported;
-        tally.pushes += pushes32;
-        tally.pops += pops32;
+        else __hip_atomic_fetch_add(&team.nodes, unreported, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+        add_tally(&tally.nodes, unreported);
+        add_tally(&tally.pushes, pushes32);
+        add_tally(&tally.pops, pops32);
       }
       unreported = pushes32 = pops32 = 0;
       if (__builtin_amdgcn_readfirstlane(spent)) inst_done = true;
@@ -890,70 +1112,86 @@ __global__ void __launch_bounds__(64) bitset_traverse_kernel(Params p) {
       continue;
     }
     if (edges == 0) {  // a vertex cover of size |S|
-      if (!PVC && L.s < seen_best) seen_best = L.s;
+      if (!PVC && L.s < seen_best) {
+        seen_best = L.s;
+        if (lane == 0)
+          __hip_atomic_fetch_min(&team.best, static_cast<uint32_t>(L.s), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
       int won = 0;
-      if (tid == 0) won = bits_claim<PVC>(p, cur, L.s);
+      if (lane == 0) won = bits_claim<PVC>(p, cur, L.s);
       if (__builtin_amdgcn_readfirstlane(won)) {
         write_cover<W>(p.covers + cur_vtx, L, cur_n);
         __threadfence();
-        if (tid == 0) bits_publish<PVC>(p, cur, L.s);
+        if (lane == 0) bits_publish<PVC>(p, cur, L.s);
       }
-      // PVC: a cover of size <= k is recorded now, by this workgroup or another one
+      // PVC: a cover of size <= k is recorded now, by this wavefront or another one
       if (PVC) inst_done = true;
       clk.charge(kActOther);
       have = false;
       continue;
     }
 
-    // branch on v_max: defer the N(v_max) child, continue with the v_max child. While the
-    // worklist is below its threshold a deferred child is donated: the oldest one on this
-    // workgroup's stack if there is one (the largest sub-tree it holds), else this one.
-    bool kept_local = true;
-    if (p.q_threshold > 0 && seen_count < static_cast<int32_t>(p.q_threshold)) {
-      const bool from_stack = top > bot;
-      const int32_t* oldest =
-          !from_stack ? nullptr
-          : stack_lds ? lstack + bot_slot * kStride
-                      : gstack + static_cast<size_t>(bot_slot) * kStride;
-      if (bits_enqueue<W>(p, c, L, vmax, oldest, cur)) {
-        if (tid == 0) ++tally.enqueues;
-        if (from_stack) {
-          ++bot;
-          bot_slot = bot_slot + 1 == cap ? 0 : bot_slot + 1;
-        }
-        else kept_local = false;
+    // branch on v_max: defer the N(v_max) child on this wavefront's stack, continue with the v_max
+    // child. Idle wavefronts of the team take the oldest entries of the stack (the largest
+    // sub-trees it holds) first; else, while the worklist is below its threshold, some are donated.
+    if (top - bot >= p.depth_cap) {  // cannot happen: the depth bound of §IV-E holds
+      if (lane == 0) {
+        atomicMax(ctr_i32(p, kError), 1);
+        store_relaxed(ctr_i32(p, kAbort), 1);
       }
+      if constexpr (SO) break;
+      stop = 1;
+      have = false;
+      top = bot;
+      top_slot = bot_slot;
+      continue;
     }
-    if (kept_local) {
-      if (top - bot >= p.depth_cap) {  // cannot happen: the depth bound of §IV-E holds
-        if (tid == 0) {
-          atomicMax(ctr_i32(p, kError), 1);
-          store_relaxed(ctr_i32(p, kAbort), 1);
-        }
-        break;
+    if (stack_lds) bits_store<W>(lstack + top_slot * kStride, L, vmax, cur);
+    else bits_store<W>(gstack + static_cast<size_t>(top_slot) * kStride, L, vmax, cur);
+    ++top;
+    top_slot = top_slot + 1 == cap ? 0 : top_slot + 1;
+    int given = 0;
+    const uint32_t idle = waves > 1 ? __builtin_amdgcn_readfirstlane(idle_raw) : 0u;
+    ++quiet;
+    if (idle) {
+      if (!stack_lds) __threadfence_block();  // lane 0's entry, about to be read by other lanes
+      given = team_give<W>(team, idle, top - bot, lstack, gstack, stack_lds, bot_slot, cap);
+    } else if (seen_count < static_cast<int32_t>(p.q_threshold) &&
+               (waves == 1 || (top - bot > 1 && quiet >= kDonateNodes))) {
+      const int m = min(kDonateMost, (top - bot + 1) / 2);
+      if (!stack_lds) __threadfence_block();
+      if (bits_enqueue<W>(p, c, cur, m, lstack, gstack, stack_lds, bot_slot)) {
+        given = m;
+        if (lane == 0) add_tally(&tally.enqueues, m);
       }
-      if (stack_lds) bits_store<W>(lstack + top_slot * kStride, L, vmax, cur);
-      else bits_store<W>(gstack + static_cast<size_t>(top_slot) * kStride, L, vmax, cur);
-      ++top;
-      top_slot = top_slot + 1 == cap ? 0 : top_slot + 1;
-      ++pushes32;
-      if (top - bot > max_depth) max_depth = top - bot;
+      quiet = 0;
     }
+    bot += given;
+    bot_slot = ring_slot(bot_slot, given, cap);
+    if (given == 0 || top > bot) ++pushes32;
+    if (top - bot > max_depth) max_depth = top - bot;
     clk.charge(kActDonate);
     remove_vertex_bits<W>(r, L, D, vmax);
     clk.charge(kActBranch);
   }
   clk.end();
 
+  if (lane == 0) {
+    __hip_atomic_fetch_add(&team.nodes, unreported, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    add_tally(&tally.nodes, unreported);
+    add_tally(&tally.pushes, pushes32);
+    add_tally(&tally.pops, pops32);
+    __hip_atomic_fetch_max(&tally.max_depth, max_depth, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (PROF)
+      for (int a = 0; a < kNumActivities; ++a)
+        add_tally(&tally.cycles[a], static_cast<int64_t>(clk.cycles[a]));
+  }
+  __syncthreads();
   if (tid == 0) {
-    if (cur >= 0) bits_report_nodes(p, cur, unreported);
-    WgStats w = tally;
-    w.nodes += unreported;
-    w.pushes += pushes32;
-    w.pops += pops32;
-    w.max_depth = max_depth;
-    for (int a = 0; a < kNumActivities; ++a) w.cycles[a] = static_cast<int64_t>(clk.cycles[a]);
-    publish_wg_stats(p, wg, w);
+    if (cur >= 0) bits_report_nodes(p, cur, team.nodes);
+    publish_wg_stats(p, wg, tally);
   }
 }
 
@@ -1019,7 +1257,8 @@ size_t bitset_lds_bytes(int n_max, int words) { return static_cast<size_t>(n_max
 int bitset_stride(int words) { return ((2 * words + 2) + 3) & ~3; }
 
 size_t bitset_traverse_lds_bytes(const Params& p) {
-  const size_t stack = p.stack_lds ? static_cast<size_t>(p.depth_cap) * bitset_stride(p.words) * 4 : 0;
+  const size_t stack = p.stack_lds
+      ? static_cast<size_t>(p.team) * p.depth_cap * bitset_stride(p.words) * 4 : 0;
   return bitset_lds_bytes(p.n_max, p.words) + stack;
 }
 
@@ -1044,7 +1283,7 @@ hipError_t launch_bitset_traverse(bool pvc, bool prof, const Params& p, hipStrea
   void* kargs[] = {&args};
   // plain launch; see launch_traverse for why co-residency is not required
   return hipLaunchKernel(bitset_fn(p.words, pvc, prof, p.start_depth > 0), dim3(p.num_wg),
-                         dim3(64), kargs, bitset_traverse_lds_bytes(p), stream);
+                         dim3(64 * p.team), kargs, bitset_traverse_lds_bytes(p), stream);
 }
 
 hipError_t launch_bitset_reduce(const Params& p, int32_t* deg, int32_t* s, int64_t bound,
@@ -1063,9 +1302,10 @@ hipError_t launch_bitset_reduce(const Params& p, int32_t* deg, int32_t* s, int64
   return hipGetLastError();
 }
 
-hipError_t bitset_occupancy(int words, bool pvc, bool prof, size_t lds, int* blocks_per_cu) {
+hipError_t bitset_occupancy(int words, bool pvc, bool prof, int team, size_t lds,
+                            int* blocks_per_cu) {
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, bitset_fn(words, pvc, prof),
-                                                      64, lds);
+                                                      64 * team, lds);
 }
 
 }  // namespace vc

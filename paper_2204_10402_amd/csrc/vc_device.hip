@@ -879,6 +879,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   uint32_t headers = 0;  // thread 0: node headers read so far
   uint64_t root_header = 0;   // thread 0: a root's header, loaded when the root was taken
   bool header_ready = false;
+  bool first = true;          // the workgroup has not looked for work yet
 
   int32_t* stack = p.stacks + static_cast<size_t>(wg) * p.depth_cap * p.stride;
   // The stack is a ring of depth_cap entries holding [bot, top): pops take the top, donations
@@ -982,7 +983,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
           if (tid == 0) release_work(p, cur);
           holding = false;
         }
-        const int got = dequeue_begin(p, c);
+        const int got = dequeue_begin(p, c, first);
         if (got != 1 && got != 2) {
           clk.charge(kActAcquire);
           break;
@@ -1225,7 +1226,6 @@ __global__ void __launch_bounds__(256) finalize_kernel(Params p, int64_t vertice
     res->aborted = *ctr_i32(p, kAbort);
     res->error = *ctr_i32(p, kError);
     res->stop_reason = *ctr_i32(p, kStopReason);
-    res->q_max_count = *ctr_i32(p, kQMaxCount);
   }
 }
 

@@ -250,17 +250,17 @@ __device__ inline void lock_acquire(int32_t* lock) {
 // reserves, so that counter can read zero only when nothing is queued, held or unstarted
 // (it starts at the number of instances: one root each).
 
-// Thread 0 tries to reserve a slot for a donated node of instance `inst`; returns 1 with
-// c.slot/c.lap set, 0 if the worklist is at its threshold, -1 if the search is being stopped.
+// One lane tries to reserve a slot for a donated node of instance `inst`; returns 1 with
+// slot_out/lap_out set, 0 if the worklist is at its threshold, -1 if the search is being stopped.
 // The instance's and the launch's outstanding-work counters are raised first.
-__device__ inline int enqueue_reserve(const Params& p, Ctrl& c, int inst) {
+__device__ inline int enqueue_reserve(const Params& p, Ctrl& c, int inst, uint32_t& slot_out,
+                                      uint32_t& lap_out) {
   int32_t* count = ctr_i32(p, kQCount);
   const int32_t seen = load_relaxed(count);
   if (seen >= static_cast<int32_t>(p.q_threshold)) return 0;
   fetch_add(p.work + inst, 1);
   fetch_add(ctr_i32(p, kWork), 1);
-  const int32_t before = fetch_add(count, 1);  // stays below cap: threshold + 2 num_wg <= cap
-  if (before + 1 > load_relaxed(ctr_i32(p, kQMaxCount))) atomicMax(ctr_i32(p, kQMaxCount), before + 1);
+  fetch_add(count, 1);  // stays below cap: threshold + 2 * producers <= cap
   const unsigned long long t = fetch_add(ctr_u64(p, kQTail), 1ull);
   const uint32_t slot = static_cast<uint32_t>(t) & (p.q_cap - 1);
   const uint32_t lap = static_cast<uint32_t>(t / p.q_cap);
@@ -269,15 +269,15 @@ __device__ inline int enqueue_reserve(const Params& p, Ctrl& c, int inst) {
     if (search_stopped(p, c)) return -1;
     backoff(spins);
   }
-  c.slot = slot;
-  c.lap = lap;
+  slot_out = slot;
+  lap_out = lap;
   return 1;
 }
 
 // Whole workgroup: try to reserve a worklist slot for a donated node. Returns true with
 // c.slot / c.lap set; the caller then writes the node and calls enqueue_publish.
 __device__ inline bool enqueue_begin(const Params& p, Ctrl& c, int inst) {
-  if (threadIdx.x == 0) c.status = enqueue_reserve(p, c, inst);
+  if (threadIdx.x == 0) c.status = enqueue_reserve(p, c, inst, c.slot, c.lap);
   __syncthreads();
   return c.status == 1;  // at threshold, or stopping: keep the node locally
 }
@@ -289,6 +289,18 @@ __device__ inline void enqueue_publish(const Params& p, const Ctrl& c) {
   __threadfence();
   __syncthreads();
   if (threadIdx.x == 0) store_release(p.seq + slot, 2u * lap + 1u);
+}
+
+// Thread 0: the workgroup's first look for work. The first num_inst workgroups take a root ticket
+// at once; the others have nothing to find yet and look again after their first back-off. Without
+// this every workgroup of the grid read the root counter as zero when a launch began and queued
+// an atomic on it (2,048 of them ahead of a single graph's first node).
+__device__ inline int first_take(const Params& p, int32_t* root) {
+  if (static_cast<int>(blockIdx.x) >= p.num_inst) return 3;
+  const int32_t r = fetch_add(ctr_i32(p, kRootNext), 1);
+  if (r >= p.num_inst) return 3;
+  *root = r;
+  return 2;
 }
 
 // Thread 0: one look for work. Returns 1 with *slot / *lap set when it has claimed a worklist
@@ -329,14 +341,15 @@ __device__ inline int worklist_take(const Params& p, Ctrl& c, bool check_stop, u
 // caller reads the node, then calls dequeue_finish), 2 with c.slot set to an instance whose
 // search has not started (its root), 0 when the whole launch is finished, -1 when it is being
 // stopped. An idle workgroup looks again with exponential back-off, and at the stop flags every
-// fourth look.
-__device__ inline int dequeue_begin(const Params& p, Ctrl& c) {
+// fourth look. `first`: the workgroup has not looked before (see first_take); cleared here.
+__device__ inline int dequeue_begin(const Params& p, Ctrl& c, bool& first) {
   int polls = 0;
   for (;;) {
     if (threadIdx.x == 0) {
       uint32_t slot = 0, lap = 0;
       int32_t root = 0;
-      int status = worklist_take(p, c, (polls & 3) == 0, &slot, &lap, &root);
+      int status = first ? first_take(p, &root)
+                         : worklist_take(p, c, (polls & 3) == 0, &slot, &lap, &root);
       if (status == 1) {
         int wait = 0;
         while (load_acquire(p.seq + slot) != 2u * lap + 1u) {
@@ -353,10 +366,11 @@ __device__ inline int dequeue_begin(const Params& p, Ctrl& c) {
       } else if (status == 3) {
         const int units = 1 << (polls < 5 ? polls : 5);
         for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(16);
-        ++polls;
+        if (!first) ++polls;
       }
       c.status = status;
     }
+    first = false;
     __syncthreads();
     const int status = c.status;
     if (status != 3) return status;

@@ -269,6 +269,8 @@ int check_graph_args(vc_ctx* ctx, const vc_graph* g) {
 struct Plan {
   int32_t wg_size = 0;
   int32_t num_wg = 0;
+  int32_t team = 1;         // wavefronts of a workgroup that walk nodes of their own (bitsets)
+  int32_t donate = 1;       // nodes a wavefront donates at once, at most
   int32_t stride = 0;
   uint32_t cap = 0;
   uint32_t threshold = 0;
@@ -287,7 +289,7 @@ int occupancy(vc_ctx* ctx, int words, bool pvc, bool prof, int ws, size_t lds, i
     *out = it->second;
     return VC_OK;
   }
-  if (words) VC_HIP(ctx, vc::bitset_occupancy(words, pvc, prof, lds, out));
+  if (words) VC_HIP(ctx, vc::bitset_occupancy(words, pvc, prof, ws / 64, lds, out));
   else VC_HIP(ctx, vc::traverse_occupancy(pvc, prof, global_node, rp_lds, ws, lds, out));
   ctx->occupancy[key] = *out;
   return VC_OK;
@@ -307,22 +309,70 @@ int choose_words(vc_ctx* ctx, int32_t n, int32_t flags, int32_t* words) {
 
 void size_worklist(Plan& pl, const vc_options* o, uint64_t min_cap);
 
+// What a launch plan depends on.
+struct Shape {
+  int32_t n_max = 0;
+  int64_t nnz_max = 0;
+  int32_t words = 0;   // bitset words; 0: degree arrays
+  int32_t count = 1;   // instances
+  int32_t depth = 1;   // stack entries per wavefront (bitsets)
+  int32_t team = 0;    // bitsets: wavefronts per workgroup (0: chosen here)
+};
+
+// Dynamic LDS of a bitset traversal with `team` stack rings of `depth` entries in LDS.
+size_t bitset_team_lds(const Shape& sh, int32_t team) {
+  return vc::bitset_lds_bytes(sh.n_max, sh.words) +
+         static_cast<size_t>(team) * sh.depth * vc::bitset_stride(sh.words) * 4;
+}
+
 // Workgroup size and count for one launch (paper §IV-E, adapted): a power-of-two workgroup of
 // about n_max/4 threads; as many workgroups as can be resident at once, fewer if their stacks
-// do not fit in device memory (size_stacks).
-int plan_launch(vc_ctx* ctx, bool pvc, int32_t n_max, int64_t nnz_max, int32_t words,
-                const vc_options* o, Plan& pl) {
+// do not fit in device memory (size_stacks). The bitset kernels walk one node per wavefront:
+// their workgroups are teams of wavefronts.
+int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Plan& pl) {
+  const int32_t n_max = sh.n_max, words = sh.words;
+  const int64_t nnz_max = sh.nnz_max;
   const bool prof = o && (o->flags & VC_OPT_PROFILE);
   const int cus = ctx->prop.multiProcessorCount;
   int best_ws = 0, best_occ = 0, rc;
   if (words) {
-    // one wavefront per workgroup; the adjacency matrix (n_max * words * 8 bytes) in LDS
     pl.stride = vc::bitset_stride(words);
-    pl.lds = vc::bitset_lds_bytes(n_max, words);
-    best_ws = 64;
     if (o && o->wg_size && o->wg_size != 64)
       return fail(ctx, VC_ERR_INVALID_ARG, "the bitset kernels use 64-thread workgroups");
-    if ((rc = occupancy(ctx, words, pvc, prof, 64, pl.lds, n_max, &best_occ))) return rc;
+    // The team: eight wavefronts (four for more than four words, whose kernels hold up to 256
+    // registers) as long as their stack rings fit in LDS beside the adjacency matrix (within the
+    // default 64 KB) and there is a workgroup for every instance: an instance occupies one
+    // workgroup, so with more instances than workgroups smaller teams leave fewer wavefronts
+    // idle. One wavefront where the caller asks for 64-thread workgroups, for no donations (each
+    // workgroup then walks its whole sub-tree in depth-first order), or for StackOnly.
+    const bool alone = o && (o->wg_size == 64 || o->wl_threshold == -1 ||
+                             (o->flags & VC_OPT_STACK_ONLY));
+    int32_t team = alone ? 1 : sh.team ? sh.team : std::min(8, vc::bitset_max_team(words));
+    if (!alone && !sh.team)
+      while (team > 1 && bitset_team_lds(sh, team) > 65536) team /= 2;
+    for (;; team /= 2) {
+      const size_t lds = bitset_team_lds(sh, team);
+      const bool in_lds = lds <= 65536;
+      pl.lds = in_lds ? lds : vc::bitset_lds_bytes(n_max, words);
+      best_ws = 64 * team;
+      if ((rc = occupancy(ctx, words, pvc, prof, best_ws, pl.lds, n_max, &best_occ))) return rc;
+      pl.num_wg = best_occ * cus;
+      // Untuned, at most 16 wavefronts per CU in teams, and eight in workgroups of one: idle
+      // workgroups beyond that only add polling on the worklist counters in small searches.
+      if (!(o && o->num_wg > 0) && !sh.team)
+        pl.num_wg = std::min(pl.num_wg, cus * (team > 1 ? std::max(1, 16 / team) : 8));
+      if (o && o->grid_share > 0) pl.num_wg = std::max(1, pl.num_wg / o->grid_share);
+      if (o && o->num_wg > 0) pl.num_wg = std::min(pl.num_wg, o->num_wg);
+      if (best_occ < 1 && team > 1) continue;
+      if (team == 1 || sh.team || pl.num_wg >= sh.count) break;
+    }
+    if (best_occ < 1)
+      return fail(ctx, VC_ERR_INVALID_ARG, "traversal kernel cannot be resident at this size");
+    pl.team = team;
+    pl.donate = vc::kDonateMost;
+    pl.wg_size = best_ws;
+    size_worklist(pl, o, 4096);
+    return VC_OK;
   } else {
     pl.stride = vc::array_stride(n_max);
     pl.lds = vc::node_lds_bytes(pl.stride, n_max, 0, 0);
@@ -382,10 +432,6 @@ int plan_launch(vc_ctx* ctx, bool pvc, int32_t n_max, int64_t nnz_max, int32_t w
     return fail(ctx, VC_ERR_INVALID_ARG, "traversal kernel cannot be resident at this size");
   pl.wg_size = best_ws;
   pl.num_wg = best_occ * cus;
-  // Untuned, at most eight one-wavefront workgroups per CU: idle workgroups beyond that only
-  // add polling on the worklist counters in small searches. The autotuner also tries 12 and 16,
-  // which large searches use well (the hard MVC batch: 400 -> 460 million nodes/s at 16).
-  if (words && !(o && o->num_wg > 0)) pl.num_wg = std::min(pl.num_wg, 8 * cus);
   if (o && o->grid_share > 0) pl.num_wg = std::max(1, pl.num_wg / o->grid_share);
   if (o && o->num_wg > 0) pl.num_wg = std::min(pl.num_wg, o->num_wg);
 
@@ -395,19 +441,21 @@ int plan_launch(vc_ctx* ctx, bool pvc, int32_t n_max, int64_t nnz_max, int32_t w
 
 // Worklist capacity and donation threshold (§IV-A) for pl.num_wg workgroups, at least
 // `min_cap` entries unless the caller chose the capacity. A producer only reserves a slot after
-// reading fewer than `threshold` reserved entries; at most num_wg producers can be past that
-// check at once, and consumers giving back a lost reservation can hide at most num_wg more, so
-// threshold + 2 * num_wg <= cap keeps every reservation inside the ring.
+// reading fewer than `threshold` reserved entries; at most one producer per team wavefront can be
+// past that check at once, each with up to pl.donate nodes, and consumers giving back a lost
+// reservation can hide at most num_wg more, so threshold + (donate + 1) * producers <= cap keeps
+// every reservation inside the ring.
 void size_worklist(Plan& pl, const vc_options* o, uint64_t min_cap) {
+  const uint64_t producers = static_cast<uint64_t>(pl.num_wg) * pl.team;
   uint64_t cap = o && o->wl_capacity ? static_cast<uint64_t>(o->wl_capacity)
                                      : std::max<uint64_t>(8ull * pl.num_wg, min_cap);
-  cap = std::max<uint64_t>(cap, 4ull * pl.num_wg);
+  cap = std::max<uint64_t>(cap, 2ull * (pl.donate + 1) * producers);
   pl.cap = next_pow2(cap);
   uint64_t thr;
   if (o && o->wl_threshold == -1) thr = 0;
   else if (o && o->wl_threshold > 0) thr = static_cast<uint64_t>(o->wl_threshold);
   else thr = std::max<uint64_t>(64, static_cast<uint64_t>(pl.num_wg) / 4);
-  thr = std::min<uint64_t>(thr, pl.cap - 2ull * static_cast<uint64_t>(pl.num_wg));
+  thr = std::min<uint64_t>(thr, pl.cap - (pl.donate + 1) * producers);
   pl.threshold = static_cast<uint32_t>(thr);
 }
 
@@ -422,7 +470,7 @@ int fit_plan_to_workspace(vc_ctx* ctx, Plan& pl, const vc_options* o, int32_t wo
   auto need = [&](const Plan& q) {
     size_t b = al(q.cap * stride_b) + al(q.cap * sizeof(uint32_t)) +
                al(static_cast<size_t>(q.num_wg) * sizeof(vc::WgStats)) +
-               al(static_cast<size_t>(depth) * stride_b);
+               al(static_cast<size_t>(depth) * q.team * stride_b);
     if (words) b += al(static_cast<size_t>(vertices) * words * sizeof(uint64_t));
     if (q.global_node)
       b += al(static_cast<size_t>(std::max<int64_t>(q.num_wg, std::min<int64_t>(count, 65535))) *
@@ -446,7 +494,7 @@ int fit_plan_to_workspace(vc_ctx* ctx, Plan& pl, const vc_options* o, int32_t wo
 // Shrink the grid so that num_wg stacks of depth_cap nodes fit in free device memory
 // (§IV-E: the stacks bound the number of workgroups), then make sure they are allocated.
 int size_stacks(vc_ctx* ctx, Plan& pl, int32_t depth_cap) {
-  const size_t per_wg = static_cast<size_t>(depth_cap) * pl.stride * sizeof(int32_t);
+  const size_t per_wg = static_cast<size_t>(depth_cap) * pl.team * pl.stride * sizeof(int32_t);
   if (per_wg * static_cast<size_t>(pl.num_wg) <= ctx->stacks.bytes) return VC_OK;
   size_t avail = 0;
   if (ctx->ws) {
@@ -673,8 +721,20 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
   const int cus = ctx->prop.multiProcessorCount;
 
   // Everything of one launch group up to (and, if `final`, including) the cover check, with
-  // the knobs of `go` and, if thr_div > 0, a donation threshold of num_wg / thr_div.
-  auto run_group = [&](int32_t gi, const vc_options* go, int thr_div, bool final) -> int {
+  // the knobs of `go` and, if thr_div > 0, a donation threshold of num_wg / thr_div; `team`: the
+  // bitset kernels' wavefronts per workgroup (0: the plan's choice).
+  auto shape = [&](const Group& g, int32_t team) {
+    Shape sh;
+    sh.n_max = g.n_max;
+    sh.nnz_max = g.nnz_max;
+    sh.words = g.words;
+    sh.count = g.end - g.begin;
+    // the stack depth of a bitset launch, as set below
+    sh.depth = (o && o->stack_depth > 0) ? o->stack_depth : pvc ? g.k_max + 1 : std::max(g.n_max, 1);
+    sh.team = team;
+    return sh;
+  };
+  auto run_group = [&](int32_t gi, const vc_options* go, int thr_div, int team, bool final) -> int {
     Group& g = groups[gi];
     vc_ctx* lc = lane(gi);
     const hipStream_t gst = lc->stream;
@@ -688,11 +748,14 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       shared.grid_share = std::max(shared.grid_share, 1) * (g.words ? 2 : 3);
       go = &shared;
     }
-    if ((rc2 = plan_launch(ctx, pvc, g.n_max, g.nnz_max, g.words, go, g.pl))) return rc2;
+    g.pl = Plan{};
+    if ((rc2 = plan_launch(ctx, pvc, shape(g, team), go, g.pl))) return rc2;
     Plan& pl = g.pl;
     if (thr_div > 0)
       pl.threshold = static_cast<uint32_t>(std::min<int64_t>(
-          std::max<int64_t>(16, pl.num_wg / thr_div), static_cast<int64_t>(pl.cap) - 2 * pl.num_wg));
+          std::max<int64_t>(16, pl.num_wg / thr_div),
+          static_cast<int64_t>(pl.cap) -
+              (pl.donate + 1ll) * pl.num_wg * pl.team));
     if (ctx->ws) {
       // the stack depth this launch will use (see below), then a plan that fits
       const int32_t d = (o && o->stack_depth > 0) ? o->stack_depth
@@ -727,10 +790,11 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     p.wg_stats = static_cast<vc::WgStats*>(lc->wg_stats.ptr);
     p.node_budget = o ? o->node_budget : 0;
     // report often enough that the whole grid overshoots a budget by at most about half
-    p.budget_chunk = std::max<int64_t>(1, std::min<int64_t>(1024, p.node_budget / (2 * pl.num_wg)));
+    p.budget_chunk = std::max<int64_t>(1, std::min<int64_t>(1024, p.node_budget / (2ll * pl.num_wg * pl.team)));
     p.q_cap = pl.cap;
     p.q_threshold = pl.threshold;
     p.num_wg = pl.num_wg;
+    p.team = pl.team;
     p.bits = g.words ? static_cast<uint64_t*>(lc->bits.ptr) : nullptr;
     p.words = g.words;
     p.rp_lds = pl.rp_lds;
@@ -797,7 +861,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       p.stack_lds = 1;
       const size_t lds = vc::bitset_traverse_lds_bytes(p);
       int occ = 0;
-      if (lds <= 65536 && (rc2 = occupancy(ctx, g.words, pvc, prof, 64, lds, g.n_max, &occ)))
+      if (lds <= 65536 && (rc2 = occupancy(ctx, g.words, pvc, prof, pl.wg_size, lds, g.n_max, &occ)))
         return rc2;
       if (static_cast<int64_t>(occ) * ctx->prop.multiProcessorCount < pl.num_wg) p.stack_lds = 0;
     }
@@ -832,7 +896,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     const int32_t gi = use_aux ? (step == 0 ? ng - 1 : step - 1) : step;
     Group& g = groups[gi];
     vc_options go = o ? *o : vc_options{};
-    int thr_div = 0;
+    int thr_div = 0, team = 0;
     if (autotune) {
       auto lg = [](int64_t x) { int l = 0; while ((int64_t(1) << l) < x) ++l; return l; };
       const auto key = std::make_tuple(g.words, pvc ? 1 : 0, flags & ~VC_OPT_AUTOTUNE, lg(g.n_max),
@@ -840,16 +904,19 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       auto it = ctx->tuned.find(key);
       if (it == ctx->tuned.end()) {
         // trial launches over a small grid; the default knobs are one of the candidates
-        std::vector<std::tuple<int, int, int>> cand;  // (wg_size, num_wg, threshold divisor)
+        // (wg_size or, for bitsets, the team; num_wg; threshold divisor)
+        std::vector<std::tuple<int, int, int>> cand;
         cand.emplace_back(0, 0, 0);
         if (g.words) {
-          // up to 16 one-wavefront workgroups per CU (the default plan stops at 8; 20 to 28 per
-          // CU measured slower on the hard MVC batch: more workgroups polling the worklist)
-          for (int mult : {1, 2, 4, 8, 12, 16})
-            for (int div : {8, 2}) cand.emplace_back(0, mult * cus, div);
+          // 8 to 32 wavefronts per CU in teams of up to 16, and workgroups of one wavefront
+          for (const auto& tw : {std::make_pair(16, 1), std::make_pair(8, 1), std::make_pair(8, 2),
+                                 std::make_pair(8, 3), std::make_pair(4, 4), std::make_pair(1, 8),
+                                 std::make_pair(1, 16)})
+            if (tw.first <= vc::bitset_max_team(g.words))
+              for (int div : {8, 2}) cand.emplace_back(tw.first, tw.second * cus, div);
         } else {
           Plan base;
-          if ((rc = plan_launch(ctx, pvc, g.n_max, g.nnz_max, 0, &go, base))) return rc;
+          if ((rc = plan_launch(ctx, pvc, shape(g, 0), &go, base))) return rc;
           // and, for fewer instances than the grid holds, one workgroup per instance (no idle
           // workgroups polling the worklist; donations then have no takers but for finished
           // instances' workgroups)
@@ -864,7 +931,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
         std::tuple<int, int, int> best = cand[0];
         for (const auto& c : cand) {
           vc_options t = go;
-          t.wg_size = std::get<0>(c);
+          if (!g.words) t.wg_size = std::get<0>(c);
           t.num_wg = std::get<1>(c);
           // two trial launches per candidate, the faster one counts (one launch's noise is as
           // large as the differences that matter)
@@ -872,7 +939,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
           bool fits = true;
           for (int trial = 0; trial < 2 && fits; ++trial) {
             if ((rc = reset_group(gi))) return rc;
-            rc = run_group(gi, &t, std::get<2>(c), false);
+            rc = run_group(gi, &t, std::get<2>(c), g.words ? std::get<0>(c) : 0, false);
             if (rc == VC_ERR_INVALID_ARG || rc == VC_ERR_NO_MEMORY) {  // does not fit
               fits = false;
               break;
@@ -893,11 +960,12 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
         it = ctx->tuned.emplace(key, best).first;
         if ((rc = reset_group(gi))) return rc;
       }
-      go.wg_size = std::get<0>(it->second);
+      if (g.words) team = std::get<0>(it->second);
+      else go.wg_size = std::get<0>(it->second);
       go.num_wg = std::get<1>(it->second);
       thr_div = std::get<2>(it->second);
     }
-    if ((rc = run_group(gi, &go, thr_div, true))) return rc;
+    if ((rc = run_group(gi, &go, thr_div, team, true))) return rc;
   }
   if (use_aux) {  // the degree-array launch and its cover check end before the copy out
     VC_HIP(ctx, hipEventRecord(ctx->ev[2 * ng + 3], ctx->aux->stream));
@@ -1250,14 +1318,20 @@ int workspace_need(vc_ctx* ctx, int32_t count, const int32_t* n, const int32_t* 
     size_t best = 0;
     for (bool pvc : {false, true}) {
       Plan pl;
-      int rc = plan_launch(ctx, pvc, f.n_max, f.nnz_max, words, o, pl);
-      if (rc) return rc;
-      const size_t stride_b = static_cast<size_t>(pl.stride) * sizeof(int32_t);
       int64_t d = depth > 0 ? depth : static_cast<int64_t>(f.n_max) + 1;
       if (o && o->stack_depth > 0) d = o->stack_depth;
+      Shape sh;
+      sh.n_max = f.n_max;
+      sh.nnz_max = f.nnz_max;
+      sh.words = words;
+      sh.count = f.count;
+      sh.depth = static_cast<int32_t>(d);
+      int rc = plan_launch(ctx, pvc, sh, o, pl);
+      if (rc) return rc;
+      const size_t stride_b = static_cast<size_t>(pl.stride) * sizeof(int32_t);
       size_t need = al(pl.cap * stride_b) + al(pl.cap * sizeof(uint32_t)) +
                     al(static_cast<size_t>(pl.num_wg) * sizeof(vc::WgStats)) +
-                    al(static_cast<size_t>(pl.num_wg) * static_cast<size_t>(d) * stride_b);
+                    al(static_cast<size_t>(pl.num_wg) * pl.team * static_cast<size_t>(d) * stride_b);
       if (words) need += al(static_cast<size_t>(f.vertices) * words * sizeof(uint64_t));
       if (pl.global_node)
         need += al(static_cast<size_t>(std::max<int64_t>(pl.num_wg, std::min(f.count, 65535))) *
@@ -1286,7 +1360,11 @@ int setup_single(vc_ctx* ctx, const vc_graph* g, int rules, int32_t flags, uint8
   Plan pl;
   vc_options o{};
   o.flags = flags & (VC_OPT_GLOBAL_NODES | VC_OPT_CSR_GLOBAL);
-  if ((rc = plan_launch(ctx, false, g->n, g->nnz, words, &o, pl))) return rc;
+  Shape sh;
+  sh.n_max = g->n;
+  sh.nnz_max = g->nnz;
+  sh.words = words;
+  if ((rc = plan_launch(ctx, false, sh, &o, pl))) return rc;
   const MetaLayout L = meta_layout(1, 1, 0);
   if ((rc = ensure(ctx, ctx->meta, L.dev_end))) return rc;
   if ((rc = ensure_pinned(ctx, L.host_end))) return rc;

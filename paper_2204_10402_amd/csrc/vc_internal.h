@@ -39,9 +39,8 @@ enum CounterSlot : int {
   kOpen = 5,       // int32: PVC: instances still without a cover (0 stops every workgroup)
   kAbort = 6,      // int32: non-zero stops every workgroup (internal error)
   kError = 7,      // int32: internal error code (1 = stack overflow, 2 = node of no instance)
-  kQMaxCount = 8,  // int32: largest worklist count seen by a producer
-  kStopReason = 9, // int32: why the launch was stopped from outside the search (kStop*)
-  kNumCounters = 10,
+  kStopReason = 8, // int32: why the launch was stopped from outside the search (kStop*)
+  kNumCounters = 9,
 };
 
 // Reasons a launch stops before its search ends, other than an internal error.
@@ -137,10 +136,11 @@ struct Params {
   DevResult* res;       // launch result block: every workgroup adds its statistics at exit
   int64_t node_budget;  // per instance; 0 = none
   int64_t budget_chunk; // nodes a workgroup visits between two reports to its instance
-  uint32_t q_cap;       // power of two, >= q_threshold + 2 * num_wg
+  uint32_t q_cap;       // power of two, >= q_threshold + (kDonateMost + 1) * (wavefronts)
   uint32_t q_threshold; // donate while count < threshold (0 = never)
   int32_t depth_cap;
   int32_t num_wg;
+  int32_t team;         // bitset kernels: wavefronts per workgroup
   uint64_t* bits;       // bitset kernels: adjacency rows, words per launch-local vertex
   int32_t words;        // bitset kernels: words per row of this launch; 0 = degree arrays
   int32_t rp_lds;       // degree-array kernels: 1 = copy the instance's row_ptr into LDS after
@@ -183,9 +183,9 @@ struct DevResult {
   int32_t aborted;
   int32_t error;
   int32_t max_depth;
-  int32_t q_max_count;
   int32_t active_wgs;   // workgroups that took any work (only they add their statistics)
   int32_t stop_reason;  // kStopHost / kStopTimeout, 0 if the launch was not stopped from outside
+  int32_t pad;
   int64_t nodes;
   int64_t wg_nodes_max;
   int64_t wg_nodes_min;
@@ -229,8 +229,14 @@ hipError_t launch_bitset_greedy(const Params& p, hipStream_t stream);
 hipError_t launch_bitset_traverse(bool pvc, bool prof, const Params& p, hipStream_t stream);
 hipError_t launch_bitset_reduce(const Params& p, int32_t* deg, int32_t* s, int64_t bound,
                                 hipStream_t stream);
-// Resident workgroups per CU of a bitset traversal launch with `lds` bytes of dynamic LDS.
-hipError_t bitset_occupancy(int words, bool pvc, bool prof, size_t lds, int* blocks_per_cu);
+// Resident workgroups per CU of a bitset traversal launch of `team` wavefronts per workgroup
+// with `lds` bytes of dynamic LDS.
+hipError_t bitset_occupancy(int words, bool pvc, bool prof, int team, size_t lds,
+                            int* blocks_per_cu);
+// Stack entries a wavefront of the bitset traversal donates to the worklist at once, at most.
+constexpr int kDonateMost = 4;
+// Largest team (wavefronts per workgroup) of the bitset traversal kernels of `words` words.
+__host__ __device__ constexpr int bitset_max_team(int words) { return words <= 3 ? 16 : (words == 4 ? 8 : 4); }
 // Dynamic LDS of the bitset kernels: the adjacency matrix (and, for a traversal launch with
 // stack_lds, the stack ring after it).
 size_t bitset_lds_bytes(int n_max, int words);

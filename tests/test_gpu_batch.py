@@ -237,3 +237,24 @@ def test_autotuned_batches_keep_answers(torch_cuda, oracle_lib):
         assert fixed.stats["num_wg"] <= 5 and fixed.size.tolist() == first.size.tolist()
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("count,team", [(40, 8), (700, 4), (1500, 2), (2500, 1)])
+def test_bitset_team_sizes(solver, oracle_lib, count, team):
+    """The wavefronts per workgroup follow the number of instances (a workgroup holds one instance
+    at a time); the tree of a PVC-no answer is the oracle's node for node with every team size, so
+    no sub-tree is lost or walked twice in a handover. Whole numbers: no tolerance."""
+    base = [G.erdos_renyi(20 + 9 * i, 3.2 / (20 + 9 * i) + 0.02, 70 + i) for i in range(12)]
+    taus = [oracle.mvc(g).size for g in base]
+    want = [oracle.pvc(g, max(t - 1, 0)).nodes for g, t in zip(base, taus)]
+    gs = [base[i % 12] for i in range(count)]
+    res = solver.pvc_batch(gs, [max(taus[i % 12] - 1, 0) for i in range(count)])
+    assert (res.status == 0).all() and not res.yes.any()
+    assert res.nodes.tolist() == [want[i % 12] for i in range(count)]
+    one = [g for g in gs if g.n <= 64]  # one kernel family
+    r1 = solver.pvc_batch(one, [max(taus[base.index(g)] - 1, 0) for g in one])
+    assert r1.nodes.tolist() == [want[base.index(g)] for g in one]
+    mv = solver.mvc_batch(gs)
+    assert mv.size.tolist() == [taus[i % 12] for i in range(count)]
+    alone = solver.mvc_batch([base[4]] * count)
+    assert alone.stats["wg_size"] == 64 * team and set(alone.size.tolist()) == {taus[4]}
