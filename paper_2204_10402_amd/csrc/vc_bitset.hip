@@ -657,9 +657,9 @@ __device__ __forceinline__ int team_give(Team<W>& t, uint32_t idle, int avail,
 // Thread 0: take work for the team. Returns 1 with the node's words in `words`, 2 with *root set
 // to an unstarted instance (its root), 0 when the launch is over, -1 when it is being stopped.
 // Queued nodes go first, then roots in instance order; an idle team looks again with exponential
-// back-off (`cap`: its longest, as a power of two of 1,024-cycle sleeps).
+// back-off.
 template <int W>
-__device__ __forceinline__ int bits_dequeue(const Params& p, Ctrl& c, bool first, int cap,
+__device__ __forceinline__ int bits_dequeue(const Params& p, Ctrl& c, bool first,
                                             uint32_t* words, int* root) {
   int status = 3;
   int polls = 0;
@@ -683,8 +683,7 @@ __device__ __forceinline__ int bits_dequeue(const Params& p, Ctrl& c, bool first
         store_release(p.seq + slot, 2u * (lap + 1u));
       }
     } else if (status == 3) {
-      const int units = 1 << (polls < cap ? polls : cap);
-      for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(16);
+      idle_sleep(p, polls);
       if (!first) ++polls;
       first = false;
     }
@@ -935,7 +934,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W)) bitset_traverse_kerne
           if (holding) release_work(p, cur);
           uint32_t words[2 * W + 2];
           int root = 0;
-          const int got = bits_dequeue<W>(p, c, first, waves > 1 ? 3 : 5, words, &root);
+          const int got = bits_dequeue<W>(p, c, first, words, &root);
           holding = got > 0;
           team.status = got;
           team.inst = got == 1 ? static_cast<int32_t>(words[2 * W + 1] >> kPendingBits) : root;

@@ -54,98 +54,87 @@ constexpr int32_t kDegMask = 0x1FFFFFFF;  // degree bits of a live entry
 // ---- node operations on the LDS degree array -------------------------------------------------
 // st[0..n) degrees (negative = in the cover), st[n] = s, st[n+1] = pending vertex (-1 = none).
 
-// Entries of the removal list: the vertices one removal step takes out, gathered from every
-// wavefront's part of the node so that the wavefronts can share their rows evenly.
-constexpr int kListCap = 1024;
-// Workgroups of fewer wavefronts than this skip the removal list (one or two wavefronts have
-// little to balance, and the list's append and read-back lengthen every removal step).
-constexpr int kListWaves = 4;
-
+// The node operations work on a node and three lists in LDS, rings of cap = mask + 1 entries
+// (at least 32 per wavefront of the workgroup):
+//  - rm: the vertices marked since the last removal step;
+//  - one, two: the vertices of degree one, and of degree two not marked kNoTri, as the last
+//    refresh_lists found them.
+// After each removal step one scan of the node (refresh_lists) finds the candidates of both rules
+// and the largest degree; the rule passes then work on packed candidates, and a rule without a
+// candidate costs nothing. A list that overflows is not used: that pass scans for itself.
 struct Node {
   int32_t* st;
   int n;
   const int32_t* __restrict__ rp;
   const int32_t* __restrict__ ci;
-  int32_t* list;   // kListCap LDS words: the removal list
-  int32_t* heads;  // 64 LDS words per wavefront for walk_rows
+  int32_t* rm;    // cap entries; `one` and `two` follow
+  uint32_t mask;
+  bool spread;    // long rows: a removal step's rows go to the wavefronts in turn
+  __device__ int32_t* one() const { return rm + mask + 1; }
+  __device__ int32_t* two() const { return rm + 2 * (mask + 1); }
 };
 
-// Inclusive max-scan over the 64 lanes (DPP, as wave_incl_scan), identity -1.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int32_t dpp_or_minus1(int32_t x) {
-  return __builtin_amdgcn_update_dpp(-1, x, CTRL, ROW_MASK, 0xF, false);
-}
-__device__ __forceinline__ int32_t wave_incl_max(int32_t x) {
-  x = max(x, dpp_or_minus1<0x111, 0xF>(x));
-  x = max(x, dpp_or_minus1<0x112, 0xF>(x));
-  x = max(x, dpp_or_minus1<0x114, 0xF>(x));
-  x = max(x, dpp_or_minus1<0x118, 0xF>(x));
-  x = max(x, dpp_or_minus1<0x142, 0xA>(x));
-  x = max(x, dpp_or_minus1<0x143, 0xC>(x));
-  return x;
-}
+// Where the lists' current entries lie (their tails grow in Ctrl), and the largest degree at the
+// last refresh, an upper bound until the next. The same in every thread of the workgroup.
+struct Front {
+  uint32_t rm;             // marked vertices already removed end here
+  uint32_t one, one_end;
+  uint32_t two, two_end;
+  int32_t most;
+  uint32_t turn;           // refreshes so far
+};
 
-// Rows longer than this are walked in 64-entry pieces; shorter ones are packed together.
-constexpr int kLongRow = 64;
+// Rows longer than this are walked in 64-entry pieces by the whole wavefront; shorter ones by
+// their own lane.
+constexpr int kLaneRow = 16;
+// Entries a walk hands on at once, per lane.
+constexpr int kWalk = 4;
 
-// Walk the CSR rows [beg, end) held by the lanes of a wavefront (empty where beg >= end).
-// fn(x, tag, j) runs for every entry x = ci[j], with `tag` the value the row's owner lane
-// passed in; it runs in divergent code. `heads` is this wavefront's 64 LDS words.
-//  - Rows of at most kLongRow entries are walked as one list, 64 consecutive entries per step,
-//    so many short rows fill one step and neighbouring lanes read neighbouring entries. The
-//    owner of each entry of a step comes from head flags: every row writes its lane into
-//    `heads` at its first position in the step, and a max-scan over the lanes carries it
-//    forward. Eight steps are issued together, with unconditional loads (an index past the
-//    list reads entry 0, whose value is discarded).
-//  - Longer rows are cut into 64-entry pieces that the whole wavefront walks one after
-//    another, eight pieces per round, with the cursor (row bounds, tag, position) in scalar
-//    registers: a piece needs no owner lookup.
+// One batch of walked entries: entry u of this lane is xs[u], of the row with tag tags[u], where
+// ok[u] (a valid vertex of some row otherwise).
+struct Walked {
+  int xs[kWalk];
+  bool ok[kWalk];
+  int tags[kWalk];
+};
+
+// Walk the CSR rows [beg, end) held by the lanes of a wavefront (empty where beg >= end; at least
+// one lane holds an entry). fn(batch) runs, in uniform control flow, for batches of kWalk entries
+// per lane, each with the `tag` of its row's owner lane. A batch's loads are issued before the
+// first is used, and fn does the same with the accesses that depend on them. Rows of up to
+// kLaneRow entries are read by their own lane, kWalk entries at a time; longer rows are cut into
+// 64-entry pieces that the whole wavefront reads, kWalk pieces at a time, with the cursor (row
+// bounds, tag, position) in scalar registers.
+// A root's reduction runs on one CU, whose four SIMDs issue one wavefront instruction a cycle
+// between them, and a large root walks 10^5 entries: the walk is bound by instructions per entry
+// (and, in small frontiers, by the latency of its chain). So loads are unconditional, with the
+// index clamped into the row, a piece's address is a scalar base plus the lane, and nothing is
+// looked up per entry.
 template <typename Fn>
-__device__ __forceinline__ void walk_rows(const int32_t* __restrict__ ci, int32_t* heads, int beg,
-                                          int end, int tag, Fn fn) {
+__device__ __forceinline__ void walk_rows(const int32_t* __restrict__ ci, int beg, int end, int tag,
+                                          Fn fn) {
   const int lane = lane_id();
-  const int full = end > beg ? end - beg : 0;
-  const bool longrow = full > kLongRow;
-  const int len = longrow ? 0 : full;
-  const int incl = wave_incl_scan(len);
-  const int excl = incl - len;
-  const int total = __builtin_amdgcn_readlane(incl, 63);
-  constexpr int kUnroll = 8;
-  for (int t0 = 0; t0 < total; t0 += 64 * kUnroll) {
-    int xs[kUnroll], tags[kUnroll], js[kUnroll];
-    bool ok[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      ok[u] = false;
-      const int s0 = t0 + u * 64;
-      if (s0 < total) {  // uniform: only as many steps as the rows need
-        heads[lane] = -1;
-        __builtin_amdgcn_wave_barrier();
-        if (len > 0 && excl < s0 + 64 && incl > s0) heads[excl > s0 ? excl - s0 : 0] = lane;
-        __builtin_amdgcn_wave_barrier();
-        const int i = wave_incl_max(heads[lane]);  // owner of entry s0 + lane
-        __builtin_amdgcn_wave_barrier();
-        const int t = s0 + lane;
-        const int src = i < 0 ? 0 : i;  // i < 0 only past the end of the list
-        const int ob = shfl(beg, src);
-        const int oe = shfl(excl, src);
-        tags[u] = shfl(tag, src);
-        ok[u] = t < total;
-        js[u] = ok[u] ? ob + (t - oe) : 0;
-        xs[u] = ci[js[u]];  // not read until every step has issued
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      if (ok[u]) fn(xs[u], tags[u], js[u]);
-  }
+  const bool longrow = end - beg > kLaneRow;
   uint64_t longs = __builtin_amdgcn_ballot_w64(longrow);
+  const int stop = longrow ? beg : max(beg, end);
+  const int last = max(stop - 1, 0);
+  int at = beg;
+  while (__builtin_amdgcn_ballot_w64(at < stop)) {
+    Walked w;
+#pragma unroll
+    for (int u = 0; u < kWalk; ++u) {
+      w.ok[u] = at + u < stop;
+      w.tags[u] = tag;
+      w.xs[u] = ci[min(at + u, last)];
+    }
+    at += kWalk;
+    fn(w);
+  }
   int rb = 0, re = 0, rt = 0;  // the piece cursor: next entry, end and tag of the current row
   while (longs || rb < re) {
-    int xs[8], js[8], ts[8];
-    bool ok[8];
+    Walked w;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kWalk; ++u) {
       if (rb >= re && longs) {
         const int o = first_lane(longs);
         longs &= longs - 1;
@@ -153,147 +142,240 @@ __device__ __forceinline__ void walk_rows(const int32_t* __restrict__ ci, int32_
         re = __builtin_amdgcn_readlane(end, o);
         rt = __builtin_amdgcn_readlane(tag, o);
       }
-      js[u] = rb + lane;
-      ok[u] = js[u] < re;
-      ts[u] = rt;
-      xs[u] = ok[u] ? ci[js[u]] : 0;
+      const int left = re - rb;  // <= 0 once the rows have run out: entry 0 of the last one, unused
+      const int32_t* piece = ci + (left > 0 ? rb : re - 1);
+      w.ok[u] = lane < left;
+      w.tags[u] = rt;
+      w.xs[u] = piece[static_cast<uint32_t>(max(min(lane, left - 1), 0))];
       rb += 64;
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (ok[u]) fn(xs[u], ts[u], js[u]);
+    fn(w);
   }
 }
 
-// Collect the vertices of this wavefront's 64-vertex chunks that satisfy pred(v, d) into
-// batches of up to 64, one candidate per lane, and hand each batch to process(cand, count)
-// (lanes < count hold a candidate). Whole wavefront, uniform control flow.
-template <typename Pred, typename Proc>
-__device__ __forceinline__ void for_each_batch(const int32_t* st, int n, Pred pred, Proc process) {
-  const int lane = lane_id();
-  int held = -1;
-  int count = 0;
-  for (int base = wave_id() * 64; base < n; base += blockDim.x) {
-    const int v = base + lane;
-    const int32_t d = v < n ? st[v] : kSent;
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(v < n && pred(v, d));
-    if (!mask) continue;
-    const int cnt = __popcll(mask);
-    if (count + cnt > 64) {
-      process(held, count);
-      held = -1;
-      count = 0;
-    }
-    const int k = lane - count;
-    const bool take = k >= 0 && k < cnt;
-    const int got = shfl(v, take ? kth_set_bit(mask, k) : lane);
-    if (take) held = got;
-    count += cnt;
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0));
+}
+
+// Append this lane's values v[u], where its bit of m[u] is set, to a list at `at` (the result of
+// list_reserve). Uniform control flow.
+__device__ __forceinline__ void list_write(int32_t* list, uint32_t mask, uint32_t at,
+                                           const uint64_t (&m)[kWalk], const int (&v)[kWalk]) {
+#pragma unroll
+  for (int u = 0; u < kWalk; ++u) {
+    if (__builtin_amdgcn_inverse_ballot_w64(m[u])) list[(at + lanes_below(m[u])) & mask] = v[u];
+    at += __popcll(m[u]);
   }
-  if (count) process(held, count);
+}
+
+__device__ __forceinline__ int count_bits(const uint64_t (&m)[kWalk]) {
+  int count = 0;
+#pragma unroll
+  for (int u = 0; u < kWalk; ++u) count += __popcll(m[u]);
+  return count;
+}
+
+// Hand the candidates that satisfy pred(d) to process(cand): one per lane, -1 where a lane has
+// none. The candidates are list entries [from, to) or, if the list has overflowed, found among
+// all vertices. Whole workgroup; the control flow is uniform in each wavefront. With `spread`,
+// list entry i goes to wavefront i mod waves, so that a few candidates with long rows do not all
+// fall to one; otherwise the list goes out 64 entries at a time, so that a short list leaves the
+// other wavefronts out of a step's instructions (every wavefront's cost issue slots of the four
+// SIMDs, whether or not its lanes hold a candidate). The scan stages its finds in the wavefront's
+// share of the overflowed list; a chunk with more finds than that goes out as it is.
+template <typename Pred, typename Proc>
+__device__ __forceinline__ void for_candidates(const Node& nd, int32_t* list, uint32_t from,
+                                               uint32_t to, bool spread, Pred pred,
+                                               Proc process) {
+  const int lane = lane_id();
+  const int wave = wave_id();
+  const int waves = blockDim.x >> 6;
+  const int total = static_cast<int>(to - from);
+  const bool scan = to - from > nd.mask + 1;
+  const int room = min(64, static_cast<int>(nd.mask + 1) / waves);
+  int32_t* staged = list + room * wave;
+  int base = wave * 64;                // scan: next chunk
+  int i0 = spread ? wave : wave * 64;  // list: first entry of the next batch
+  for (;;) {
+    int held = -1;
+    if (!scan) {
+      if (i0 >= total) break;
+      const int i = spread ? i0 + waves * lane : i0 + lane;
+      if (i < total) {
+        const int v = list[(from + static_cast<uint32_t>(i)) & nd.mask];
+        if (pred(nd.st[v])) held = v;
+      }
+      i0 += waves * 64;
+    } else {
+      int count = 0;
+      for (; base < nd.n; base += blockDim.x) {
+        const int v = base + lane;
+        const bool take = v < nd.n && pred(nd.st[v]);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(take);
+        const int cnt = __popcll(m);
+        if (count + cnt > room) {  // this chunk starts the next batch, or is one by itself
+          if (count == 0) {
+            held = take ? v : -1;
+            base += blockDim.x;
+            count = -1;
+          }
+          break;
+        }
+        if (take) staged[count + lanes_below(m)] = v;
+        count += cnt;
+      }
+      if (count == 0) break;
+      __builtin_amdgcn_wave_barrier();
+      if (lane < count) held = staged[lane];
+      __builtin_amdgcn_wave_barrier();
+    }
+    process(held);
+  }
+}
+
+// Is an entry live and not marked?
+__device__ __forceinline__ bool unmarked(int32_t d) {
+  return static_cast<uint32_t>(d) < static_cast<uint32_t>(kFlag);
+}
+
+// The largest of the wavefronts' values in `part` (one per wavefront, kMaxWaves long): one LDS
+// read and a reduction inside each wavefront.
+__device__ __forceinline__ int32_t block_part_max(const int32_t* part) {
+  const int waves = blockDim.x >> 6;
+  const int32_t x = lane_id() < waves ? part[lane_id() & (kMaxWaves - 1)] : 0;
+  return static_cast<int32_t>(wave_max32(static_cast<uint32_t>(x)));
 }
 
 // Remove every marked vertex (paper §IV-B): marked vertices become kSent and s grows by their
-// number; each live unmarked neighbour of a marked vertex loses one degree per marked
-// neighbour. The scan sets each marked vertex to kSent and appends it to the workgroup's
-// removal list; after a barrier the wavefronts take the list's rows round-robin (list entry i
-// goes to wavefront i mod waves), so a few marked vertices with long rows in one wavefront's
-// part of the node do not leave the others idle. Marked vertices beyond the list's capacity
-// stay marked and are taken by further rounds of scan and walk. Workgroups of fewer than
-// kListWaves wavefronts skip the list: each wavefront walks the rows it finds. The walks only
-// decrement entries that are live and unmarked (a marked vertex is set to kSent by the scan,
-// whichever of the two happens first), which also keeps the LDS atomics off the entries of
+// number; each live unmarked neighbour of a marked vertex loses one degree per marked neighbour.
+// The walks only decrement entries that are live and unmarked (a marked vertex may turn kSent
+// meanwhile: either way it is left alone), which also keeps the LDS atomics off the entries of
 // vertices already removed. Called right after a barrier that ends a decide step (or a mark
-// step); ends with a barrier. Two calls are always separated by another barrier (a decide
-// step), which orders the reset of the list count before the next call's appends.
-__device__ __forceinline__ void apply_marks(const Node nd, Ctrl& c) {
-  const int n = nd.n;
+// step); ends with a barrier.
+__device__ __forceinline__ void apply_marks(const Node& nd, Ctrl& c, Front& f) {
   int32_t* st = nd.st;
-  const int lane = lane_id();
-  const int waves = blockDim.x >> 6;
-  const auto decrement = [&](int x, int, int) {
-    const int32_t dx = st[x];
-    if (dx >= 0 && !(dx & kFlag)) atomicSub(&st[x], 1);
-  };
-  if (waves < kListWaves) {
-    // few wavefronts, little to balance: each walks the rows of the marked vertices it finds
-    int cnt = 0;
-    for_each_batch(st, n,
-                   [&](int v, int32_t d) {
-                     const bool marked = d >= 0 && (d & kFlag);
-                     if (marked) {
-                       st[v] = kSent;
-                       ++cnt;
-                     }
-                     return marked;
-                   },
-                   [&](int f, int count) {
-                     const bool mine = lane < count;
-                     walk_rows(nd.ci, nd.heads + 64 * wave_id(), mine ? nd.rp[f] : 0,
-                               mine ? nd.rp[f + 1] : 0, f, decrement);
-                   });
-    cnt = wave_sum(cnt);
-    if (lane == 0 && cnt) atomicAdd(&st[n], cnt);
-    __syncthreads();
-    return;
+  const uint32_t tail = c.rm_tail;
+  for_candidates(
+      nd, nd.rm, f.rm, tail, nd.spread, [](int32_t d) { return d >= 0 && (d & kFlag); },
+      [&](int v) {
+        const bool mine = v >= 0;
+        if (mine) st[v] = kSent;
+        walk_rows(nd.ci, mine ? nd.rp[v] : 0, mine ? nd.rp[v + 1] : 0, v, [&](const Walked& w) {
+          int32_t d[kWalk];
+#pragma unroll
+          for (int u = 0; u < kWalk; ++u) d[u] = st[w.xs[u]];
+#pragma unroll
+          for (int u = 0; u < kWalk; ++u)
+            if (w.ok[u] && unmarked(d[u])) atomicSub(&st[w.xs[u]], 1);
+        });
+      });
+  if (threadIdx.x == 0) st[nd.n] += static_cast<int32_t>(tail - f.rm);
+  f.rm = tail;
+  __syncthreads();
+}
+
+// The four entries from vertex v0 on (a multiple of four), kSent past the last vertex.
+__device__ __forceinline__ void four_entries(const Node& nd, int v0, bool whole,
+                                             int32_t (&d)[kWalk]) {
+  const int4* st4 = reinterpret_cast<const int4*>(nd.st);
+  const int4 x = whole || v0 < nd.n ? st4[v0 >> 2] : int4{kSent, kSent, kSent, kSent};
+  d[0] = x.x, d[1] = x.y, d[2] = x.z, d[3] = x.w;
+  if (!whole) {
+#pragma unroll
+    for (int u = 0; u < kWalk; ++u) d[u] = v0 + u < nd.n ? d[u] : kSent;
   }
-  for (;;) {
-    for (int base = wave_id() * 64; base < n; base += blockDim.x) {
-      const int v = base + lane;
-      const int32_t d = v < n ? st[v] : kSent;
-      const bool marked = v < n && d >= 0 && (d & kFlag);
-      const uint64_t mask = __builtin_amdgcn_ballot_w64(marked);
-      if (!mask) continue;
-      int at = 0;
-      if (lane == 0) at = atomicAdd(&c.list_n, __popcll(mask));
-      at = __builtin_amdgcn_readfirstlane(at);
-      const uint32_t below = __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0);
-      const int rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), below);
-      if (marked && at + rank < kListCap) {  // beyond the list: left marked for the next round
-        st[v] = kSent;
-        nd.list[at + rank] = v;
+}
+
+// The candidates of the degree-one and triangle rules and the largest degree of the node as it
+// stands (nothing marked), by one scan, four consecutive vertices per thread and step: four
+// vector instructions per 64 vertices where there is no candidate. Holds one barrier. (red_max is
+// used in turn: the barrier of the next refresh lies between the reads of this one and the next
+// write of the same half.)
+__device__ __forceinline__ void refresh_lists(const Node& nd, Ctrl& c, Front& f) {
+  f.one = f.one_end;
+  f.two = f.two_end;
+  int32_t most = 0;
+  for (int base = wave_id() * 256; base < nd.n; base += 4 * blockDim.x) {
+    const int v0 = base + 4 * lane_id();
+    int32_t d[kWalk];
+    four_entries(nd, v0, base + 256 <= nd.n, d);
+    uint64_t one[kWalk], two[kWalk];
+    uint64_t any = 0;
+    int v[kWalk];
+#pragma unroll
+    for (int u = 0; u < kWalk; ++u) {
+      const int32_t e = d[u] & ~kNoTri;  // the degree, negative where the vertex is in the cover
+      most = max(most, e);
+      one[u] = __builtin_amdgcn_ballot_w64(e == 1);
+      two[u] = __builtin_amdgcn_ballot_w64(d[u] == 2);
+      any |= one[u] | two[u];
+      v[u] = v0 + u;
+    }
+    if (any) {
+      const int n1 = count_bits(one), n2 = count_bits(two);
+      uint32_t at1 = 0, at2 = 0;
+      if (lane_id() == 0) {
+        at1 = atomicAdd(&c.one_tail, static_cast<uint32_t>(n1));
+        at2 = atomicAdd(&c.two_tail, static_cast<uint32_t>(n2));
       }
+      if (n1) list_write(nd.one(), nd.mask, __builtin_amdgcn_readfirstlane(at1), one, v);
+      if (n2) list_write(nd.two(), nd.mask, __builtin_amdgcn_readfirstlane(at2), two, v);
     }
-    __syncthreads();
-    const int total = c.list_n;
-    const int listed = total < kListCap ? total : kListCap;
-    for (int i0 = wave_id(); i0 < listed; i0 += waves * 64) {
-      const int i = i0 + waves * lane;
-      const bool mine = i < listed;
-      const int f = mine ? nd.list[i] : 0;
-      walk_rows(nd.ci, nd.heads + 64 * wave_id(), mine ? nd.rp[f] : 0, mine ? nd.rp[f + 1] : 0, f,
-                decrement);
-    }
-    if (threadIdx.x == 0) st[n] += listed;
-    __syncthreads();
-    if (total <= kListCap) break;
-    // rare: more marked vertices than the list holds; the rest go in another round
-    if (threadIdx.x == 0) c.list_n = 0;
-    __syncthreads();
   }
-  if (threadIdx.x == 0) c.list_n = 0;
+  int32_t* part = c.red_max[f.turn++ & 1u];
+  most = static_cast<int32_t>(wave_max32(static_cast<uint32_t>(most)));
+  if (lane_id() == 0) part[wave_id()] = most;
+  __syncthreads();
+  f.one_end = c.one_tail;
+  f.two_end = c.two_tail;
+  f.most = block_part_max(part);
 }
 
 // Degree-one rule (§II-B): v with one live neighbour u puts u in the cover; of two adjacent
 // degree-one vertices only the smaller id is removed, and a shared neighbour once (§IV-D).
 // The rows of all degree-one vertices are walked together; the one live entry of a row names
 // u, and the lane that reads it makes the decision for that row's owner.
-__device__ __forceinline__ void decide_degree_one(const Node nd, Ctrl& c, int epoch) {
+__device__ __forceinline__ void decide_degree_one(const Node& nd, Ctrl& c, const Front& f) {
   int32_t* st = nd.st;
-  for_each_batch(st, nd.n, [](int, int32_t d) { return d >= 0 && (d & kDegMask) == 1; },
-                 [&](int cv, int count) {
-                   const bool mine = lane_id() < count;
-                   walk_rows(nd.ci, nd.heads + 64 * wave_id(), mine ? nd.rp[cv] : 0,
-                             mine ? nd.rp[cv + 1] : 0, cv,
-                             [&](int u, int v, int) {
-                               const int32_t du = st[u];
-                               if (du < 0) return;  // not the live neighbour of v
-                               if ((du & kDegMask) != 1 || u < v) {
-                                 atomicOr(&st[u], kFlag);
-                                 c.flag_epoch = epoch;
-                               }
-                             });
-                 });
+  for_candidates(
+      nd, nd.one(), f.one, f.one_end, false,
+      [](int32_t d) { return d >= 0 && (d & kDegMask) == 1; },
+      [&](int cv) {
+        const bool mine = cv >= 0;
+        walk_rows(nd.ci, mine ? nd.rp[cv] : 0, mine ? nd.rp[cv + 1] : 0, cv, [&](const Walked& w) {
+          int32_t d[kWalk];
+#pragma unroll
+          for (int u = 0; u < kWalk; ++u) d[u] = st[w.xs[u]];
+          // the live neighbour of the row's owner, if it is to go and no other lane has marked it
+          bool hit[kWalk];
+          bool any = false;
+#pragma unroll
+          for (int u = 0; u < kWalk; ++u) {
+            hit[u] = w.ok[u] && unmarked(d[u]);
+            any |= hit[u];
+          }
+          if (!__builtin_amdgcn_ballot_w64(any)) return;
+          uint64_t m[kWalk];
+#pragma unroll
+          for (int u = 0; u < kWalk; ++u) {
+            bool take = hit[u] && ((d[u] & kDegMask) != 1 || w.xs[u] < w.tags[u]);
+            if (take) take = !(atomicOr(&st[w.xs[u]], kFlag) & kFlag);
+            m[u] = __builtin_amdgcn_ballot_w64(take);
+          }
+          const int count = count_bits(m);
+          if (count == 0) return;
+          uint32_t at = 0;
+          if (lane_id() == 0) at = atomicAdd(&c.rm_tail, static_cast<uint32_t>(count));
+          list_write(nd.rm, nd.mask, __builtin_amdgcn_readfirstlane(at), m, w.xs);
+        });
+      });
+}
+
+// Mark v for the next removal step.
+__device__ __forceinline__ void mark(const Node& nd, Ctrl& c, int v) {
+  if (!(atomicOr(&nd.st[v], kFlag) & kFlag))
+    nd.rm[atomicAdd(&c.rm_tail, 1u) & nd.mask] = v;
 }
 
 // Is `key` in the sorted CSR segment ci[lo, hi)? An 8-ary search: each round reads seven
@@ -328,14 +410,14 @@ __device__ __forceinline__ bool row_contains(const int32_t* __restrict__ ci, int
 // Each lane takes one degree-two vertex: it finds the two live neighbours in its own row (rows
 // longer than kLaneRow are searched by the whole wavefront), then searches the shorter of the
 // two neighbours' rows for the other.
-__device__ __forceinline__ void decide_triangle(const Node nd, Ctrl& c, int epoch) {
+__device__ __forceinline__ void decide_triangle(const Node& nd, Ctrl& c, const Front& f) {
   constexpr int kLaneRow = 32;
   int32_t* st = nd.st;
   const int lane = lane_id();
-  for_each_batch(st, nd.n,
-                 [](int, int32_t d) { return d >= 0 && (d & kDegMask) == 2 && !(d & kNoTri); },
-                 [&](int cv, int count) {
-                   const bool mine = lane < count;
+  for_candidates(nd, nd.two(), f.two, f.two_end, false,
+                 [](int32_t d) { return d >= 0 && (d & kDegMask) == 2 && !(d & kNoTri); },
+                 [&](int cv) {
+                   const bool mine = cv >= 0;
                    const int beg = mine ? nd.rp[cv] : 0, end = mine ? nd.rp[cv + 1] : 0;
                    int a = -1, b = -1;
                    if (mine && end - beg <= kLaneRow) {
@@ -386,21 +468,20 @@ __device__ __forceinline__ void decide_triangle(const Node nd, Ctrl& c, int epoc
                    }
                    const int32_t da = st[a] & kDegMask, db = st[b] & kDegMask;
                    if ((da == 2 && a < cv) || (db == 2 && b < cv)) return;
-                   atomicOr(&st[a], kFlag);
-                   atomicOr(&st[b], kFlag);
-                   c.flag_epoch = epoch;
+                   mark(nd, c, a);
+                   mark(nd, c, b);
                  });
 }
 
 // High-degree rule (§II-B): a vertex whose degree exceeds r = bound - s is in every cover of
 // size <= bound (bound = best - 1 for MVC, k for PVC).
-__device__ __forceinline__ void decide_high_degree(const Node nd, Ctrl& c, int epoch, int64_t r) {
+__device__ __forceinline__ void decide_high_degree(const Node& nd, Ctrl& c, int64_t r) {
   int32_t* st = nd.st;
   for (int v = threadIdx.x; v < nd.n; v += blockDim.x) {
     const int32_t d = st[v];
     if (d >= 0 && static_cast<int64_t>(d & kDegMask) > r) {
       st[v] = d | kFlag;
-      c.flag_epoch = epoch;
+      nd.rm[atomicAdd(&c.rm_tail, 1u) & nd.mask] = v;
     }
   }
 }
@@ -413,112 +494,132 @@ struct NoClock {
 // The reduction rules until the graph stops changing (§II-B, §IV-D), or until s > bound.
 // Precondition: the node is visible to the whole workgroup. With `marked`, the vertices that
 // mark_vertex / mark_neighbourhood flagged (a branch's removal) are removed first. The three
-// rules take turns through one loop, so that the removal step, the longest code, is compiled
-// once per kernel.
+// rules take turns through one loop, so that the removal step is compiled once per kernel.
 template <typename Clock>
-__device__ __forceinline__ void reduce_node(const Node nd, Ctrl& c, int64_t bound, int rules,
-                                            int& epoch, Clock& clk, bool marked) {
-  const int n = nd.n;
+__device__ __forceinline__ void reduce_node(const Node& nd, Ctrl& c, Front& f, int64_t bound,
+                                            int rules, Clock& clk, bool marked) {
   int32_t* st = nd.st;
-  if (marked) {
-    apply_marks(nd, c);
-    clk.charge(kActBranch);
-  }
-  // A rule pass is skipped when nothing has been removed since it last found nothing: its
-  // inputs (the graph, and |S| for the high-degree rule) are then unchanged, so it would find
-  // nothing again. This drops the empty passes of the final round, not any decision.
-  int changes = 0;                   // removal steps applied in this call
+  // A rule pass is skipped when nothing has been removed since it last found nothing, and when it
+  // has no candidate: its list is empty, or (high-degree rule) no degree exceeds r. It would find
+  // nothing: this drops empty passes, not any decision.
+  int changes = 0;                   // removal steps applied by the rules in this call
   int quiet[3] = {-1, -1, -1};       // `changes` when each rule last found nothing
-  int32_t s0 = st[n];                // s at the start of the current round
-  if (s0 > bound) return;
-  for (int rule = 0;; rule = rule == 2 ? 0 : rule + 1) {
-    if (rule == 0 && changes > 0) {  // a new round: stop if the last one removed nothing
-      const int32_t s1 = st[n];
-      if (s1 == s0) return;
-      s0 = s1;
+  int32_t s0 = 0;                    // s at the start of the current round
+  int rule = -1;
+  for (;;) {
+    if (rule >= 0) {
+      if (rule == 0) {
+        const int32_t s1 = st[nd.n];
+        if (changes > 0 && s1 == s0) return;  // a round that removed nothing
+        s0 = s1;
+      }
+      bool skip = !(rules & (kRuleDeg1 << rule)) || quiet[rule] == changes;
+      if (rule == 0) skip |= f.one_end == f.one;
+      else if (rule == 1) skip |= f.two_end == f.two;
+      else skip |= f.most <= bound - st[nd.n];
+      if (!skip) {
+        if (rule == 0) decide_degree_one(nd, c, f);
+        else if (rule == 1) decide_triangle(nd, c, f);
+        else decide_high_degree(nd, c, bound - st[nd.n]);
+        __syncthreads();
+        if (rule == 0) clk.charge(kActDeg1);
+        else if (rule == 1) clk.charge(kActTri);
+        else clk.charge(kActHigh);
+        skip = c.rm_tail == f.rm;
+        if (skip) quiet[rule] = changes;
+      }
+      if (skip) {
+        if (rule == 2 && changes == 0) return;  // a first round that found nothing
+        rule = rule == 2 ? 0 : rule + 1;
+        continue;
+      }
     }
-    if (!(rules & (kRuleDeg1 << rule)) || quiet[rule] == changes) {
-      if (rule == 2 && changes == 0) return;  // a first round that found nothing
-      continue;
-    }
-    ++epoch;
-    if (rule == 0) {
-      decide_degree_one(nd, c, epoch);
-      __syncthreads();
-      clk.charge(kActDeg1);
-    } else if (rule == 1) {
-      decide_triangle(nd, c, epoch);
-      __syncthreads();
-      clk.charge(kActTri);
+    if (rule >= 0 || marked) apply_marks(nd, c, f);
+    if (st[nd.n] > bound) return;
+    refresh_lists(nd, c, f);
+    if (rule < 0) {
+      clk.charge(kActBranch);
     } else {
-      decide_high_degree(nd, c, epoch, bound - st[n]);
-      __syncthreads();
-      clk.charge(kActHigh);
+      ++changes;
+      clk.charge(kActApply);
     }
-    if (c.flag_epoch != epoch) {
-      quiet[rule] = changes;
-      if (rule == 2 && changes == 0) return;
-      continue;
-    }
-    apply_marks(nd, c);
-    ++changes;
-    clk.charge(kActApply);
-    if (st[n] > bound) return;
+    rule = rule == 2 ? 0 : rule + 1;
   }
 }
 
-__device__ __forceinline__ void reduce_node(const Node nd, Ctrl& c, int64_t bound, int rules,
-                                            int& epoch, bool marked = false) {
+__device__ __forceinline__ void reduce_node(const Node& nd, Ctrl& c, Front& f, int64_t bound,
+                                            int rules, bool marked = false) {
   NoClock none;
-  reduce_node(nd, c, bound, rules, epoch, none, marked);
+  reduce_node(nd, c, f, bound, rules, none, marked);
 }
 
-// One pass over the degree array: the sum of live degrees (= 2|E|) and the live vertex of
-// maximum degree, smallest id on ties (§IV-B). Results are the same in every thread.
-__device__ __forceinline__ void max_degree_and_sum(const Node nd, Ctrl& c, int& vmax, int& dmax,
-                                   int32_t& degsum) {
-  const int n = nd.n;
-  const int32_t* st = nd.st;
-  uint64_t key = 0;
+// The sum of live degrees (= 2|E|) and the live vertex of maximum degree, smallest id on ties
+// (§IV-B), of a node that reduce_node has just left: its largest degree is known. No scan when
+// there is no edge left. Results are the same in every thread.
+__device__ __forceinline__ void max_degree_and_sum(const Node& nd, Ctrl& c, const Front& f,
+                                                   int& vmax, int32_t& degsum) {
+  vmax = -1;
+  degsum = 0;
+  if (f.most <= 0) return;
+  uint32_t key = 0;  // largest ~id of a vertex of the largest degree
   int32_t sum = 0;
-  for (int v = threadIdx.x; v < n; v += blockDim.x) {
-    const int32_t raw = st[v];
-    if (raw >= 0) {
-      const int32_t d = raw & kDegMask;
-      sum += d;
-      key = umax64(key, (static_cast<uint64_t>(static_cast<uint32_t>(d)) << 32) |
-                            static_cast<uint32_t>(~static_cast<uint32_t>(v)));
+  for (int base = wave_id() * 256; base < nd.n; base += 4 * blockDim.x) {
+    const int v0 = base + 4 * lane_id();
+    int32_t d[kWalk];
+    four_entries(nd, v0, base + 256 <= nd.n, d);
+#pragma unroll
+    for (int u = 0; u < kWalk; ++u) {
+      const int32_t e = d[u] & ~kNoTri;
+      sum += max(e, 0);
+      key = max(key, e == f.most ? ~static_cast<uint32_t>(v0 + u) : 0u);
     }
   }
-  key = wave_max(key);
+  key = wave_max32(key);
   sum = wave_sum(sum);
   if (lane_id() == 0) {
     c.red_key[wave_id()] = key;
     c.red_sum[wave_id()] = sum;
   }
   __syncthreads();
-  key = 0;
-  sum = 0;
   const int waves = blockDim.x >> 6;
-  for (int w = 0; w < waves; ++w) {
-    key = umax64(key, c.red_key[w]);
-    sum += c.red_sum[w];
+  const bool mine = lane_id() < waves;
+  const int at = lane_id() & (kMaxWaves - 1);
+  vmax = static_cast<int>(~wave_max32(mine ? c.red_key[at] : 0u));
+  degsum = wave_sum(mine ? c.red_sum[at] : 0);
+}
+
+// The cover of the node, one byte per vertex: four to a store where the output is aligned to four
+// bytes (a packed batch's covers start anywhere).
+__device__ __forceinline__ void store_cover(uint8_t* cov, const Node& nd) {
+  if ((reinterpret_cast<uintptr_t>(cov) & 3u) == 0) {
+    for (int v0 = 4 * threadIdx.x; v0 < nd.n; v0 += 4 * blockDim.x) {
+      int32_t d[kWalk];
+      four_entries(nd, v0, v0 + 4 <= nd.n, d);
+      if (v0 + 4 <= nd.n) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int u = 0; u < kWalk; ++u) x |= (static_cast<uint32_t>(d[u]) >> 31) << (8 * u);
+        *reinterpret_cast<uint32_t*>(cov + v0) = x;
+      } else {
+        for (int v = v0; v < nd.n; ++v) cov[v] = nd.st[v] < 0;
+      }
+    }
+  } else {
+    for (int v = threadIdx.x; v < nd.n; v += blockDim.x) cov[v] = nd.st[v] < 0;
   }
-  vmax = static_cast<int>(~static_cast<uint32_t>(key));
-  dmax = static_cast<int>(key >> 32);
-  degsum = sum;
 }
 
 // Flag every live neighbour of v (the "N(v) in the cover" child, §II-B); the next reduce_node
 // (marked = true) removes them. Ends with a barrier.
-__device__ __forceinline__ void mark_neighbourhood(const Node nd, int v) {
+__device__ __forceinline__ void mark_neighbourhood(const Node& nd, Ctrl& c, int v) {
   int32_t* st = nd.st;
-  const int lane = lane_id();
-  if (wave_id() == 0) {
-    const int beg = nd.rp[v], end = nd.rp[v + 1];
-    for (int j = beg + lane; j < end; j += 64) {
-      const int x = nd.ci[j];
-      if (st[x] >= 0) st[x] |= kFlag;  // distinct x per lane: plain read-modify-write
+  const int beg = nd.rp[v], end = nd.rp[v + 1];
+  for (int j = beg + static_cast<int>(threadIdx.x); j < end; j += blockDim.x) {
+    const int x = nd.ci[j];
+    const int32_t d = st[x];  // distinct x per thread: plain read-modify-write
+    if (d >= 0) {
+      st[x] = d | kFlag;
+      nd.rm[atomicAdd(&c.rm_tail, 1u) & nd.mask] = x;
     }
   }
   __syncthreads();
@@ -526,8 +627,11 @@ __device__ __forceinline__ void mark_neighbourhood(const Node nd, int v) {
 
 // Flag v alone (the "v in the cover" child, §II-B); the next reduce_node (marked = true)
 // removes it. Ends with a barrier.
-__device__ __forceinline__ void mark_vertex(const Node nd, int v) {
-  if (threadIdx.x == 0) nd.st[v] |= kFlag;
+__device__ __forceinline__ void mark_vertex(const Node& nd, Ctrl& c, int v) {
+  if (threadIdx.x == 0) {
+    nd.st[v] |= kFlag;
+    nd.rm[c.rm_tail++ & nd.mask] = v;
+  }
   __syncthreads();
 }
 
@@ -584,13 +688,18 @@ enum MemMode : int {
   kMemLdsCsr = 3,  // node and the whole CSR in LDS
 };
 
+// The dynamic LDS: the lists, then (node in LDS) the node and the staged CSR.
+__device__ __forceinline__ int32_t* lists_base() {
+  extern __shared__ int4 lds4[];
+  return reinterpret_cast<int32_t*>(lds4);
+}
+
 template <int MEM>
 __device__ __forceinline__ int32_t* node_base(const Params& p, int slot) {
   if constexpr (MEM == kMemGlobal) {
     return p.gnodes + static_cast<size_t>(slot) * p.stride;
   } else {
-    extern __shared__ int4 lds4[];
-    return reinterpret_cast<int32_t*>(lds4);
+    return lists_base() + list_lds_words(p.list_cap);
   }
 }
 
@@ -607,48 +716,73 @@ __device__ __forceinline__ int32_t* node_base(const Params& p, int slot) {
 // passes find them in this XCD's L2.
 constexpr int32_t kTouchMaxEntries = 1 << 18;
 
+// Average degree from which a removal step spreads its rows over the wavefronts.
+constexpr int32_t kSpreadDegree = 8;
+
+__device__ __forceinline__ Node make_node(const Params& p, int32_t* st, const Instance& in,
+                                          const int32_t* rp, const int32_t* ci) {
+  return Node{st, in.n, rp, ci, lists_base(), static_cast<uint32_t>(p.list_cap) - 1u,
+              in.nnz / kSpreadDegree >= in.n};
+}
+
+// Copy `count` words into LDS, eight independent loads per thread and step (one at a time, a
+// root's 16,000 row pointers took sixteen device-memory latencies).
+__device__ __forceinline__ void stage(int32_t* dst, const int32_t* __restrict__ src, int count) {
+  constexpr int kAhead = 8;
+  for (int i0 = threadIdx.x; i0 < count; i0 += kAhead * blockDim.x) {
+    int32_t x[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int i = i0 + u * static_cast<int>(blockDim.x);
+      x[u] = src[i < count ? i : count - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int i = i0 + u * static_cast<int>(blockDim.x);
+      if (i < count) dst[i] = x[u];
+    }
+  }
+}
+
 template <int MEM>
-__device__ __forceinline__ Node load_instance(const Params& p, int j, int32_t* st,
-                                              int32_t* list, int32_t* heads) {
+__device__ __forceinline__ Node load_instance(const Params& p, int j, int32_t* st) {
   const Instance in = p.inst[j];
   const int32_t* rp = p.rp_all + in.rp_off;
   const int32_t* ci = p.ci_all + in.ci_off;
+  int32_t acc = 0;
   if constexpr (MEM == kMemLds || MEM == kMemLdsRp) {
-    if (in.nnz <= kTouchMaxEntries) {
-      int32_t acc = 0;
+    if (in.nnz <= kTouchMaxEntries)
       for (int i = threadIdx.x * 32; i < in.nnz; i += blockDim.x * 32) acc ^= ci[i];
-      asm volatile("" ::"v"(acc));
-    }
   }
   if constexpr (MEM >= kMemLdsRp) {
     int32_t* dst = st + p.stride;
-    for (int i = threadIdx.x; i <= in.n; i += blockDim.x) dst[i] = rp[i];
+    stage(dst, rp, in.n + 1);
     if constexpr (MEM == kMemLdsCsr) {
       int32_t* dci = dst + rp_lds_words(p.n_max);
-      for (int i = threadIdx.x; i < in.nnz; i += blockDim.x) dci[i] = ci[i];
+      stage(dci, ci, in.nnz);
       ci = dci;
     }
     __syncthreads();
     rp = dst;
   }
-  return Node{st, in.n, rp, ci, list, heads};
+  asm volatile("" ::"v"(acc));  // the touches are waited for last
+  return make_node(p, st, in, rp, ci);
 }
 
 // A node with no instance yet, whose CSR pointers already point where this memory mode keeps
 // them (so that the compiler sees one kind of memory behind each pointer).
 template <int MEM>
-__device__ __forceinline__ Node empty_node(const Params& p, int32_t* st, int32_t* list,
-                                           int32_t* heads) {
+__device__ __forceinline__ Node empty_node(const Params& p, int32_t* st) {
   const int32_t* rp = p.rp_all;
   const int32_t* ci = p.ci_all;
   if constexpr (MEM >= kMemLdsRp) rp = st + p.stride;
   if constexpr (MEM == kMemLdsCsr) ci = st + p.stride + rp_lds_words(p.n_max);
-  return Node{st, 0, rp, ci, list, heads};
+  return make_node(p, st, Instance{}, rp, ci);
 }
 
 // Whole workgroup: the root of instance j in LDS -- the input's degree array, s = 0, nothing
 // pending, the instance in the last word. Ends with a barrier.
-__device__ __forceinline__ void build_root(const Params& p, const Node nd, int j) {
+__device__ __forceinline__ void build_root(const Params& p, const Node& nd, int j) {
   for (int v = threadIdx.x; v < p.stride; v += blockDim.x) {
     int32_t x = 0;
     if (v < nd.n) x = nd.rp[v + 1] - nd.rp[v];
@@ -783,34 +917,29 @@ __global__ void prepare_kernel(Params p, DevResult* res, int64_t vertices, int64
 template <int MEM>
 __global__ void __launch_bounds__(1024) greedy_kernel(Params p) {
   __shared__ Ctrl c;
-  __shared__ int32_t rm_list[kListCap];
-  __shared__ int32_t heads[kMaxWaves * 64];
   int32_t* st = node_base<MEM>(p, blockIdx.x);
-  if (threadIdx.x == 0) {
-    c.flag_epoch = -1;
-    c.list_n = 0;
-  }
-  int epoch = 0;
+  if (threadIdx.x == 0) c.rm_tail = c.one_tail = c.two_tail = 0;
+  Front f{};
   for (int j = blockIdx.x; j < p.num_inst; j += gridDim.x) {
     if (threadIdx.x == 0) c.err = load_relaxed(&p.ist[j].err_row) != kNoRow;
     __syncthreads();
     const bool skip = c.err;
     __syncthreads();  // every thread has read c.err before thread 0 writes it again
     if (skip) continue;
-    const Node nd = load_instance<MEM>(p, j, st, rm_list, heads);
+    const Node nd = load_instance<MEM>(p, j, st);
     build_root(p, nd, j);
     const int64_t unbounded = 0x3FFFFFFFFFFFFFFFll;
     for (bool marked = false;; marked = true) {
-      reduce_node(nd, c, unbounded, kRuleDeg1 | kRuleTri, epoch, marked);
-      int vmax, dmax;
+      reduce_node(nd, c, f, unbounded, kRuleDeg1 | kRuleTri, marked);
+      int vmax;
       int32_t degsum;
-      max_degree_and_sum(nd, c, vmax, dmax, degsum);
+      max_degree_and_sum(nd, c, f, vmax, degsum);
       if (degsum == 0) break;
-      mark_vertex(nd, vmax);
+      mark_vertex(nd, c, vmax);
     }
     const int s = st[nd.n];
     uint8_t* cov = p.covers + p.inst[j].vtx_off;
-    for (int v = threadIdx.x; v < nd.n; v += blockDim.x) cov[v] = st[v] < 0;
+    store_cover(cov, nd);
     if (threadIdx.x == 0) {
       p.ist[j].best = s;
       p.ist[j].greedy = s;
@@ -863,16 +992,14 @@ __device__ __forceinline__ void report_nodes(const Params& p, int j, int64_t cou
 template <bool PVC, bool PROF, int MEM, bool SO>
 __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   __shared__ Ctrl c;
-  __shared__ int32_t rm_list[kListCap];
-  __shared__ int32_t heads[kMaxWaves * 64];
   int32_t* st = node_base<MEM>(p, blockIdx.x);
   const int wg = blockIdx.x;
   const int tid = threadIdx.x;
   if (tid == 0) {
-    c.flag_epoch = -1;
     c.stop = 0;
-    c.list_n = 0;
+    c.rm_tail = c.one_tail = c.two_tail = 0;
   }
+  __syncthreads();
   ActivityClock<PROF> clk;
   clk.begin();
   if (tid == 0) watch_begin(c);
@@ -891,8 +1018,8 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   bool marked = false;    // the node in LDS has flagged vertices still to be removed
   int cur = -1;           // instance of the node in LDS
   int32_t cur_k = 0, cur_vtx = 0;
-  Node nd = empty_node<MEM>(p, st, rm_list, heads);
-  int epoch = 0;
+  Node nd = empty_node<MEM>(p, st);
+  Front f{};
   int64_t nodes = 0, pushes = 0, pops = 0, enqueues = 0, dequeues = 0, insts = 0;
   int64_t unreported = 0;  // nodes on `cur` not yet added to its counter
   int max_depth = 0;
@@ -901,6 +1028,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   for (;;) {
     if (!have) {
       marked = false;   // whatever node comes next replaces the one in LDS
+      f.rm = c.rm_tail;  // (what a dropped node still had marked is no longer to be removed)
       __syncthreads();  // every thread has read the last broadcast before thread 0 writes
       if (top > bot) {
         --top;
@@ -912,7 +1040,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
         // StackOnly (the comparison method of §V-A), as in bitset_traverse_kernel: walk this
         // workgroup's next path down from the root, then take the node at the start depth.
         if (cur < 0) {
-          nd = load_instance<MEM>(p, 0, st, rm_list, heads);
+          nd = load_instance<MEM>(p, 0, st);
           const Instance in = p.inst[0];
           cur = 0;
           cur_k = in.k;
@@ -946,13 +1074,13 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
           const int64_t bound = PVC ? static_cast<int64_t>(cur_k) : static_cast<int64_t>(c.best) - 1;
           ++nodes;
           if (owner) ++unreported;
-          reduce_node(nd, c, bound, p.rules, epoch, clk, marked);
+          reduce_node(nd, c, f, bound, p.rules, clk, marked);
           marked = false;
           const int32_t s = st[nd.n];
           const int64_t r = bound - s;
-          int vmax = 0, dmax = 0;
+          int vmax = 0;
           int32_t degsum = 0;
-          if (r >= 0) max_degree_and_sum(nd, c, vmax, dmax, degsum);
+          if (r >= 0) max_degree_and_sum(nd, c, f, vmax, degsum);
           const int64_t edges = degsum / 2;
           if (r < 0 || ((p.rules & kPruneEdges) && (p.rules & kRuleHigh) && edges > r * r)) {
             reached = false;
@@ -962,7 +1090,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
               __syncthreads();
               if (c.status) {
                 uint8_t* cov = p.covers + cur_vtx;
-                for (int v = tid; v < nd.n; v += blockDim.x) cov[v] = st[v] < 0;
+                store_cover(cov, nd);
                 __threadfence();
                 __syncthreads();
                 if (tid == 0) publish_solution<PVC>(p, cur, s);
@@ -970,8 +1098,8 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
             }
             reached = false;
           } else {
-            if ((so_path >> d) & 1u) mark_neighbourhood(nd, vmax);
-            else mark_vertex(nd, vmax);
+            if ((so_path >> d) & 1u) mark_neighbourhood(nd, c, vmax);
+            else mark_vertex(nd, c, vmax);
             marked = true;
           }
           __syncthreads();  // every thread has read c.* before thread 0 writes it again
@@ -1017,7 +1145,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
         if (j != cur) {
           if (tid == 0 && cur >= 0) report_nodes(p, cur, unreported);
           unreported = 0;
-          nd = load_instance<MEM>(p, j, st, rm_list, heads);
+          nd = load_instance<MEM>(p, j, st);
           const Instance in = p.inst[j];
           cur = j;
           cur_k = in.k;
@@ -1041,7 +1169,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
       if (pending >= 0) {
         __syncthreads();  // every thread has read the pending vertex
         if (tid == 0) st[nd.n + 1] = -1;
-        mark_neighbourhood(nd, pending);
+        mark_neighbourhood(nd, c, pending);
         marked = true;
       }
       clk.charge(kActBranch);
@@ -1075,7 +1203,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
     }
 
     const int64_t bound = PVC ? static_cast<int64_t>(cur_k) : static_cast<int64_t>(c.best) - 1;
-    reduce_node(nd, c, bound, p.rules, epoch, clk, marked);
+    reduce_node(nd, c, f, bound, p.rules, clk, marked);
     marked = false;
     clk.charge(kActReduce);
 
@@ -1088,9 +1216,9 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
       have = false;
       continue;
     }
-    int vmax, dmax;
+    int vmax;
     int32_t degsum;
-    max_degree_and_sum(nd, c, vmax, dmax, degsum);
+    max_degree_and_sum(nd, c, f, vmax, degsum);
     clk.charge(kActBranch);
     const int64_t edges = degsum / 2;
     if ((p.rules & kPruneEdges) && (p.rules & kRuleHigh) && edges > r * r) {
@@ -1102,7 +1230,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
       __syncthreads();
       if (c.status) {
         uint8_t* cov = p.covers + cur_vtx;
-        for (int v = tid; v < n; v += blockDim.x) cov[v] = st[v] < 0;
+        store_cover(cov, nd);
         __threadfence();
         __syncthreads();
         if (tid == 0) publish_solution<PVC>(p, cur, s);
@@ -1141,7 +1269,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
       __syncthreads();  // the copy has read the node before it changes below
     }
     clk.charge(kActDonate);
-    mark_vertex(nd, vmax);
+    mark_vertex(nd, c, vmax);
     marked = true;
     clk.charge(kActBranch);
   }
@@ -1188,7 +1316,6 @@ __device__ void add_grouped(int32_t* dst, int32_t x) {
 // to the result block themselves.) Packed entry offsets must fit in int32.
 __global__ void __launch_bounds__(256) finalize_kernel(Params p, int64_t vertices,
                                                        int64_t entries, DevResult* res) {
-  __shared__ int32_t heads[4 * 64];
   (void)entries;
   const int64_t waves = static_cast<int64_t>(gridDim.x) * (blockDim.x >> 6);
   for (int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x >> 6) + wave_id();
@@ -1218,8 +1345,14 @@ __global__ void __launch_bounds__(256) finalize_kernel(Params p, int64_t vertice
       ones_dst = &p.ist[j].cover_count;
     }
     add_grouped(ones_dst, one);
-    walk_rows(p.ci_all, heads + 64 * wave_id(), beg, end, j, [&](int u, int jj, int) {
-      if (p.covers[p.inst[jj].vtx_off + u] == 0) atomicAdd(&p.ist[jj].uncovered, 1);
+    walk_rows(p.ci_all, beg, end, j, [&](const Walked& w) {
+      uint8_t c[kWalk];
+#pragma unroll
+      for (int u = 0; u < kWalk; ++u)
+        c[u] = w.ok[u] ? p.covers[p.inst[w.tags[u]].vtx_off + w.xs[u]] : 1;
+#pragma unroll
+      for (int u = 0; u < kWalk; ++u)
+        if (c[u] == 0) atomicAdd(&p.ist[w.tags[u]].uncovered, 1);
     });
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1235,23 +1368,20 @@ template <int MEM>
 __global__ void __launch_bounds__(1024) reduce_kernel(Params p, int32_t* deg, int32_t* s,
                                                       int64_t bound) {
   __shared__ Ctrl c;
-  __shared__ int32_t rm_list[kListCap];
-  __shared__ int32_t heads[kMaxWaves * 64];
   int32_t* st = node_base<MEM>(p, 0);
   if (threadIdx.x == 0) {
     c.err = load_relaxed(&p.ist[0].err_row) != kNoRow;
-    c.flag_epoch = -1;
-    c.list_n = 0;
+    c.rm_tail = c.one_tail = c.two_tail = 0;
   }
   __syncthreads();
   if (c.err) return;
-  const Node nd = load_instance<MEM>(p, 0, st, rm_list, heads);
+  const Node nd = load_instance<MEM>(p, 0, st);
   const int n = nd.n;
   for (int v = threadIdx.x; v < p.stride; v += blockDim.x)
     st[v] = v < n ? deg[v] : (v == n ? *s : (v == n + 1 ? -1 : 0));
   __syncthreads();
-  int epoch = 0;
-  reduce_node(nd, c, bound, p.rules, epoch);
+  Front f{};
+  reduce_node(nd, c, f, bound, p.rules);
   for (int v = threadIdx.x; v < n; v += blockDim.x) deg[v] = st[v] < 0 ? kSent : (st[v] & kDegMask);
   if (threadIdx.x == 0) *s = st[n];
 }
@@ -1305,13 +1435,14 @@ static int mem_mode(bool global_node, int32_t rp_lds) {
 
 template <int MEM>
 static size_t launch_lds(const Params& p) {
-  return MEM == kMemGlobal ? 0 : node_lds_bytes(p.stride, p.n_max, p.rp_lds, p.nnz_max);
+  return 4 * list_lds_words(p.list_cap) +
+         (MEM == kMemGlobal ? 0 : node_lds_bytes(p.stride, p.n_max, p.rp_lds, p.nnz_max));
 }
 
 template <int MEM>
 static void greedy_on(const Params& p, int32_t wg_size, hipStream_t stream) {
-  hipLaunchKernelGGL(greedy_kernel<MEM>, dim3(greedy_grid(p)), dim3(wg_size), launch_lds<MEM>(p),
-                     stream, p);
+  hipLaunchKernelGGL(greedy_kernel<MEM>, dim3(greedy_grid(p)), dim3(wg_size),
+                     launch_lds<MEM>(p), stream, p);
 }
 
 hipError_t launch_greedy(const Params& p, int32_t wg_size, hipStream_t stream) {
@@ -1355,7 +1486,9 @@ static const void* traverse_fn(bool pvc, bool prof, int mem, bool stack_only = f
 hipError_t launch_traverse(bool pvc, bool prof, const Params& p, int32_t wg_size,
                            hipStream_t stream) {
   const bool global_node = p.gnodes != nullptr;
-  const size_t lds = global_node ? 0 : node_lds_bytes(p.stride, p.n_max, p.rp_lds, p.nnz_max);
+  const size_t lds =
+      4 * list_lds_words(p.list_cap) +
+      (global_node ? 0 : node_lds_bytes(p.stride, p.n_max, p.rp_lds, p.nnz_max));
   Params args = p;
   void* kargs[] = {&args};
   return hipLaunchKernel(traverse_fn(pvc, prof, mem_mode(global_node, p.rp_lds), p.start_depth > 0),
@@ -1373,8 +1506,8 @@ hipError_t launch_finalize(const Params& p, int64_t vertices, int64_t entries, D
 template <int MEM>
 static void reduce_on(const Params& p, int32_t wg_size, int32_t* deg, int32_t* s, int64_t bound,
                       hipStream_t stream) {
-  hipLaunchKernelGGL(reduce_kernel<MEM>, dim3(1), dim3(wg_size), launch_lds<MEM>(p), stream, p, deg,
-                     s, bound);
+  hipLaunchKernelGGL(reduce_kernel<MEM>, dim3(1), dim3(wg_size), launch_lds<MEM>(p),
+                     stream, p, deg, s, bound);
 }
 
 hipError_t launch_reduce(const Params& p, int32_t wg_size, int32_t* deg, int32_t* s,

@@ -120,7 +120,6 @@ __device__ __forceinline__ int bcast(int x, int lane) { return __builtin_amdgcn_
 struct Ctrl {
   uint64_t t_start;    // thread 0: the device clock when this workgroup started (watchdog)
   uint64_t t_host;     // thread 0 of workgroup 0: when it last read the host's stop word
-  int32_t flag_epoch;  // epoch of the last decide step that marked a vertex
   int32_t status;      // broadcast of a result computed by thread 0
   uint32_t slot;
   uint32_t lap;
@@ -128,8 +127,12 @@ struct Ctrl {
   int32_t stop;        // broadcast: the launch is being stopped
   int32_t err;         // broadcast: the instance's input graph was rejected
   int32_t drop;        // broadcast: the current instance is answered or out of budget
-  int32_t list_n;      // degree-array removal step: vertices appended to the removal list
-  uint64_t red_key[kMaxWaves];
+  // degree-array lists: entries ever appended (see Front in the degree-array kernels)
+  uint32_t rm_tail;
+  uint32_t one_tail;
+  uint32_t two_tail;
+  int32_t red_max[2][kMaxWaves];  // used in turn (see refresh_lists)
+  uint32_t red_key[kMaxWaves];
   int32_t red_sum[kMaxWaves];
 };
 
@@ -337,6 +340,16 @@ __device__ inline int worklist_take(const Params& p, Ctrl& c, bool check_stop, u
   return load_relaxed(ctr_i32(p, kWork)) == 0 ? 0 : 3;
 }
 
+// One workgroup's pause between looks for work: exponential back-off in units of about 1,024
+// cycles. A launch ends when its last idle workgroup looks again, so the longest pause is a tail
+// on every call; it grows with the grid (one unit per 64 workgroups, 4 to 32), so that the looks
+// of all idle workgroups together stay below about 150 a microsecond.
+__device__ __forceinline__ void idle_sleep(const Params& p, int polls) {
+  const int most = min(32, max(4, p.num_wg >> 6));
+  const int units = min(1 << min(polls, 5), most);
+  for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(16);
+}
+
 // Whole workgroup: wait for work. Returns 1 with c.slot / c.lap set for a worklist entry (the
 // caller reads the node, then calls dequeue_finish), 2 with c.slot set to an instance whose
 // search has not started (its root), 0 when the whole launch is finished, -1 when it is being
@@ -364,8 +377,7 @@ __device__ inline int dequeue_begin(const Params& p, Ctrl& c, bool& first) {
       } else if (status == 2) {
         c.slot = static_cast<uint32_t>(root);
       } else if (status == 3) {
-        const int units = 1 << (polls < 5 ? polls : 5);
-        for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(16);
+        idle_sleep(p, polls);
         if (!first) ++polls;
       }
       c.status = status;

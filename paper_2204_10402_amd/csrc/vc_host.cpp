@@ -73,6 +73,10 @@ namespace {
 constexpr size_t kMaxGroups = vc::kMaxBitsetWords + 1;
 // Pinned staging made with a context (grown by the allocating forms as batches need).
 constexpr size_t kPinnedStart = size_t(1) << 20;
+// Entries of each candidate list of a degree-array workgroup: from 256 (what the small graphs
+// need whose resident workgroups LDS limits) up to 8,192, where that costs none.
+constexpr int32_t kListCapLeast = 256;
+constexpr int32_t kListCapMost = 8192;
 
 using vc::DevResult;
 using vc::Instance;
@@ -275,6 +279,7 @@ struct Plan {
   uint32_t cap = 0;
   uint32_t threshold = 0;
   size_t lds = 0;
+  int32_t list_cap = 1;     // degree-array kernels: entries of each candidate list
   int32_t rp_lds = 0;       // degree-array kernels: 1 = row_ptr staged in LDS, 2 = the CSR
   int32_t global_node = 0;  // degree-array kernels: the node lives in device memory
 };
@@ -375,23 +380,7 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
     return VC_OK;
   } else {
     pl.stride = vc::array_stride(n_max);
-    pl.lds = vc::node_lds_bytes(pl.stride, n_max, 0, 0);
     const size_t lds_cap = static_cast<size_t>(ctx->prop.maxSharedMemoryPerMultiProcessor);
-    // Selection rule (§IV-E, adapted): the node stays in LDS while it fits there with room
-    // to spare; larger graphs (or VC_OPT_GLOBAL_NODES) keep it in device memory.
-    pl.global_node = ((o && (o->flags & VC_OPT_GLOBAL_NODES)) || pl.lds + 1024 > lds_cap) ? 1 : 0;
-    if (pl.global_node) pl.lds = 0;
-    const size_t lds_rp = vc::node_lds_bytes(pl.stride, n_max, 1, 0);
-    const size_t lds_csr = vc::node_lds_bytes(pl.stride, n_max, 2, nnz_max);
-    const bool csr_fits = !pl.global_node && !(o && (o->flags & VC_OPT_CSR_GLOBAL)) &&
-                          lds_csr + 1024 <= lds_cap;
-    const size_t lds_max = pl.global_node ? 0
-                           : csr_fits     ? lds_csr
-                                          : (lds_rp + 1024 <= lds_cap ? lds_rp : pl.lds);
-    if (lds_max > 65536 && ctx->lds_limit_set < lds_max) {
-      VC_HIP(ctx, vc::set_lds_limit(lds_max));
-      ctx->lds_limit_set = lds_max;
-    }
     if (o && o->wg_size) {
       best_ws = o->wg_size;
     } else {
@@ -403,30 +392,66 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
       while (ws < 1024 && ws * 2 <= std::max(n_max, 1) / 4) ws *= 2;
       best_ws = ws;
     }
-    if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, pl.lds, n_max, &best_occ,
-                        pl.global_node != 0)))
+    // The candidate lists at their shortest (32 entries per wavefront, see for_candidates), and
+    // 1 KB for what else a workgroup shares.
+    const int32_t list_least = std::max<int32_t>(kListCapLeast, next_pow2(best_ws) / 2);
+    const size_t lists_least = 4 * vc::list_lds_words(list_least);
+    auto fits = [&](size_t node_bytes) { return node_bytes + lists_least + 1024 <= lds_cap; };
+    const size_t lds_node = vc::node_lds_bytes(pl.stride, n_max, 0, 0);
+    const size_t lds_rp = vc::node_lds_bytes(pl.stride, n_max, 1, 0);
+    const size_t lds_csr = vc::node_lds_bytes(pl.stride, n_max, 2, nnz_max);
+    // Selection rule (§IV-E, adapted): the node stays in LDS while it fits there with room
+    // to spare; larger graphs (or VC_OPT_GLOBAL_NODES) keep it in device memory.
+    pl.global_node = ((o && (o->flags & VC_OPT_GLOBAL_NODES)) || !fits(lds_node)) ? 1 : 0;
+    const bool csr_fits = !pl.global_node && !(o && (o->flags & VC_OPT_CSR_GLOBAL)) && fits(lds_csr);
+    if (ctx->lds_limit_set < lds_cap - 1024) {
+      VC_HIP(ctx, vc::set_lds_limit(lds_cap - 1024));
+      ctx->lds_limit_set = lds_cap - 1024;
+    }
+    const auto with_lists = [&](size_t node_bytes, int32_t list_cap) {
+      return node_bytes + 4 * vc::list_lds_words(list_cap);
+    };
+    pl.list_cap = list_least;
+    size_t node_bytes = pl.global_node ? 0 : lds_node;
+    if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, with_lists(node_bytes, pl.list_cap), n_max,
+                        &best_occ, pl.global_node != 0)))
       return rc;
     // Keep row_ptr in LDS too when that costs no resident workgroup.
-    if (!pl.global_node && lds_rp + 1024 <= lds_cap) {
+    if (!pl.global_node && fits(lds_rp)) {
       int occ_rp = 0;
-      if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, lds_rp, n_max, &occ_rp, false, 1))) return rc;
+      if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, with_lists(lds_rp, pl.list_cap), n_max,
+                          &occ_rp, false, 1)))
+        return rc;
       if (occ_rp == best_occ) {
         pl.rp_lds = 1;
-        pl.lds = lds_rp;
+        node_bytes = lds_rp;
       }
     }
     // And the column indices when that keeps at least half of the resident workgroups: a
     // rule pass is a chain of dependent row walks, which then read LDS instead of L2 or HBM.
     if (csr_fits) {
       int occ_csr = 0;
-      if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, lds_csr, n_max, &occ_csr, false, 2)))
+      if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, with_lists(lds_csr, pl.list_cap), n_max,
+                          &occ_csr, false, 2)))
         return rc;
       if (occ_csr >= 1 && 2 * occ_csr >= best_occ) {
         pl.rp_lds = 2;
-        pl.lds = lds_csr;
+        node_bytes = lds_csr;
         best_occ = occ_csr;
       }
     }
+    // Longer lists, up to the number of vertices, where they cost no resident workgroup: a list
+    // that overflows sends its next pass back to a scan of every vertex.
+    while (pl.list_cap < kListCapMost && pl.list_cap < n_max &&
+           node_bytes + 4 * vc::list_lds_words(2 * pl.list_cap) + 1024 <= lds_cap) {
+      int occ_more = 0;
+      if ((rc = occupancy(ctx, 0, pvc, prof, best_ws, with_lists(node_bytes, 2 * pl.list_cap),
+                          n_max, &occ_more, pl.global_node != 0, pl.rp_lds)))
+        return rc;
+      if (occ_more < best_occ) break;
+      pl.list_cap *= 2;
+    }
+    pl.lds = with_lists(node_bytes, pl.list_cap);
   }
   if (best_occ < 1)
     return fail(ctx, VC_ERR_INVALID_ARG, "traversal kernel cannot be resident at this size");
@@ -512,6 +537,12 @@ int size_stacks(vc_ctx* ctx, Plan& pl, int32_t depth_cap) {
                                            std::to_string(per_wg) + " bytes");
   if (fit < static_cast<size_t>(pl.num_wg)) pl.num_wg = static_cast<int32_t>(fit);
   return ensure(ctx, ctx->stacks, per_wg * static_cast<size_t>(pl.num_wg));
+}
+
+// Threads of a degree-array kernel that gives each instance one workgroup (greedy, reduce): about
+// one per vertex, as many as the launch's lists serve (32 entries per wavefront).
+int32_t one_workgroup_size(int32_t n_max, const Plan& pl) {
+  return static_cast<int32_t>(std::min<int64_t>({1024, round_up(n_max, 64), 2ll * pl.list_cap}));
 }
 
 double ms_since(std::chrono::steady_clock::time_point t0) {
@@ -798,6 +829,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     p.bits = g.words ? static_cast<uint64_t*>(lc->bits.ptr) : nullptr;
     p.words = g.words;
     p.rp_lds = pl.rp_lds;
+    p.list_cap = pl.list_cap;
     p.pvc = pvc ? 1 : 0;
     if (pl.global_node) {
       // one node slot per traversal workgroup and per greedy workgroup
@@ -822,7 +854,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
 
     VC_HIP(ctx, vc::launch_prepare(p, dres, g.vertices, g.entries, gst));
     if (!pvc) {
-      const int gws = g.words ? 64 : static_cast<int>(std::min<int64_t>(1024, round_up(g.n_max, 64)));
+      const int gws = g.words ? 64 : one_workgroup_size(g.n_max, pl);
       hipEvent_t e0 = ctx->ev[2 * ng + 4 + 2 * gi], e1 = ctx->ev[2 * ng + 5 + 2 * gi];
       VC_HIP(ctx, hipEventRecord(e0, gst));
       if (g.words) VC_HIP(ctx, vc::launch_bitset_greedy(p, gst));
@@ -1402,11 +1434,12 @@ int setup_single(vc_ctx* ctx, const vc_graph* g, int rules, int32_t flags, uint8
   p.bits = words ? static_cast<uint64_t*>(ctx->bits.ptr) : nullptr;
   p.words = words;
   p.rp_lds = pl.rp_lds;
+  p.list_cap = pl.list_cap;
   if (pl.global_node) {
     if ((rc = ensure(ctx, ctx->gnodes, static_cast<size_t>(pl.stride) * sizeof(int32_t)))) return rc;
     p.gnodes = static_cast<int32_t*>(ctx->gnodes.ptr);
   }
-  *wg_size = words ? 64 : static_cast<int32_t>(std::min<int64_t>(1024, round_up(g->n, 64)));
+  *wg_size = words ? 64 : one_workgroup_size(g->n, pl);
   DevResult* dres = reinterpret_cast<DevResult*>(dev + L.res);
   p.res = dres;
   VC_HIP(ctx, vc::launch_prepare(p, dres, g->n, g->nnz, ctx->stream));

@@ -146,6 +146,7 @@ struct Params {
   int32_t rp_lds;       // degree-array kernels: 1 = copy the instance's row_ptr into LDS after
                         // the node, 2 = its col_idx too (after row_ptr); 0 = neither
   int32_t nnz_max;      // largest nnz of this launch (sizes the LDS copy of col_idx)
+  int32_t list_cap;     // degree-array kernels: entries of each candidate list (a power of two)
   int32_t* gnodes;      // degree-array kernels with the node in device memory: one stride-word
                         // slot per workgroup (nullptr: the node lives in LDS)
   int32_t stack_lds;    // bitset kernels: 1 = each workgroup's stack ring lives in LDS after the
@@ -169,8 +170,15 @@ inline int32_t array_stride(int32_t n_max) {
 // LDS words that hold a staged row_ptr (n_max + 1 entries, padded to 16 bytes).
 __host__ __device__ inline size_t rp_lds_words(int32_t n_max) { return (static_cast<size_t>(n_max) + 1 + 3) / 4 * 4; }
 
-// Dynamic LDS of a degree-array kernel: the node (stride words), then row_ptr if staged
-// (rp_lds >= 1), then col_idx if staged (rp_lds == 2).
+// LDS words of a degree-array workgroup's lists (removal list and the lists of degree-one and
+// degree-two vertices, `list_cap` entries each). They come first in the dynamic LDS, in every
+// memory mode.
+__host__ __device__ inline size_t list_lds_words(int32_t list_cap) {
+  return 3 * static_cast<size_t>(list_cap);
+}
+
+// Dynamic LDS of a degree-array kernel after its lists: the node (stride words), then row_ptr if
+// staged (rp_lds >= 1), then col_idx if staged (rp_lds == 2).
 inline size_t node_lds_bytes(int32_t stride, int32_t n_max, int32_t rp_lds, int64_t nnz_max) {
   size_t words = static_cast<size_t>(stride);
   if (rp_lds >= 1) words += rp_lds_words(n_max);

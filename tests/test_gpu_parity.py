@@ -449,6 +449,38 @@ def first_bad_row(n, rp, ci):
     return None
 
 
+@pytest.mark.parametrize("kernel", ["degree_arrays", "csr_global", "global_nodes"])
+@pytest.mark.parametrize("shape", ["edges", "triangles", "mixed", "paths"])
+def test_candidate_lists_overflow(solver, oracle_lib, torch_cuda, shape, kernel):
+    """More candidates in one pass than a degree-array workgroup's lists hold (at most 8,192
+    entries): 9,000 disjoint edges (18,000 degree-one vertices, 9,000 removals at once), 3,000
+    triangles (9,000 degree-two vertices), both at once with stars whose long rows are cut into
+    pieces, and 600 paths of 31 vertices (a long cascade of short passes). The fixpoint equals
+    the oracle's vertex by vertex; MVC and PVC sizes are the components' closed forms."""
+    edges = [G.path(2)] * 9000
+    triangles = [G.complete(3)] * 3000
+    g, tau = {"edges": lambda: (G.disjoint_union(*edges), 9000),
+              "triangles": lambda: (G.disjoint_union(*triangles), 6000),
+              "mixed": lambda: (G.disjoint_union(*(edges[:4200] + triangles[:2800] +
+                                                   [G.star(300)] * 7)), 4200 + 5600 + 7),
+              "paths": lambda: (G.disjoint_union(*([G.path(31)] * 600)), 9000)}[shape]()
+    flags = KERNELS[kernel]
+    rp, ci = torch_cuda.from_numpy(g.row_ptr).to("cuda:0"), torch_cuda.from_numpy(g.col_idx).to("cuda:0")
+    for bound in (g.n, tau, tau // 2):
+        deg = torch_cuda.from_numpy(g.degrees()).to("cuda:0")
+        s = solver.reduce_device(rp, ci, deg, 0, bound, flags)
+        want, ws = oracle.reduce(g, g.degrees(), 0, bound)
+        if ws <= bound:
+            assert s == ws and np.array_equal(deg.cpu().numpy(), want), bound
+        else:
+            assert s > bound
+    o = opts(flags=flags, num_wg=4)
+    r = solver.mvc(g, o)
+    assert r.size == tau
+    check_cover(g, r.cover, tau)
+    assert solver.pvc(g, tau, o).yes and not solver.pvc(g, tau - 1, o).yes
+
+
 @pytest.mark.parametrize("kind", ["out_of_range", "self_loop", "asymmetric", "unsorted"])
 def test_invalid_entry_deep_in_a_large_graph(solver, kind):
     """A defect in one entry of G(600, 0.05) (about 18,000 entries, many validation blocks):
