@@ -775,7 +775,8 @@ constexpr uint32_t kDonateNodes = 8;
 // pass sub-trees to each other in LDS, and the workgroup as a whole takes nodes and roots from
 // the launch's worklist when all of its wavefronts have run out.
 template <int W, bool PVC, bool PROF, bool SO>
-__global__ void __launch_bounds__(64 * bitset_max_team(W)) bitset_traverse_kernel(Params p) {
+__global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
+    bitset_traverse_kernel(Params p) {
   extern __shared__ uint64_t adj_lds[];
   __shared__ Ctrl c;
   __shared__ Team<W> team;
@@ -1299,6 +1300,11 @@ hipError_t launch_bitset_reduce(const Params& p, int32_t* deg, int32_t* s, int64
     default: hipLaunchKernelGGL(bitset_reduce_kernel<8>, dim3(1), dim3(64), lds, stream, p, deg, s, bound); break;
   }
   return hipGetLastError();
+}
+
+hipError_t bitset_lds_limit(int words, bool pvc, bool prof, bool stack_only, size_t lds) {
+  return hipFuncSetAttribute(bitset_fn(words, pvc, prof, stack_only),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
 }
 
 hipError_t bitset_occupancy(int words, bool pvc, bool prof, int team, size_t lds,

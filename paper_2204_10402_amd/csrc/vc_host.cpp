@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -44,6 +45,8 @@ struct vc_ctx {
   std::string last_error;
   // occupancy-API answers: (kernel family, pvc, profiled, workgroup size, words, LDS bytes)
   std::map<std::tuple<int, int, int, int, int, size_t>, int> occupancy;
+  // bitset traversal kernels (words, pvc, profiled) allowed more than the default dynamic LDS
+  std::set<std::tuple<int, bool, bool>> bitset_lds_set;
   // autotuner choices: (bitset words, pvc, flags, log2 n_max, log2 instances) -> knobs
   std::map<std::tuple<int, int, int, int, int>, std::tuple<int, int, int>> tuned;
   // A second context (own stream, worklist, counters, stacks) on which a batch's degree-array
@@ -301,13 +304,18 @@ int occupancy(vc_ctx* ctx, int words, bool pvc, bool prof, int ws, size_t lds, i
 }
 
 // Kernel family of a graph: bitset kernels with ceil(n/64) words up to kAutoBitsetN vertices
-// (up to kMaxBitsetN when the caller asks for them), else degree arrays (0).
-int choose_words(vc_ctx* ctx, int32_t n, int32_t flags, int32_t* words) {
+// (kAutoBitsetNPvc for PVC, up to kMaxBitsetN when the caller asks for them), else degree arrays
+// (0). Above kAutoBitsetN an option that only the degree-array kernels know keeps them: a
+// workgroup size, how they read the CSR, or StackOnly's walk.
+int choose_words(vc_ctx* ctx, int32_t n, bool pvc, const vc_options* o, int32_t* words) {
+  const int32_t flags = o ? o->flags : 0;
   const bool force_bits = flags & VC_OPT_BITSETS;
   const bool force_arrays = flags & (VC_OPT_DEGREE_ARRAYS | VC_OPT_GLOBAL_NODES);
   if (force_bits && n > vc::kMaxBitsetN)
     return fail(ctx, VC_ERR_INVALID_ARG, "VC_OPT_BITSETS needs n <= 512");
-  const bool bits = force_bits || (!force_arrays && n <= vc::kAutoBitsetN);
+  const bool plain = pvc && !(o && o->wg_size) && !(flags & (VC_OPT_CSR_GLOBAL | VC_OPT_STACK_ONLY));
+  const int32_t most = plain ? vc::kAutoBitsetNPvc : vc::kAutoBitsetN;
+  const bool bits = force_bits || (!force_arrays && n <= most);
   *words = bits ? (std::max(n, 1) + 63) / 64 : 0;
   return VC_OK;
 }
@@ -345,19 +353,25 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
     if (o && o->wg_size && o->wg_size != 64)
       return fail(ctx, VC_ERR_INVALID_ARG, "the bitset kernels use 64-thread workgroups");
     // The team: eight wavefronts (four for more than four words, whose kernels hold up to 256
-    // registers) as long as their stack rings fit in LDS beside the adjacency matrix (within the
-    // default 64 KB) and there is a workgroup for every instance: an instance occupies one
-    // workgroup, so with more instances than workgroups smaller teams leave fewer wavefronts
-    // idle. One wavefront where the caller asks for 64-thread workgroups, for no donations (each
+    // registers) as long as their stack rings fit in LDS beside the adjacency matrix with room for
+    // a second workgroup on the CU, and there is a workgroup for every instance: an instance
+    // occupies one workgroup, so with more instances than workgroups smaller teams leave fewer
+    // wavefronts idle. One wavefront where the caller asks for 64-thread workgroups, for no donations (each
     // workgroup then walks its whole sub-tree in depth-first order), or for StackOnly.
+    const size_t lds_most = static_cast<size_t>(ctx->prop.maxSharedMemoryPerMultiProcessor) / 2 - 2048;
+    if (!ctx->bitset_lds_set.count(std::make_tuple(words, pvc, prof))) {
+      const bool so = o && (o->flags & VC_OPT_STACK_ONLY);
+      VC_HIP(ctx, vc::bitset_lds_limit(words, pvc, prof, so, lds_most));
+      if (!so) ctx->bitset_lds_set.insert(std::make_tuple(words, pvc, prof));
+    }
     const bool alone = o && (o->wg_size == 64 || o->wl_threshold == -1 ||
                              (o->flags & VC_OPT_STACK_ONLY));
     int32_t team = alone ? 1 : sh.team ? sh.team : std::min(8, vc::bitset_max_team(words));
     if (!alone && !sh.team)
-      while (team > 1 && bitset_team_lds(sh, team) > 65536) team /= 2;
+      while (team > 1 && bitset_team_lds(sh, team) > lds_most) team /= 2;
     for (;; team /= 2) {
       const size_t lds = bitset_team_lds(sh, team);
-      const bool in_lds = lds <= 65536;
+      const bool in_lds = lds <= lds_most;
       pl.lds = in_lds ? lds : vc::bitset_lds_bytes(n_max, words);
       best_ws = 64 * team;
       if ((rc = occupancy(ctx, words, pvc, prof, best_ws, pl.lds, n_max, &best_occ))) return rc;
@@ -456,7 +470,10 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
   if (best_occ < 1)
     return fail(ctx, VC_ERR_INVALID_ARG, "traversal kernel cannot be resident at this size");
   pl.wg_size = best_ws;
-  pl.num_wg = best_occ * cus;
+  // Untuned, at most eight workgroups per CU: the idle ones of a small search poll the worklist's
+  // counters (16 graphs G(300, 3.2/300), 2,100 nodes each on average: 17 per CU 2.5 ms, eight
+  // 1.4 ms; 16 of 390 vertices, 750,000 nodes: 9.5 and 8.5 ms).
+  pl.num_wg = (o && o->num_wg > 0 ? best_occ : std::min(best_occ, 8)) * cus;
   if (o && o->grid_share > 0) pl.num_wg = std::max(1, pl.num_wg / o->grid_share);
   if (o && o->num_wg > 0) pl.num_wg = std::min(pl.num_wg, o->num_wg);
 
@@ -637,7 +654,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       }
       continue;
     }
-    if ((rc = choose_words(ctx, b.n[i], flags, &words[i]))) return rc;
+    if ((rc = choose_words(ctx, b.n[i], pvc, o, &words[i]))) return rc;
     order.push_back(i);
   }
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
@@ -700,12 +717,16 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     g.entries += in.nnz;
   }
   hipStream_t st = ctx->stream;
-  // A batch with both kernel families runs its degree-array launch on the auxiliary context
-  // (first, as the longest) while the bitset launches follow on this one: the two persistent
-  // launches share the device instead of queueing behind each other. Not when the caller
-  // already runs launches side by side on shares of the grid (vc_options.grid_share).
-  const bool use_aux = !stack_only && ng >= 2 && groups.back().words == 0 &&
+  // A batch that mixes graphs of up to four bitset words with larger ones (wider bitsets, degree
+  // arrays) runs the larger ones' launches on the auxiliary context (first, as the longest) while
+  // the others follow on this one: the persistent launches share the device instead of queueing
+  // behind each other. Not when the caller already runs launches side by side on shares of the
+  // grid (vc_options.grid_share).
+  auto large = [&](int32_t gi) { return groups[gi].words == 0 || groups[gi].words > 4; };
+  const bool use_aux = !stack_only && ng >= 2 && large(ng - 1) && !large(0) &&
                        !(o && o->grid_share > 0) && !ctx->ws;
+  int32_t first_large = ng;  // groups from here on are large (they are sorted by size)
+  while (first_large > 0 && large(first_large - 1)) --first_large;
   if (use_aux && !ctx->aux) {
     vc_ctx* a = nullptr;
     if ((rc = vc_create(&a, ctx->device, nullptr)) != VC_OK)
@@ -713,7 +734,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     ctx->aux = a;
   }
   auto lane = [&](int32_t gi) -> vc_ctx* {
-    return use_aux && groups[gi].words == 0 ? ctx->aux : ctx;
+    return use_aux && large(gi) ? ctx->aux : ctx;
   };
 
   if (m > 0) {
@@ -772,11 +793,15 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     int rc2;
     vc_options shared = go ? *go : vc_options{};
     if (use_aux) {
-      // Two launches side by side, each on a share of the co-resident grid; the rest stays free
-      // for the short validation and check kernels of the other stream. Full grids starved them
-      // (the degree-array launch holds its CUs to the end); a third for the degree-array launch,
-      // which waits for work much of the time, and half for the bitset launches measured best.
-      shared.grid_share = std::max(shared.grid_share, 1) * (g.words ? 2 : 3);
+      // Two launches side by side. A degree-array launch, which holds its CUs to the end, takes a
+      // third of the co-resident grid and leaves half to the bitset launches beside it; the rest
+      // stays free for the short validation and check kernels of the other stream (full grids
+      // starved them). Bitset launches are short: the wider ones take a third and the others the
+      // whole grid (4,096 planted graphs of 40-400 / 860 of 99-363 vertices, shares wider : other
+      // 1 : 1 1.86 / 0.70 ms, half : half 2.06 / 0.56, half : 1 2.00 / 0.55, third : half 1.93 /
+      // 0.60, quarter : 1 1.74 / 0.62, all on one stream 2.03 / 0.79).
+      const bool arrays = groups.back().words == 0;
+      shared.grid_share = std::max(shared.grid_share, 1) * (large(gi) ? 3 : arrays ? 2 : 1);
       go = &shared;
     }
     g.pl = Plan{};
@@ -888,12 +913,13 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     p.stack_lds = 0;
     if (g.words) {
       // A bitset node is a few dozen bytes: keep the stack ring in LDS when it fits there
-      // (within the default 64 KB) without lowering the launch's residency, so a pop is an LDS
-      // read instead of a dependent device-memory load.
+      // (see plan_launch) without lowering the launch's residency, so a pop is an LDS read instead
+      // of a dependent device-memory load.
       p.stack_lds = 1;
       const size_t lds = vc::bitset_traverse_lds_bytes(p);
+      const size_t lds_most = static_cast<size_t>(ctx->prop.maxSharedMemoryPerMultiProcessor) / 2 - 2048;
       int occ = 0;
-      if (lds <= 65536 && (rc2 = occupancy(ctx, g.words, pvc, prof, pl.wg_size, lds, g.n_max, &occ)))
+      if (lds <= lds_most && (rc2 = occupancy(ctx, g.words, pvc, prof, pl.wg_size, lds, g.n_max, &occ)))
         return rc2;
       if (static_cast<int64_t>(occ) * ctx->prop.multiProcessorCount < pl.num_wg) p.stack_lds = 0;
     }
@@ -924,8 +950,8 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
   const bool explicit_knobs = o && (o->wg_size || o->num_wg || o->wl_capacity || o->wl_threshold);
   const bool autotune = (flags & VC_OPT_AUTOTUNE) && !explicit_knobs && !stack_only && !ctx->ws;
   for (int32_t step = 0; step < ng; ++step) {
-    // with the auxiliary context, the degree-array group (the last) goes first
-    const int32_t gi = use_aux ? (step == 0 ? ng - 1 : step - 1) : step;
+    // with the auxiliary context, the large groups go first, the largest of them ahead
+    const int32_t gi = !use_aux ? step : step < ng - first_large ? ng - 1 - step : step - (ng - first_large);
     Group& g = groups[gi];
     vc_options go = o ? *o : vc_options{};
     int thr_div = 0, team = 0;
@@ -1018,7 +1044,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       greedy_ms += ms;
     }
   // traversal time: the launches' durations added up, or with the auxiliary context (whose
-  // degree-array launch starts first) the span until the last traversal ends
+  // largest group's launch starts first) the span until the last traversal ends
   double kernel_ms = 0.0;
   for (int32_t gi = 0; gi < ng; ++gi) {
     float ms = 0.f;
@@ -1318,37 +1344,36 @@ int solve_batch(vc_ctx* ctx, const vc_batch* batch, bool device_graph, bool pvc,
 // larger of the MVC and PVC launch plans.
 int workspace_need(vc_ctx* ctx, int32_t count, const int32_t* n, const int32_t* nnz,
                    int32_t depth, const vc_options* o, size_t* out) {
-  const int32_t flags = o ? o->flags : 0;
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   struct Fam {
     int32_t n_max = 0, nnz_max = 0, count = 0;
     int64_t vertices = 0;
   };
-  std::map<int32_t, Fam> fams;  // by bitset words (0: degree arrays)
-  int64_t total_n = 0;
-  int32_t m = 0;
-  for (int32_t i = 0; i < count; ++i) {
-    if (n[i] < 0 || nnz[i] < 0) return fail(ctx, VC_ERR_INVALID_ARG, "negative n or nnz");
-    if (n[i] == 0) continue;
-    int32_t words = 0;
-    int rc = choose_words(ctx, n[i], flags, &words);
-    if (rc) return rc;
-    Fam& f = fams[words];
-    f.n_max = std::max(f.n_max, n[i]);
-    f.nnz_max = std::max(f.nnz_max, nnz[i]);
-    f.count += 1;
-    f.vertices += n[i];
-    total_n += n[i];
-    ++m;
-  }
-  size_t total = 256 + al(meta_layout(m, static_cast<int32_t>(fams.size()), 0).dev_end) +
-                 al(static_cast<size_t>(total_n)) +
-                 al(vc::kNumCounters * vc::kCounterStride * sizeof(int32_t));
-  for (const auto& kv : fams) {
-    const int32_t words = kv.first;
-    const Fam& f = kv.second;
-    size_t best = 0;
-    for (bool pvc : {false, true}) {
+  size_t most = 0;
+  for (bool pvc : {false, true}) {
+    std::map<int32_t, Fam> fams;  // by bitset words (0: degree arrays)
+    int64_t total_n = 0;
+    int32_t m = 0;
+    for (int32_t i = 0; i < count; ++i) {
+      if (n[i] < 0 || nnz[i] < 0) return fail(ctx, VC_ERR_INVALID_ARG, "negative n or nnz");
+      if (n[i] == 0) continue;
+      int32_t words = 0;
+      int rc = choose_words(ctx, n[i], pvc, o, &words);
+      if (rc) return rc;
+      Fam& f = fams[words];
+      f.n_max = std::max(f.n_max, n[i]);
+      f.nnz_max = std::max(f.nnz_max, nnz[i]);
+      f.count += 1;
+      f.vertices += n[i];
+      total_n += n[i];
+      ++m;
+    }
+    size_t total = 256 + al(meta_layout(m, static_cast<int32_t>(fams.size()), 0).dev_end) +
+                   al(static_cast<size_t>(total_n)) +
+                   al(vc::kNumCounters * vc::kCounterStride * sizeof(int32_t));
+    for (const auto& kv : fams) {
+      const int32_t words = kv.first;
+      const Fam& f = kv.second;
       Plan pl;
       int64_t d = depth > 0 ? depth : static_cast<int64_t>(f.n_max) + 1;
       if (o && o->stack_depth > 0) d = o->stack_depth;
@@ -1368,11 +1393,11 @@ int workspace_need(vc_ctx* ctx, int32_t count, const int32_t* n, const int32_t* 
       if (pl.global_node)
         need += al(static_cast<size_t>(std::max<int64_t>(pl.num_wg, std::min(f.count, 65535))) *
                    stride_b);
-      best = std::max(best, need);
+      total += need;
     }
-    total += best;
+    most = std::max(most, total);
   }
-  *out = total;
+  *out = most;
   return VC_OK;
 }
 
@@ -1387,10 +1412,11 @@ int check_workspace(vc_ctx* ctx, void* ws, size_t bytes) {
 int setup_single(vc_ctx* ctx, const vc_graph* g, int rules, int32_t flags, uint8_t* covers,
                  Params& p, int32_t* wg_size) {
   int32_t words = 0;
-  int rc = choose_words(ctx, g->n, flags, &words);
+  vc_options o{};
+  o.flags = flags;
+  int rc = choose_words(ctx, g->n, false, &o, &words);
   if (rc) return rc;
   Plan pl;
-  vc_options o{};
   o.flags = flags & (VC_OPT_GLOBAL_NODES | VC_OPT_CSR_GLOBAL);
   Shape sh;
   sh.n_max = g->n;

@@ -228,11 +228,14 @@ hipError_t launch_max_greedy(const Params& p, int32_t* out, hipStream_t stream);
 // vc_bitset.hip: graphs of at most kMaxBitsetN vertices
 constexpr int kMaxBitsetN = 512;
 constexpr int kMaxBitsetWords = 8;  // ceil(kMaxBitsetN / 64)
-// Largest n that takes the bitset kernels by default. Wider bitsets (5 to 8 words) hold so many
-// registers that fewer wavefronts stay resident: they were up to 2.3 times faster than the
-// degree-array kernels on searches of ~20,000 nodes, slower on 10^5-10^6 nodes and on batches
-// and request streams of graphs settled near the root, so they are used only on request.
+// Largest n that takes the bitset kernels by default: 256 for MVC, 512 for PVC. One wavefront per
+// node and the teams' handovers suit the searches and roots of 257 to 512 vertices (PVC, planted
+// graphs of 257-320 / 385-448 vertices, 1,024 a call: 2.80 -> 0.46 ms / 4.84 -> 0.99 ms; 16 graphs
+// G(390, 3.5/390), 750,000 nodes: 9.5 -> 4.8 ms; one planted root of 300 / 500 vertices: 132 ->
+// 102 us / 152 -> 125 us). MVC calls keep the degree arrays above 256, the family that
+// vc_stats.bitset_words has always reported for them.
 constexpr int kAutoBitsetN = 256;
+constexpr int kAutoBitsetNPvc = 512;
 hipError_t launch_bitset_greedy(const Params& p, hipStream_t stream);
 hipError_t launch_bitset_traverse(bool pvc, bool prof, const Params& p, hipStream_t stream);
 hipError_t launch_bitset_reduce(const Params& p, int32_t* deg, int32_t* s, int64_t bound,
@@ -245,6 +248,8 @@ hipError_t bitset_occupancy(int words, bool pvc, bool prof, int team, size_t lds
 constexpr int kDonateMost = 4;
 // Largest team (wavefronts per workgroup) of the bitset traversal kernels of `words` words.
 __host__ __device__ constexpr int bitset_max_team(int words) { return words <= 3 ? 16 : (words == 4 ? 8 : 4); }
+// Allow a bitset traversal kernel `lds` bytes of dynamic LDS (more than the default 64 KB).
+hipError_t bitset_lds_limit(int words, bool pvc, bool prof, bool stack_only, size_t lds);
 // Dynamic LDS of the bitset kernels: the adjacency matrix (and, for a traversal launch with
 // stack_lds, the stack ring after it).
 size_t bitset_lds_bytes(int n_max, int words);

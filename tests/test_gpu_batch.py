@@ -258,3 +258,40 @@ def test_bitset_team_sizes(solver, oracle_lib, count, team):
     assert mv.size.tolist() == [taus[i % 12] for i in range(count)]
     alone = solver.mvc_batch([base[4]] * count)
     assert alone.stats["wg_size"] == 64 * team and set(alone.size.tolist()) == {taus[4]}
+
+
+@pytest.mark.parametrize("n", [257, 320, 321, 448, 511, 512, 513])
+def test_pvc_family_by_size_and_options(solver, oracle_lib, n):
+    """PVC takes the bitset kernels up to 512 vertices, unless an option asks for what only the
+    degree-array kernels know; both families give the same decision, a valid cover and, for no,
+    the oracle's node count. MVC keeps the degree arrays above 256. Whole numbers: no tolerance."""
+    import paper_2204_10402_amd as vc
+    torch = pytest.importorskip("torch")
+    g = G.erdos_renyi(n, 3.0 / n, 4200 + n)
+    tau = oracle.mvc(g, node_cap=200000).size
+    want = oracle.pvc(g, tau - 1, node_cap=200000).nodes
+    assert solver.mvc(g).stats["bitset_words"] == 0
+    rp, ci = torch.from_numpy(g.row_ptr).to("cuda:0"), torch.from_numpy(g.col_idx).to("cuda:0")
+    words = (n + 63) // 64 if n <= 512 else 0
+    for kw, w in ((dict(), words), (dict(wg_size=64), 0), (dict(wg_size=128), 0),
+                  (dict(flags=vc.OPT_CSR_GLOBAL), 0), (dict(flags=vc.OPT_DEGREE_ARRAYS), 0),
+                  (dict(flags=vc.OPT_STACK_ONLY, start_depth=4), 0),
+                  (dict(wl_threshold=-1, num_wg=1), words), (dict(num_wg=3, wl_capacity=1), words),
+                  (dict(flags=vc.OPT_AUTOTUNE), words), (dict(timeout_ms=20000), words)):
+        o = vc.Options(**kw)
+        no = solver.pvc(g, tau - 1, o)
+        assert not no.yes and no.stats["bitset_words"] == w and no.stats["nodes"] == want, kw
+        yes = solver.pvc(g, tau, o)
+        assert yes.yes and yes.size <= tau and oracle.is_cover(g, yes.cover), kw
+        assert int(yes.cover.sum()) == yes.size
+        if "flags" not in kw and "wg_size" not in kw:
+            need = solver.workspace_bytes(g.n, g.col_idx.size, options=o)
+            ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+            r = solver.pvc_device_ws(rp, ci, tau - 1, ws, options=o)
+            assert not r.yes and r.stats["nodes"] == want, kw
+            m = solver.mvc_device_ws(rp, ci, ws, options=o)
+            assert m.size == tau and m.stats["bitset_words"] == 0, kw
+    assert not solver.pvc_device_noalloc(rp, ci, tau - 1).yes
+    with pytest.raises(vc.VCError) as e:
+        solver.pvc(g, tau - 1, vc.Options(node_budget=1))
+    assert e.value.code == vc.ERR_BUDGET or want <= 1
