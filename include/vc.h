@@ -164,10 +164,11 @@ typedef struct {
   int32_t bitset_words;   /* 64-bit words per node with the bitset kernels; 0 = degree arrays
                              (batches: the largest used) */
   int32_t node_bytes;     /* bytes of one search node's state (batches: the largest) */
-  double kernel_ms;       /* traversal kernel time (HIP events; batches: summed over the
-                             launches, or, when a batch's degree-array launch runs beside its
-                             bitset launches, the span from its start to the last one's end) */
-  double greedy_ms;       /* greedy kernel time (MVC) */
+  double kernel_ms;       /* traversal kernel time (device clock, from the first workgroup's start
+                             to the cover check after it; batches: summed over the launches, or,
+                             when launches run side by side, the span from the first one's start
+                             to the last one's end) */
+  double greedy_ms;       /* greedy kernel time (MVC; device clock) */
   double total_ms;        /* wall clock of the whole call */
   /* With VC_OPT_PROFILE, shader-clock cycles summed over the workgroups, with the bitset kernels
    * over every wavefront of them (paper §V-D):

@@ -698,6 +698,7 @@ __device__ __forceinline__ int bits_dequeue(const Params& p, Ctrl& c, bool first
 template <int W>
 __global__ void __launch_bounds__(64) bitset_greedy_kernel(Params p) {
   extern __shared__ uint64_t adj_lds[];
+  if (blockIdx.x == 0 && threadIdx.x == 0) p.res->t_greedy = realtime();
   for (int j = blockIdx.x; j < p.num_inst; j += gridDim.x) {
     if (__builtin_amdgcn_readfirstlane(load_relaxed(&p.ist[j].err_row)) != kNoRow) continue;
     Rows<W> r;
@@ -792,7 +793,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
   ActivityClock<PROF> clk;
   clk.begin();
   if (tid == 0) {
-    watch_begin(c);
+    watch_begin(p, c);
     tally = WgStats{};
     team.nodes = 0;
   }

@@ -831,12 +831,67 @@ __device__ __forceinline__ bool try_enqueue(const Params& p, const Node nd, Ctrl
 // ---- kernels ---------------------------------------------------------------------------------
 
 
+// Row v of a CSR: are its bounds wrong?
+__device__ __forceinline__ bool row_bad(const int32_t* __restrict__ rp, int n, int nnz, int v) {
+  const int beg = rp[v], end = rp[v + 1];
+  return (v == 0 && beg != 0) || (v == n - 1 && end != nnz) || beg < 0 || end < beg || end > nnz;
+}
+
+// Row v (of good bounds) as adjacency words.
+__device__ __forceinline__ void pack_row(const int32_t* __restrict__ rp,
+                                         const int32_t* __restrict__ ci, int n, int v, int words,
+                                         uint64_t* __restrict__ dst) {
+  uint64_t row[kMaxBitsetWords] = {};
+  for (int e = rp[v]; e < rp[v + 1]; ++e) {
+    const int u = ci[e];
+    if (u >= 0 && u < n) row[u >> 6] |= 1ull << (u & 63);
+  }
+  for (int w = 0; w < words; ++w) dst[w] = row[w];
+}
+
+// CSR entry e: the row it makes the graph invalid in (out of range, a self-loop, not above the
+// entry before it, or not present in reverse), kNoRow if none. Every read is bounds-checked
+// before it is made.
+__device__ __forceinline__ int32_t entry_bad_row(const int32_t* __restrict__ rp,
+                                                 const int32_t* __restrict__ ci, int n, int nnz,
+                                                 int e) {
+  const int v = owner_row(rp, n, e);
+  const int beg = rp[v], end = rp[v + 1];
+  if (!(beg <= e && e < end && beg >= 0 && end <= nnz)) return kNoRow;  // row_bad finds it
+  const int u = ci[e];
+  bool bad = u < 0 || u >= n || u == v || (e > beg && ci[e - 1] >= u);
+  if (!bad) {
+    const int ub = rp[u], ue = rp[u + 1];
+    bad = ub < 0 || ue < ub || ue > nnz;
+    if (!bad) {
+      int lo = ub, hi = ue;
+      while (lo < hi) {
+        const int mid = lo + ((hi - lo) >> 1);
+        if (ci[mid] < v) lo = mid + 1; else hi = mid;
+      }
+      bad = lo >= ue || ci[lo] != v;
+    }
+  }
+  return bad ? v : kNoRow;
+}
+
+// Whole workgroup: the launch's control lines and result block.
+__device__ __forceinline__ void reset_launch(const Params& p, DevResult* res) {
+  for (int i = threadIdx.x; i < kNumCounters * kCounterStride; i += blockDim.x) p.ctr[i] = 0;
+  char* r = reinterpret_cast<char*>(res);
+  for (int i = threadIdx.x; i < static_cast<int>(sizeof(DevResult)); i += blockDim.x) r[i] = 0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    *ctr_i32(p, kWork) = p.num_inst;
+    *ctr_i32(p, kOpen) = p.num_inst;
+    res->wg_nodes_min = INT64_MAX;
+  }
+}
+
 // Check every graph of the launch (simple undirected, §II-A). Index i < vertices checks row
 // i's bounds (and, for the bitset kernels, packs the row into adjacency words); index i <
-// entries checks one CSR entry: in range, not a self-loop, larger than the entry before it in
-// its row, and present in reverse. Every read is bounds-checked before it is made, so a
-// malformed input cannot send a thread out of its instance's arrays. Each instance keeps the
-// smallest offending row.
+// entries checks one CSR entry. A malformed input cannot send a thread out of its instance's
+// arrays. Each instance keeps the smallest offending row.
 //
 // The same launch first resets the launch's control lines and result block and marks every
 // worklist slot free (the host uploads the fresh per-instance state with the instance table);
@@ -845,17 +900,7 @@ __device__ __forceinline__ bool try_enqueue(const Params& p, const Node nd, Ctrl
 __global__ void prepare_kernel(Params p, DevResult* res, int64_t vertices, int64_t entries) {
   const int64_t total = vertices > entries ? vertices : entries;
   const int64_t gsize = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < kNumCounters * kCounterStride; i += blockDim.x) p.ctr[i] = 0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      *ctr_i32(p, kWork) = p.num_inst;
-      *ctr_i32(p, kOpen) = p.num_inst;
-      char* r = reinterpret_cast<char*>(res);
-      for (size_t i = 0; i < sizeof(DevResult); ++i) r[i] = 0;
-      res->wg_nodes_min = INT64_MAX;
-    }
-  }
+  if (blockIdx.x == 0) reset_launch(p, res);
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < p.q_cap;
        i += gsize)
     p.seq[i] = 0u;
@@ -867,46 +912,59 @@ __global__ void prepare_kernel(Params p, DevResult* res, int64_t vertices, int64
       const int v = static_cast<int>(i - in.vtx_first);
       const int32_t* rp = p.rp_all + in.rp_off;
       const int32_t* ci = p.ci_all + in.ci_off;
-      const int beg = rp[v], end = rp[v + 1];
-      const bool bad = (v == 0 && beg != 0) || (v == in.n - 1 && end != in.nnz) || beg < 0 ||
-                       end < beg || end > in.nnz;
+      const bool bad = row_bad(rp, in.n, in.nnz, v);
       if (bad) atomicMin(&p.ist[j].err_row, v);
-      if (p.words && !bad) {
-        uint64_t row[kMaxBitsetWords] = {};
-        for (int e = beg; e < end; ++e) {
-          const int u = ci[e];
-          if (u >= 0 && u < in.n) row[u >> 6] |= 1ull << (u & 63);
-        }
-        uint64_t* dst = p.bits + (static_cast<int64_t>(in.vtx_first) + v) * p.words;
-        for (int w = 0; w < p.words; ++w) dst[w] = row[w];
-      }
+      if (p.words && !bad)
+        pack_row(rp, ci, in.n, v, p.words,
+                 p.bits + (static_cast<int64_t>(in.vtx_first) + v) * p.words);
     }
     if (i < entries) {
       const int j = instance_of_entry(p, i);
       const Instance in = p.inst[j];
-      const int e = static_cast<int>(i - in.ent_first);
-      const int32_t* rp = p.rp_all + in.rp_off;
-      const int32_t* ci = p.ci_all + in.ci_off;
-      const int v = owner_row(rp, in.n, e);
-      const int beg = rp[v], end = rp[v + 1];
-      if (beg <= e && e < end && beg >= 0 && end <= in.nnz) {  // otherwise row bounds are bad
-        const int u = ci[e];
-        bool bad = u < 0 || u >= in.n || u == v || (e > beg && ci[e - 1] >= u);
-        if (!bad) {
-          const int ub = rp[u], ue = rp[u + 1];
-          bad = ub < 0 || ue < ub || ue > in.nnz;
-          if (!bad) {
-            int lo = ub, hi = ue;
-            while (lo < hi) {
-              const int mid = lo + ((hi - lo) >> 1);
-              if (ci[mid] < v) lo = mid + 1; else hi = mid;
-            }
-            bad = lo >= ue || ci[lo] != v;
-          }
-        }
-        if (bad) atomicMin(&p.ist[j].err_row, v);
-      }
+      const int32_t bad = entry_bad_row(p.rp_all + in.rp_off, p.ci_all + in.ci_off, in.n, in.nnz,
+                                        static_cast<int>(i - in.ent_first));
+      if (bad != kNoRow) atomicMin(&p.ist[j].err_row, bad);
     }
+  }
+}
+
+// prepare_kernel for a launch of one small graph (see kSmallEntries). Block 0 copies the CSR into
+// LDS, where the searches of an entry's check cost a tenth of what they cost in L2, and writes the
+// instance table, state and work counter itself, so that the call needs no copy command before its
+// first kernel (G(60, 0.1): a copy, a gap and a validation of 25 us became one launch); the other
+// blocks free the worklist's slots.
+__global__ void __launch_bounds__(1024) prepare_small_kernel(Params p, DevResult* res, Instance in) {
+  extern __shared__ int32_t csr[];
+  __shared__ int32_t err;
+  if (blockIdx.x > 0) {
+    for (uint32_t i = (blockIdx.x - 1) * blockDim.x + threadIdx.x; i < p.q_cap;
+         i += (gridDim.x - 1) * blockDim.x)
+      p.seq[i] = 0u;
+    return;
+  }
+  int32_t* rp = csr;
+  int32_t* ci = csr + in.n + 1;
+  stage(rp, p.rp_all + in.rp_off, in.n + 1);
+  if (in.nnz > 0) stage(ci, p.ci_all + in.ci_off, in.nnz);
+  if (threadIdx.x == 0) err = kNoRow;
+  reset_launch(p, res);  // holds a barrier
+  for (int v = threadIdx.x; v < in.n; v += blockDim.x) {
+    if (row_bad(rp, in.n, in.nnz, v)) atomicMin(&err, v);
+    else if (p.words) pack_row(rp, ci, in.n, v, p.words, p.bits + static_cast<int64_t>(v) * p.words);
+  }
+  for (int e = threadIdx.x; e < in.nnz; e += blockDim.x) {
+    const int32_t bad = entry_bad_row(rp, ci, in.n, in.nnz, e);
+    if (bad != kNoRow) atomicMin(&err, bad);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    InstState s{};
+    s.best = kNoBest;
+    s.err_row = err;
+    s.greedy = -1;
+    *const_cast<Instance*>(p.inst) = in;
+    *p.ist = s;
+    *p.work = 1;
   }
 }
 
@@ -918,7 +976,10 @@ template <int MEM>
 __global__ void __launch_bounds__(1024) greedy_kernel(Params p) {
   __shared__ Ctrl c;
   int32_t* st = node_base<MEM>(p, blockIdx.x);
-  if (threadIdx.x == 0) c.rm_tail = c.one_tail = c.two_tail = 0;
+  if (threadIdx.x == 0) {
+    c.rm_tail = c.one_tail = c.two_tail = 0;
+    if (blockIdx.x == 0) p.res->t_greedy = realtime();
+  }
   Front f{};
   for (int j = blockIdx.x; j < p.num_inst; j += gridDim.x) {
     if (threadIdx.x == 0) c.err = load_relaxed(&p.ist[j].err_row) != kNoRow;
@@ -1002,7 +1063,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   __syncthreads();
   ActivityClock<PROF> clk;
   clk.begin();
-  if (tid == 0) watch_begin(c);
+  if (tid == 0) watch_begin(p, c);
   uint32_t headers = 0;  // thread 0: node headers read so far
   uint64_t root_header = 0;   // thread 0: a root's header, loaded when the root was taken
   bool header_ready = false;
@@ -1314,9 +1375,11 @@ __device__ void add_grouped(int32_t* dst, int32_t x) {
 // uncovered edge is counted from each end. Clear the cover output of instances without an
 // answer (rejected, out of budget, PVC no). (The traversal's workgroups add their statistics
 // to the result block themselves.) Packed entry offsets must fit in int32.
-__global__ void __launch_bounds__(256) finalize_kernel(Params p, int64_t vertices,
-                                                       int64_t entries, DevResult* res) {
-  (void)entries;
+// With ist_host, the last block to finish writes the instances' states and the result block to
+// host memory, which saves the call a copy command after its last kernel.
+__global__ void __launch_bounds__(256) finalize_kernel(Params p, int64_t vertices, DevResult* res,
+                                                       InstState* ist_host, DevResult* res_host) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) res->t_end = realtime();
   const int64_t waves = static_cast<int64_t>(gridDim.x) * (blockDim.x >> 6);
   for (int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x >> 6) + wave_id();
        w * 64 < vertices; w += waves) {
@@ -1360,7 +1423,28 @@ __global__ void __launch_bounds__(256) finalize_kernel(Params p, int64_t vertice
     res->error = *ctr_i32(p, kError);
     res->stop_reason = *ctr_i32(p, kStopReason);
   }
+  if (ist_host == nullptr) return;
+  __shared__ int last;
+  __threadfence();  // this thread's counts and result fields, before its block counts as done
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last = fetch_add(ctr_i32(p, kDone), 1) == static_cast<int32_t>(gridDim.x) - 1;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  // agent-scope loads: other blocks' counts and fields may sit in other XCDs' caches
+  using ull = unsigned long long;
+  const int states = p.num_inst * static_cast<int>(sizeof(InstState) / sizeof(ull));
+  constexpr int kRes = static_cast<int>(sizeof(DevResult) / sizeof(ull));
+  for (int i = threadIdx.x; i < states + kRes; i += blockDim.x) {
+    if (i < states)
+      reinterpret_cast<ull*>(ist_host)[i] = load_relaxed(reinterpret_cast<ull*>(p.ist) + i);
+    else
+      reinterpret_cast<ull*>(res_host)[i - states] =
+          load_relaxed(reinterpret_cast<ull*>(res) + (i - states));
+  }
 }
+static_assert(sizeof(InstState) % 8 == 0 && sizeof(DevResult) % 8 == 0, "copied in 8-byte words");
 
 // The reduction rules of one node, alone, on a degree array in device memory (instance 0 of
 // the launch, one workgroup). A rejected input leaves the degree array alone.
@@ -1388,6 +1472,7 @@ __global__ void __launch_bounds__(1024) reduce_kernel(Params p, int32_t* deg, in
 
 // Largest greedy cover size over the launch's instances (the stack depth bound of MVC).
 __global__ void __launch_bounds__(256) max_greedy_kernel(Params p, int32_t* out) {
+  if (threadIdx.x == 0) p.res->t_greedy_end = realtime();
   int32_t m = 0;
   for (int j = threadIdx.x; j < p.num_inst; j += blockDim.x) {
     const int32_t g = p.ist[j].greedy;
@@ -1495,11 +1580,18 @@ hipError_t launch_traverse(bool pvc, bool prof, const Params& p, int32_t wg_size
                          dim3(p.num_wg), dim3(wg_size), kargs, lds, stream);
 }
 
-hipError_t launch_finalize(const Params& p, int64_t vertices, int64_t entries, DevResult* res,
-                           hipStream_t stream) {
-  const int64_t items = vertices;
-  hipLaunchKernelGGL(finalize_kernel, dim3(grid_for(items, 256, 1024)), dim3(256), 0, stream, p,
-                     vertices, entries, res);
+hipError_t launch_prepare_small(const Params& p, DevResult* res, const Instance& in,
+                                hipStream_t stream) {
+  const size_t lds = 4 * (static_cast<size_t>(in.n) + 1 + static_cast<size_t>(in.nnz));
+  hipLaunchKernelGGL(prepare_small_kernel, dim3(1 + grid_for(p.q_cap, 4096, 16)), dim3(1024), lds,
+                     stream, p, res, in);
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize(const Params& p, int64_t vertices, DevResult* res, InstState* ist_host,
+                           DevResult* res_host, hipStream_t stream) {
+  hipLaunchKernelGGL(finalize_kernel, dim3(grid_for(vertices, 256, 1024)), dim3(256), 0, stream, p,
+                     vertices, res, ist_host, res_host);
   return hipGetLastError();
 }
 

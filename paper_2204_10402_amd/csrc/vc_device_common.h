@@ -198,8 +198,9 @@ __device__ __forceinline__ uint64_t realtime() { return __builtin_amdgcn_s_memre
 constexpr uint64_t kHostPollTicks = 5000;
 
 // Thread 0, at the start of a traversal workgroup.
-__device__ __forceinline__ void watch_begin(Ctrl& c) {
+__device__ __forceinline__ void watch_begin(const Params& p, Ctrl& c) {
   c.t_start = realtime();
+  if (blockIdx.x == 0) p.res->t_begin = c.t_start;
   c.t_host = c.t_start;
 }
 

@@ -39,6 +39,7 @@ struct vc_ctx {
   // mirrored in pinned host memory so that each call makes one copy in and one copy out
   DevBuf rp, ci, meta, payload, seq, ctr, stacks, covers, wg_stats, scratch, bits, gnodes;
   void* pinned = nullptr;
+  char* pinned_dev = nullptr;  // the same memory as the device addresses it
   size_t pinned_bytes = 0;
   std::vector<hipEvent_t> ev;  // two per launch group
   int32_t last_num_wg = 0;     // grid of the last traversal launch (its WgStats are kept)
@@ -52,6 +53,7 @@ struct vc_ctx {
   // A second context (own stream, worklist, counters, stacks) on which a batch's degree-array
   // launch runs while its bitset launches run on this one; created on first use.
   vc_ctx* aux = nullptr;
+  bool aux_busy = false;  // work was queued on it that no call has waited for (an error return)
   vc_ctx* stats_src = nullptr;  // the context holding the last traversal's per-workgroup stats
   // vc_abort: a host-pinned word, mapped for the device; vc_abort increments it and a launch
   // stops when it differs from its value at the start of the call
@@ -153,6 +155,10 @@ int ensure_pinned(vc_ctx* ctx, size_t bytes) {
     ctx->pinned = nullptr;
     return hip_fail(ctx, e, "hipHostMalloc");
   }
+  void* dptr = nullptr;
+  e = hipHostGetDevicePointer(&dptr, ctx->pinned, 0);
+  if (e != hipSuccess) return hip_fail(ctx, e, "hipHostGetDevicePointer");
+  ctx->pinned_dev = static_cast<char*>(dptr);
   ctx->pinned_bytes = bytes;
   return VC_OK;
 }
@@ -205,7 +211,7 @@ void init_state(vc::InstState* is, int32_t* work, int32_t m) {
   for (int32_t j = 0; j < m; ++j) {
     vc::InstState s{};
     s.err_row = vc::kNoRow;
-    s.best = 0x7FFFFFFF;
+    s.best = vc::kNoBest;
     s.greedy = -1;
     is[j] = s;
     work[j] = 1;
@@ -657,10 +663,16 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     if ((rc = choose_words(ctx, b.n[i], pvc, o, &words[i]))) return rc;
     order.push_back(i);
   }
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-    const int32_t kx = words[x] ? words[x] : 99, ky = words[y] ? words[y] : 99;
-    return kx < ky;
-  });
+  // by bitset words, degree arrays last, in the caller's order within a family (counting sort)
+  {
+    int32_t first[vc::kMaxBitsetWords + 2] = {};
+    auto key = [&](int32_t i) { return words[i] ? words[i] - 1 : vc::kMaxBitsetWords; };
+    for (int32_t i : order) ++first[key(i) + 1];
+    for (int32_t w = 0; w <= vc::kMaxBitsetWords; ++w) first[w + 1] += first[w];
+    std::vector<int32_t> sorted(order.size());
+    for (int32_t i : order) sorted[first[key(i)]++] = i;
+    order.swap(sorted);
+  }
   std::vector<int64_t> rp_off(b.count), ci_off(b.count), vtx_off(b.count);
   {
     int64_t r = 0, c = 0, v = 0;
@@ -737,10 +749,15 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     return use_aux && large(gi) ? ctx->aux : ctx;
   };
 
+  // results straight into the pinned mirror, where that is what the call stages in
+  const bool direct = m > 0 && m <= vc::kDirectInstances && host == ctx->pinned;
+  const bool small = m == 1 && h_inst[0].nnz <= vc::kSmallEntries &&
+                     static_cast<int64_t>(h_inst[0].n) + 1 + h_inst[0].nnz <= vc::kSmallWords;
+
   if (m > 0) {
     if ((rc = ensure(ctx, ctx->ctr, vc::kNumCounters * vc::kCounterStride * sizeof(int32_t)))) return rc;
     if ((rc = ensure_events(ctx, 4 * static_cast<size_t>(ng) + 4))) return rc;
-    if (ctx->aux) {
+    if (ctx->aux && ctx->aux_busy) {
       // whatever an earlier call left on the auxiliary stream (an error return does not wait
       // for it) finishes before this call's table overwrites the meta buffer
       VC_HIP(ctx, hipEventRecord(ctx->ev[2 * ng + 3], ctx->aux->stream));
@@ -749,9 +766,11 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     if (use_aux &&
         (rc = ensure(ctx, ctx->aux->ctr, vc::kNumCounters * vc::kCounterStride * sizeof(int32_t))))
       return rc;
-    // one copy in: instance table, fresh per-instance state and work counters
-    VC_HIP(ctx, hipMemcpyAsync(dev, host, L.res, hipMemcpyHostToDevice, st));
+    // one copy in: instance table, fresh per-instance state and work counters (a small single
+    // graph's are written by its validation kernel)
+    if (!small) VC_HIP(ctx, hipMemcpyAsync(dev, host, L.res, hipMemcpyHostToDevice, st));
     if (use_aux) {
+      ctx->aux_busy = true;
       VC_HIP(ctx, hipEventRecord(ctx->ev[2 * ng + 2], st));
       VC_HIP(ctx, hipStreamWaitEvent(ctx->aux->stream, ctx->ev[2 * ng + 2], 0));
     }
@@ -769,7 +788,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
   DevResult* d_res = reinterpret_cast<DevResult*>(dev + L.res);
   int32_t* d_greedy = reinterpret_cast<int32_t*>(dev + L.gmax);
   std::vector<Params> params(ng);
-  float greedy_ms = 0.f;
+  double greedy_ms = 0.0;
   const int cus = ctx->prop.multiProcessorCount;
 
   // Everything of one launch group up to (and, if `final`, including) the cover check, with
@@ -877,14 +896,12 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       p.timeout_ticks = std::max<uint64_t>(1, static_cast<uint64_t>(left_ms * ctx->clock_khz));
     }
 
-    VC_HIP(ctx, vc::launch_prepare(p, dres, g.vertices, g.entries, gst));
+    if (small) VC_HIP(ctx, vc::launch_prepare_small(p, dres, h_inst[0], gst));
+    else VC_HIP(ctx, vc::launch_prepare(p, dres, g.vertices, g.entries, gst));
     if (!pvc) {
       const int gws = g.words ? 64 : one_workgroup_size(g.n_max, pl);
-      hipEvent_t e0 = ctx->ev[2 * ng + 4 + 2 * gi], e1 = ctx->ev[2 * ng + 5 + 2 * gi];
-      VC_HIP(ctx, hipEventRecord(e0, gst));
       if (g.words) VC_HIP(ctx, vc::launch_bitset_greedy(p, gst));
       else VC_HIP(ctx, vc::launch_greedy(p, gws, gst));
-      VC_HIP(ctx, hipEventRecord(e1, gst));
       if (g.words || ctx->ws) {
         // A path branches at most best - 1 <= n - 1 times. Bitset nodes are a few dozen bytes,
         // so their stacks are provisioned for that bound straight away instead of waiting on
@@ -925,11 +942,18 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     }
     lc->last_num_wg = pl.num_wg;
     ctx->stats_src = lc;
-    VC_HIP(ctx, hipEventRecord(ctx->ev[2 * gi], gst));
+    // (the launch's times come from the device clock, in its result block; an event costs a few
+    // microseconds of the queue on either side of a kernel, so only the tuner's trials use them)
+    if (!final) VC_HIP(ctx, hipEventRecord(ctx->ev[2 * gi], gst));
     if (g.words) VC_HIP(ctx, vc::launch_bitset_traverse(pvc, prof, p, gst));
     else VC_HIP(ctx, vc::launch_traverse(pvc, prof, p, pl.wg_size, gst));
-    VC_HIP(ctx, hipEventRecord(ctx->ev[2 * gi + 1], gst));
-    if (final) VC_HIP(ctx, vc::launch_finalize(p, g.vertices, g.entries, dres, gst));
+    if (!final) VC_HIP(ctx, hipEventRecord(ctx->ev[2 * gi + 1], gst));
+    if (final)
+      VC_HIP(ctx, vc::launch_finalize(
+                      p, g.vertices, dres,
+                      direct ? reinterpret_cast<InstState*>(ctx->pinned_dev + L.ist) + g.begin : nullptr,
+                      direct ? reinterpret_cast<DevResult*>(ctx->pinned_dev + L.res) + gi : nullptr,
+                      gst));
     return VC_OK;
   };
 
@@ -1030,32 +1054,31 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     VC_HIP(ctx, hipStreamWaitEvent(st, ctx->ev[2 * ng + 3], 0));
   }
 
-  // one copy out: per-instance state, work counters and result blocks
-  if (m > 0)
+  // one copy out, unless the cover checks write there: per-instance state, work counters and
+  // result blocks
+  if (m > 0 && !direct)
     VC_HIP(ctx, hipMemcpyAsync(host + L.ist, dev + L.ist, L.gmax - L.ist, hipMemcpyDeviceToHost, st));
   uint8_t* h_cover = reinterpret_cast<uint8_t*>(host + L.cover);
   if (out.cover_host && total_n > 0)
     VC_HIP(ctx, hipMemcpyAsync(h_cover, covers, static_cast<size_t>(total_n), hipMemcpyDeviceToHost, st));
   VC_HIP(ctx, hipStreamSynchronize(st));
-  if (!pvc)
-    for (int32_t gi = 0; gi < ng; ++gi) {
-      float ms = 0.f;
-      VC_HIP(ctx, hipEventElapsedTime(&ms, ctx->ev[2 * ng + 4 + 2 * gi], ctx->ev[2 * ng + 5 + 2 * gi]));
-      greedy_ms += ms;
-    }
-  // traversal time: the launches' durations added up, or with the auxiliary context (whose
-  // largest group's launch starts first) the span until the last traversal ends
+  if (use_aux) ctx->aux_busy = false;
+  // The greedy's time, and the traversal's: from its first workgroup's start to the cover check,
+  // added up over the launches, or with the auxiliary context the span from the first launch's
+  // start until the last one's end.
+  const auto ticks_ms = [&](uint64_t from, uint64_t to) {
+    return to > from ? static_cast<double>(to - from) / static_cast<double>(ctx->clock_khz) : 0.0;
+  };
   double kernel_ms = 0.0;
+  uint64_t first_begin = UINT64_MAX, last_end = 0;
   for (int32_t gi = 0; gi < ng; ++gi) {
-    float ms = 0.f;
-    if (use_aux) {
-      VC_HIP(ctx, hipEventElapsedTime(&ms, ctx->ev[2 * (ng - 1)], ctx->ev[2 * gi + 1]));
-      kernel_ms = std::max(kernel_ms, static_cast<double>(ms));
-    } else {
-      VC_HIP(ctx, hipEventElapsedTime(&ms, ctx->ev[2 * gi], ctx->ev[2 * gi + 1]));
-      kernel_ms += ms;
-    }
+    const DevResult& r = h_res[gi];
+    if (!pvc) greedy_ms += ticks_ms(r.t_greedy, r.t_greedy_end ? r.t_greedy_end : r.t_begin);
+    kernel_ms += ticks_ms(r.t_begin, r.t_end);
+    first_begin = std::min(first_begin, r.t_begin);
+    last_end = std::max(last_end, r.t_end);
   }
+  if (use_aux) kernel_ms = ticks_ms(first_begin, last_end);
 
   // launch-wide failures end the whole call
   for (int32_t gi = 0; gi < ng; ++gi) {

@@ -27,6 +27,7 @@ enum : int32_t {
 };
 
 constexpr int32_t kNoRow = 0x7FFFFFFF;  // err_row of a graph that passed every check
+constexpr int32_t kNoBest = 0x7FFFFFFF; // best of an instance without a cover yet
 
 // Control words of one launch, each on its own 128-byte line so unrelated atomics never share
 // a line.
@@ -40,7 +41,8 @@ enum CounterSlot : int {
   kAbort = 6,      // int32: non-zero stops every workgroup (internal error)
   kError = 7,      // int32: internal error code (1 = stack overflow, 2 = node of no instance)
   kStopReason = 8, // int32: why the launch was stopped from outside the search (kStop*)
-  kNumCounters = 9,
+  kDone = 9,       // int32: blocks of the cover check that have finished
+  kNumCounters = 10,
 };
 
 // Reasons a launch stops before its search ends, other than an internal error.
@@ -203,7 +205,24 @@ struct DevResult {
   int64_t dequeues;
   int64_t instances;
   int64_t cycles[kNumActivities];
+  // The device's constant clock: the greedy's first block, what follows the greedy, the
+  // traversal's first workgroup, the cover check.
+  uint64_t t_greedy;
+  uint64_t t_greedy_end;
+  uint64_t t_begin;
+  uint64_t t_end;
 };
+
+// Instances up to which the cover check writes the call's results to host memory itself (its last
+// block copies them, one device-memory latency per 256 of their words) instead of leaving them to
+// a copy command.
+constexpr int32_t kDirectInstances = 64;
+
+// A single graph is validated by one workgroup from a copy in LDS, and its tables are written on
+// the way, up to these sizes; larger ones by one thread per entry over the whole device, after a
+// copy command for the tables.
+constexpr int32_t kSmallEntries = 8192;
+constexpr int32_t kSmallWords = 12288;  // row pointers and entries together
 
 // Kernel launchers. All run on `stream`; they return the HIP status of the launch itself.
 // `vertices` / `entries` are totals over the launch's instances (sum of n, sum of nnz).
@@ -212,12 +231,18 @@ struct DevResult {
 // Reset the launch's control words, result block and worklist tickets, and validate every CSR.
 hipError_t launch_prepare(const Params& p, DevResult* res, int64_t vertices, int64_t entries,
                           hipStream_t stream);
+// The same for a launch of the one small graph `in` (see kSmallEntries), which also writes the
+// instance table, state and work counter.
+hipError_t launch_prepare_small(const Params& p, DevResult* res, const Instance& in,
+                                hipStream_t stream);
 hipError_t launch_greedy(const Params& p, int32_t wg_size, hipStream_t stream);
 int greedy_grid(const Params& p);
 hipError_t launch_traverse(bool pvc, bool prof, const Params& p, int32_t wg_size,
                            hipStream_t stream);
-hipError_t launch_finalize(const Params& p, int64_t vertices, int64_t entries, DevResult* res,
-                           hipStream_t stream);
+// With `ist_host` / `res_host` (host memory as the device sees it), the instances' states and the
+// result block are also written there.
+hipError_t launch_finalize(const Params& p, int64_t vertices, DevResult* res, InstState* ist_host,
+                           DevResult* res_host, hipStream_t stream);
 hipError_t launch_reduce(const Params& p, int32_t wg_size, int32_t* deg, int32_t* s,
                          int64_t bound, hipStream_t stream);
 hipError_t traverse_occupancy(bool pvc, bool prof, bool global_node, int32_t rp_lds,

@@ -295,3 +295,25 @@ def test_pvc_family_by_size_and_options(solver, oracle_lib, n):
     with pytest.raises(vc.VCError) as e:
         solver.pvc(g, tau - 1, vc.Options(node_budget=1))
     assert e.value.code == vc.ERR_BUDGET or want <= 1
+
+
+@pytest.mark.parametrize("count", [1, 2, 63, 64, 65, 130])
+def test_results_of_batches_around_the_direct_limit(solver, oracle_lib, count):
+    """Up to 64 graphs the cover check writes the results to host memory, above that a copy
+    command brings them: sizes, decisions, node counts and covers are the oracle's either way, on
+    a second call with other graphs too."""
+    for seed in (0, 1):
+        gs = [G.erdos_renyi(24 + (7 * i + 13 * seed) % 50, 0.09, 800 + 31 * seed + i)
+              for i in range(count)]
+        want = [oracle.mvc(g) for g in gs]
+        mv = solver.mvc_batch(gs)
+        assert mv.size.tolist() == [w.size for w in want]
+        for i, g in enumerate(gs):
+            c = np.asarray(mv.cover_of(i))
+            assert oracle.is_cover(g, c) and int(c.sum()) == want[i].size, i
+        ks = [max(w.size - 1, 0) for w in want]
+        no = solver.pvc_batch(gs, ks)
+        o = [oracle.pvc(g, k) for g, k in zip(gs, ks)]
+        assert no.yes.tolist() == [x.yes for x in o]
+        assert [int(no.nodes[i]) for i in range(count) if not o[i].yes] == \
+            [x.nodes for x in o if not x.yes]

@@ -481,6 +481,38 @@ def test_candidate_lists_overflow(solver, oracle_lib, torch_cuda, shape, kernel)
     assert solver.pvc(g, tau, o).yes and not solver.pvc(g, tau - 1, o).yes
 
 
+@pytest.mark.parametrize("name,make,tau", [
+    ("8190 entries", lambda: G.complete(91), 90), ("8372 entries", lambda: G.complete(92), 91),
+    ("12287 words", lambda: G.path(4096), 2048), ("12290 words", lambda: G.path(4097), 2048),
+    ("one edge", lambda: G.path(2), 1), ("no edge", lambda: G.empty(3), 0)])
+def test_validation_on_both_sides_of_the_small_graph_limit(solver, name, make, tau):
+    """A single graph of up to 8,192 entries and 12,288 CSR words is validated by one workgroup,
+    a larger one by the whole device: the same sizes and the same first offending row (as the
+    format defines it) just below and above the limits."""
+    import paper_2204_10402_amd as vc
+    g = make()
+    assert solver.mvc(g).size == tau
+    assert solver.pvc(g, tau).yes and (tau == 0 or not solver.pvc(g, tau - 1).yes)
+    if g.nnz < 4:
+        return
+
+    class Raw:
+        pass
+    rng = np.random.default_rng(g.nnz)
+    for _ in range(4):
+        bad = Raw()
+        bad.n, bad.row_ptr, bad.col_idx = g.n, g.row_ptr.copy(), g.col_idx.copy()
+        j = int(rng.integers(0, g.nnz))
+        bad.col_idx[j] = int(rng.integers(-1, g.n + 1))
+        want = first_bad_row(bad.n, bad.row_ptr, bad.col_idx)
+        if want is None:
+            continue
+        with pytest.raises(vc.VCError) as ei:
+            solver.mvc(bad)
+        assert ei.value.code == vc.ERR_INVALID_GRAPH and f"row {want} " in str(ei.value)
+    assert solver.mvc(g).size == tau
+
+
 @pytest.mark.parametrize("kind", ["out_of_range", "self_loop", "asymmetric", "unsorted"])
 def test_invalid_entry_deep_in_a_large_graph(solver, kind):
     """A defect in one entry of G(600, 0.05) (about 18,000 entries, many validation blocks):
