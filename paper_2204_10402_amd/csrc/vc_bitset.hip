@@ -777,7 +777,9 @@ constexpr uint32_t kDonateNodes = 8;
 // the launch's worklist when all of its wavefronts have run out.
 template <int W, bool PVC, bool PROF, bool SO>
 __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
-    bitset_traverse_kernel(Params p) {
+    bitset_traverse_kernel(Params args) {
+  const int rules = args.rules;
+  const int32_t threshold = static_cast<int32_t>(args.q_threshold);
   extern __shared__ uint64_t adj_lds[];
   __shared__ Ctrl c;
   __shared__ Team<W> team;
@@ -788,12 +790,12 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(wave_id());
-  const int waves = p.team;
+  const int waves = args.team;
   Rows<W> r;
   ActivityClock<PROF> clk;
   clk.begin();
   if (tid == 0) {
-    watch_begin(p, c);
+    watch_begin(args, c);
     tally = WgStats{};
     team.nodes = 0;
   }
@@ -809,18 +811,20 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
   // are addressed through separate pointers, each access under a uniform branch, so that LDS
   // entries are read and written with LDS instructions rather than flat ones (a flat access
   // waits for every outstanding memory operation, the node header's load included).
-  const bool stack_lds = p.stack_lds != 0;
-  int32_t* const lstack = reinterpret_cast<int32_t*>(adj_lds + static_cast<size_t>(p.n_max) * W) +
-                          static_cast<size_t>(wave) * p.depth_cap * kStride;
-  int32_t* const gstack =
-      p.stacks + (static_cast<size_t>(wg) * waves + wave) * p.depth_cap * kStride;
+  const bool stack_lds = args.stack_lds != 0;
+  int32_t* const lstack = reinterpret_cast<int32_t*>(adj_lds + static_cast<size_t>(args.n_max) * W) +
+                          static_cast<size_t>(wave) * args.depth_cap * kStride;
+  const auto gstack = [&]() -> int32_t* {
+    const Params& p = cold_params();
+    return p.stacks + (static_cast<size_t>(wg) * waves + wave) * p.depth_cap * kStride;
+  };
   // The stack is a ring of depth_cap entries holding [bot, top): pops take the top, handovers and
   // donations take the bottom (the oldest deferred child, nearest its sub-tree root). Every entry
   // belongs to the team's instance.
   int top = 0, bot = 0;
   // ring slots of top and bot, kept reduced modulo depth_cap (no division per push or pop)
   int top_slot = 0, bot_slot = 0;
-  const int cap = p.depth_cap;
+  const int cap = args.depth_cap;
   bool have = false;
   bool held = false;     // this wavefront holds a sub-tree (counted in team.active)
   bool holding = false;  // thread 0: the team holds a sub-tree of the launch (a root, a queued node)
@@ -830,7 +834,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
   // Statistics: nodes and stack traffic are counted in 32 bits since the last flush (instance
   // switch, budget report, or every 2^30 nodes) and folded into `tally` there.
   uint32_t unreported = 0, pushes32 = 0, pops32 = 0;  // since the last flush
-  const uint32_t flush_at = p.node_budget > 0 ? static_cast<uint32_t>(p.budget_chunk) : (1u << 30);
+  const uint32_t flush_at = args.node_budget > 0 ? static_cast<uint32_t>(args.budget_chunk) : (1u << 30);
   int max_depth = 0;
   uint32_t headers = 0;  // nodes since the last header, and so on (see kPollNodes)
   uint32_t so_path = 0;  // StackOnly: the current path index
@@ -849,7 +853,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
         --top;
         top_slot = top_slot == 0 ? cap - 1 : top_slot - 1;
         if (stack_lds) bits_load_lds<W>(lstack + top_slot * kStride, L, pending, inst);
-        else bits_load<W>(gstack + static_cast<size_t>(top_slot) * kStride, L, pending, inst);
+        else bits_load<W>(gstack() + static_cast<size_t>(top_slot) * kStride, L, pending, inst);
         ++pops32;
         clk.charge(kActAcquire);
       } else if constexpr (SO) {
@@ -858,6 +862,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
         // which child at depth d); it walks each path down from the root, then walks the sub-tree
         // with its stack. A node above the start depth counts for the instance only on the path
         // whose remaining bits are zero, so the instance's node count is the tree's.
+        const Params& p = cold_params();
         if (cur < 0) {
           cur_n = load_adjacency<W>(p, 0, adj_lds, r);
           const Instance in = p.inst[0];
@@ -931,6 +936,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       } else {
         // the whole team is out of work: every wavefront of the workgroup comes here
         held = false;
+        const Params& p = cold_params();
         __syncthreads();
         if (tid == 0) {
           if (holding) release_work(p, cur);
@@ -1038,6 +1044,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     uint64_t hraw = 0;
     int32_t qraw = 0, abort_raw = 0, open_raw = 1;
     if (poll) {
+      const Params& p = cold_params();
       hraw = inst_header(p, cur);
       if (p.q_threshold > 0) qraw = load_relaxed(ctr_i32(p, kQCount));
       abort_raw = load_relaxed(ctr_i32(p, kAbort));
@@ -1052,16 +1059,23 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
         seen_best = min(seen_best, __builtin_amdgcn_readfirstlane(
                                        static_cast<int>(team_load(&team.best))));
     }
-    const int32_t early = PVC ? cur_k : seen_best - 1;
-    reduce_bits<W>(r, L, D, adj_lds, early, p.rules);
-
-    if (poll) {
-      const uint64_t h = uniform64(hraw);
-      const int32_t state = static_cast<int32_t>(h >> 32);
-      if ((state & kInstOutOfBudget) || (PVC && (state & kInstFound))) inst_done = true;
-      if (!PVC) seen_best = min(seen_best, static_cast<int32_t>(static_cast<uint32_t>(h)));
-      seen_count = __builtin_amdgcn_readfirstlane(qraw);
-      stop |= __builtin_amdgcn_readfirstlane((abort_raw != 0 || open_raw == 0) ? 1 : 0);
+    int32_t bound = PVC ? cur_k : seen_best - 1;
+    for (bool looked = !poll;;) {
+      reduce_bits<W>(r, L, D, adj_lds, bound, rules);
+      if (!looked) {
+        looked = true;
+        const uint64_t h = uniform64(hraw);
+        const int32_t state = static_cast<int32_t>(h >> 32);
+        if ((state & kInstOutOfBudget) || (PVC && (state & kInstFound))) inst_done = true;
+        if (!PVC) seen_best = min(seen_best, static_cast<int32_t>(static_cast<uint32_t>(h)));
+        seen_count = __builtin_amdgcn_readfirstlane(qraw);
+        stop |= __builtin_amdgcn_readfirstlane((abort_raw != 0 || open_raw == 0) ? 1 : 0);
+        if (!PVC && seen_best - 1 < bound) {  // continue under the fresh best
+          bound = seen_best - 1;
+          continue;
+        }
+      }
+      break;
     }
     clk.charge(kActReduce);
     if (stop | static_cast<int>(inst_done)) {
@@ -1080,6 +1094,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     if (++unreported >= flush_at) {
       int spent = 0;
       if (lane == 0) {
+        const Params& p = cold_params();
         if (p.node_budget > 0) spent = bits_report_nodes(p, cur, unreported);
         else __hip_atomic_fetch_add(&team.nodes, unreported, __ATOMIC_RELAXED,
                                     __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1089,12 +1104,6 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       }
       unreported = pushes32 = pops32 = 0;
       if (__builtin_amdgcn_readfirstlane(spent)) inst_done = true;
-    }
-
-    const int32_t bound = PVC ? cur_k : seen_best - 1;
-    if (!PVC && bound < early) {
-      reduce_bits<W>(r, L, D, adj_lds, bound, p.rules);
-      clk.charge(kActReduce);
     }
 
     const int32_t rr = bound - L.s;
@@ -1108,7 +1117,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     clk.charge(kActBranch);
     // (rr >= n - |S| leaves no room for the prune: |E| < (n - |S|)^2 / 2)
     const int32_t edges = degsum / 2;
-    if ((p.rules & kPruneEdges) && (p.rules & kRuleHigh) && rr < cur_n && edges > rr * rr) {
+    if ((rules & kPruneEdges) && (rules & kRuleHigh) && rr < cur_n && edges > rr * rr) {
       have = false;
       continue;
     }
@@ -1119,6 +1128,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
           __hip_atomic_fetch_min(&team.best, static_cast<uint32_t>(L.s), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
       }
+      const Params& p = cold_params();
       int won = 0;
       if (lane == 0) won = bits_claim<PVC>(p, cur, L.s);
       if (__builtin_amdgcn_readfirstlane(won)) {
@@ -1136,8 +1146,9 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     // branch on v_max: defer the N(v_max) child on this wavefront's stack, continue with the v_max
     // child. Idle wavefronts of the team take the oldest entries of the stack (the largest
     // sub-trees it holds) first; else, while the worklist is below its threshold, some are donated.
-    if (top - bot >= p.depth_cap) {  // cannot happen: the depth bound of §IV-E holds
+    if (top - bot >= cap) {  // cannot happen: the depth bound of §IV-E holds
       if (lane == 0) {
+        const Params& p = cold_params();
         atomicMax(ctr_i32(p, kError), 1);
         store_relaxed(ctr_i32(p, kAbort), 1);
       }
@@ -1149,7 +1160,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       continue;
     }
     if (stack_lds) bits_store<W>(lstack + top_slot * kStride, L, vmax, cur);
-    else bits_store<W>(gstack + static_cast<size_t>(top_slot) * kStride, L, vmax, cur);
+    else bits_store<W>(gstack() + static_cast<size_t>(top_slot) * kStride, L, vmax, cur);
     ++top;
     top_slot = top_slot + 1 == cap ? 0 : top_slot + 1;
     int given = 0;
@@ -1157,12 +1168,14 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     ++quiet;
     if (idle) {
       if (!stack_lds) __threadfence_block();  // lane 0's entry, about to be read by other lanes
-      given = team_give<W>(team, idle, top - bot, lstack, gstack, stack_lds, bot_slot, cap);
-    } else if (seen_count < static_cast<int32_t>(p.q_threshold) &&
+      given = team_give<W>(team, idle, top - bot, lstack, stack_lds ? nullptr : gstack(), stack_lds,
+                           bot_slot, cap);
+    } else if (seen_count < threshold &&
                (waves == 1 || (top - bot > 1 && quiet >= kDonateNodes))) {
       const int m = min(kDonateMost, (top - bot + 1) / 2);
       if (!stack_lds) __threadfence_block();
-      if (bits_enqueue<W>(p, c, cur, m, lstack, gstack, stack_lds, bot_slot)) {
+      const Params& p = cold_params();
+      if (bits_enqueue<W>(p, c, cur, m, lstack, stack_lds ? nullptr : gstack(), stack_lds, bot_slot)) {
         given = m;
         if (lane == 0) add_tally(&tally.enqueues, m);
       }
@@ -1191,6 +1204,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
   }
   __syncthreads();
   if (tid == 0) {
+    const Params& p = cold_params();
     if (cur >= 0) bits_report_nodes(p, cur, team.nodes);
     publish_wg_stats(p, wg, tally);
   }

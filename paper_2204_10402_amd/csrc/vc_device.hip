@@ -1051,9 +1051,10 @@ __device__ __forceinline__ void report_nodes(const Params& p, int j, int64_t cou
 // the worklist, walks that node's sub-tree depth first with its stack, and loads an instance
 // (row pointers) only when the node it takes belongs to another one than the last.
 template <bool PVC, bool PROF, int MEM, bool SO>
-__global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
+__global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
   __shared__ Ctrl c;
-  int32_t* st = node_base<MEM>(p, blockIdx.x);
+  int32_t* st = node_base<MEM>(args, blockIdx.x);
+  const int rules = args.rules;
   const int wg = blockIdx.x;
   const int tid = threadIdx.x;
   if (tid == 0) {
@@ -1063,13 +1064,16 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   __syncthreads();
   ActivityClock<PROF> clk;
   clk.begin();
-  if (tid == 0) watch_begin(p, c);
+  if (tid == 0) watch_begin(args, c);
   uint32_t headers = 0;  // thread 0: node headers read so far
   uint64_t root_header = 0;   // thread 0: a root's header, loaded when the root was taken
   bool header_ready = false;
   bool first = true;          // the workgroup has not looked for work yet
 
-  int32_t* stack = p.stacks + static_cast<size_t>(wg) * p.depth_cap * p.stride;
+  const auto stack_slot = [&](const Params& p, int at) -> int32_t* {
+    return p.stacks +
+           (static_cast<size_t>(wg) * p.depth_cap + static_cast<size_t>(at % p.depth_cap)) * p.stride;
+  };
   // The stack is a ring of depth_cap entries holding [bot, top): pops take the top, donations
   // take the bottom (the oldest deferred child, nearest its sub-tree root). Every entry belongs
   // to the instance of the sub-tree being walked.
@@ -1079,7 +1083,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   bool marked = false;    // the node in LDS has flagged vertices still to be removed
   int cur = -1;           // instance of the node in LDS
   int32_t cur_k = 0, cur_vtx = 0;
-  Node nd = empty_node<MEM>(p, st);
+  Node nd = empty_node<MEM>(args, st);
   Front f{};
   int64_t nodes = 0, pushes = 0, pops = 0, enqueues = 0, dequeues = 0, insts = 0;
   int64_t unreported = 0;  // nodes on `cur` not yet added to its counter
@@ -1088,12 +1092,13 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
 
   for (;;) {
     if (!have) {
+      const Params& p = cold_params();
       marked = false;   // whatever node comes next replaces the one in LDS
       f.rm = c.rm_tail;  // (what a dropped node still had marked is no longer to be removed)
       __syncthreads();  // every thread has read the last broadcast before thread 0 writes
       if (top > bot) {
         --top;
-        node_load(st, stack + static_cast<size_t>(top % p.depth_cap) * p.stride, p.stride);
+        node_load(st, stack_slot(p, top), p.stride);
         ++pops;
         __syncthreads();
         clk.charge(kActAcquire);
@@ -1135,7 +1140,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
           const int64_t bound = PVC ? static_cast<int64_t>(cur_k) : static_cast<int64_t>(c.best) - 1;
           ++nodes;
           if (owner) ++unreported;
-          reduce_node(nd, c, f, bound, p.rules, clk, marked);
+          reduce_node(nd, c, f, bound, rules, clk, marked);
           marked = false;
           const int32_t s = st[nd.n];
           const int64_t r = bound - s;
@@ -1143,7 +1148,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
           int32_t degsum = 0;
           if (r >= 0) max_degree_and_sum(nd, c, f, vmax, degsum);
           const int64_t edges = degsum / 2;
-          if (r < 0 || ((p.rules & kPruneEdges) && (p.rules & kRuleHigh) && edges > r * r)) {
+          if (r < 0 || ((rules & kPruneEdges) && (rules & kRuleHigh) && edges > r * r)) {
             reached = false;
           } else if (edges == 0) {  // a cover: recorded once, on the owning path
             if (owner) {
@@ -1240,6 +1245,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
     // node header: the instance's flags and current best (one load), and every 16 nodes
     // the launch-wide stop (idle workgroups also look at it while they wait for work)
     if (tid == 0) {
+      const Params& p = cold_params();
       const uint64_t h = header_ready ? root_header : inst_header(p, cur);
       header_ready = false;
       const int32_t state = static_cast<int32_t>(h >> 32);
@@ -1258,13 +1264,16 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
 
     ++nodes;
     ++unreported;
-    if (p.node_budget > 0 && unreported >= p.budget_chunk) {
-      if (tid == 0) report_nodes(p, cur, unreported);
-      unreported = 0;
+    {
+      const Params& p = cold_params();
+      if (p.node_budget > 0 && unreported >= p.budget_chunk) {
+        if (tid == 0) report_nodes(p, cur, unreported);
+        unreported = 0;
+      }
     }
 
     const int64_t bound = PVC ? static_cast<int64_t>(cur_k) : static_cast<int64_t>(c.best) - 1;
-    reduce_node(nd, c, f, bound, p.rules, clk, marked);
+    reduce_node(nd, c, f, bound, rules, clk, marked);
     marked = false;
     clk.charge(kActReduce);
 
@@ -1282,10 +1291,11 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
     max_degree_and_sum(nd, c, f, vmax, degsum);
     clk.charge(kActBranch);
     const int64_t edges = degsum / 2;
-    if ((p.rules & kPruneEdges) && (p.rules & kRuleHigh) && edges > r * r) {
+    if ((rules & kPruneEdges) && (rules & kRuleHigh) && edges > r * r) {
       have = false;
       continue;
     }
+    const Params& p = cold_params();
     if (edges == 0) {  // a vertex cover of size s
       if (tid == 0) c.status = claim_solution<PVC>(p, cur, s);
       __syncthreads();
@@ -1308,7 +1318,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
     if (p.q_threshold > 0) {
       const bool from_stack = top > bot;
       const int32_t* oldest =
-          from_stack ? stack + static_cast<size_t>(bot % p.depth_cap) * p.stride : nullptr;
+          from_stack ? stack_slot(p, bot) : nullptr;
       if (try_enqueue(p, nd, c, vmax, oldest, cur)) {
         ++enqueues;
         if (from_stack) ++bot;
@@ -1323,7 +1333,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
         }
         break;
       }
-      node_store(stack + static_cast<size_t>(top % p.depth_cap) * p.stride, st, p.stride, n, vmax);
+      node_store(stack_slot(p, top), st, p.stride, n, vmax);
       ++top;
       ++pushes;
       if (top - bot > max_depth) max_depth = top - bot;
@@ -1337,6 +1347,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params p) {
   clk.end();
 
   if (tid == 0) {
+    const Params& p = cold_params();
     if (cur >= 0) report_nodes(p, cur, unreported);
     WgStats w{};
     w.nodes = nodes;

@@ -13,6 +13,16 @@ namespace vc {
 constexpr int32_t kSent = -1;
 constexpr int kMaxWaves = 16;             // 1024 threads
 
+// The kernel's Params (its first argument) read again from the kernel argument segment. Used on the
+// paths that a traversal takes once in many nodes, so that their pointers and sizes are scalar
+// loads there instead of scalar registers held (and spilled to vector lanes) through the loop.
+__device__ __forceinline__ const Params& cold_params() {
+  using Segment = const __attribute__((address_space(4))) Params*;
+  Segment k = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(k));  // a fresh value: nothing loaded through it is kept from before
+  return *(const Params*)k;
+}
+
 // ---- scoped atomics ------------------------------------------------------------------------
 
 __device__ __forceinline__ int32_t* ctr_i32(const Params& p, int slot) {
