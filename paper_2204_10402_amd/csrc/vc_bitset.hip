@@ -33,6 +33,12 @@ struct Live {  // a search node, uniform across the wavefront
   int32_t s;
 };
 
+// After a branch that only some lanes take, and before a jump: keeps the lanes' meeting point a
+// block of its own. Folded into the jump's target, it makes every value that meets there look
+// different from lane to lane to the compiler, the loop's exit included, and the node, the stack
+// positions and all masks move from scalar to vector registers.
+__device__ __forceinline__ void rejoin() { __builtin_amdgcn_wave_barrier(); }
+
 __device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
@@ -186,8 +192,9 @@ __device__ __forceinline__ int lowest_bit(const uint64_t (&N)[W]) {
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     const uint32_t lo = static_cast<uint32_t>(N[w]), hi = static_cast<uint32_t>(N[w] >> 32);
-    const uint32_t flo = lo ? (static_cast<uint32_t>(__builtin_ctz(lo)) | (64u * w)) : 0xFFFFFFFFu;
-    const uint32_t fhi = hi ? (static_cast<uint32_t>(__builtin_ctz(hi)) | (64u * w + 32u)) : 0xFFFFFFFFu;
+    // (the search of an empty half gives all ones, which the or leaves: no test of its own)
+    const uint32_t flo = (lo ? static_cast<uint32_t>(__builtin_ctz(lo)) : 0xFFFFFFFFu) | (64u * w);
+    const uint32_t fhi = (hi ? static_cast<uint32_t>(__builtin_ctz(hi)) : 0xFFFFFFFFu) | (64u * w + 32u);
     best = min(best, min(flo, fhi));
   }
   return static_cast<int>(best);
@@ -319,25 +326,37 @@ __device__ __forceinline__ void reduce_bits(const Rows<W>& r, Live<W>& L, Degree
   }
 }
 
-// Live vertex of maximum degree (smallest id on ties) and the sum of live degrees, from the
-// cached degrees: one 32-bit key (degree << 16 | 0xFFFF - id) per vertex, reduced with DPP.
+// Live vertex of maximum degree (smallest id on ties) and that degree, from the cached degrees: one
+// 32-bit key (degree << 16 | 0xFFFF - id) per vertex, reduced with DPP.
 template <int W>
 __device__ __forceinline__ void bits_max_degree(const Live<W>& L, const Degrees<W>& D, int& vmax,
-                                                int32_t& degsum) {
+                                                int32_t& dmax) {
   uint32_t key = 0;
-  int32_t sum = 0;
   const int lane = lane_id();
 #pragma unroll
   for (int wv = 0; wv < W; ++wv) {
-    const bool live = held_live(L, wv);
     const uint32_t k = (static_cast<uint32_t>(D.deg[wv]) << 16) |
                        (0xFFFFu - static_cast<uint32_t>(wv * 64 + lane));
-    key = max(key, live ? k : 0u);
-    sum += live ? D.deg[wv] : 0;
+    key = max(key, held_live(L, wv) ? k : 0u);
   }
   key = wave_max32(key);
-  degsum = wave_sum(sum);
   vmax = static_cast<int>(0xFFFFu - (key & 0xFFFFu));
+  dmax = static_cast<int32_t>(key >> 16);
+}
+
+// The stop test's |E| > limit (§II-B), limit >= 0. The degrees are added up only where the live
+// vertices could reach the limit at all, each with the largest degree.
+template <int W>
+__device__ __forceinline__ bool bits_more_edges(const Live<W>& L, const Degrees<W>& D, int32_t dmax,
+                                                int32_t limit) {
+  int32_t live = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) live += __popcll(L.bits[w]);
+  if (live * dmax <= 2 * limit) return false;
+  int32_t sum = 0;
+#pragma unroll
+  for (int wv = 0; wv < W; ++wv) sum += held_live(L, wv) ? D.deg[wv] : 0;
+  return wave_sum(sum) / 2 > limit;
 }
 
 // The v_max child: v joins the cover.
@@ -567,6 +586,7 @@ __device__ __forceinline__ bool bits_enqueue(const Params& p, Ctrl& c, int inst,
       store_release(p.seq + slot, 2u * lap + 1u);
     }
   }
+  rejoin();
   return true;
 }
 
@@ -651,6 +671,7 @@ __device__ __forceinline__ int team_give(Team<W>& t, uint32_t idle, int avail,
     bits_copy_entry<W>(t.box[lane], lstack, gstack, stack_lds, ring_slot(bot_slot, e, cap));
     __hip_atomic_store(&t.mail[lane], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
+  rejoin();
   return given;
 }
 
@@ -711,9 +732,9 @@ __global__ void __launch_bounds__(64) bitset_greedy_kernel(Params p) {
     for (;;) {
       reduce_bits<W>(r, L, D, adj_lds, unbounded, kRuleDeg1 | kRuleTri);
       int vmax;
-      int32_t degsum;
-      bits_max_degree<W>(L, D, vmax, degsum);
-      if (degsum == 0) break;
+      int32_t dmax;
+      bits_max_degree<W>(L, D, vmax, dmax);
+      if (dmax == 0) break;
       remove_vertex_bits<W>(r, L, D, vmax);
     }
     write_cover<W>(p.covers + p.inst[j].vtx_off, L, n);
@@ -903,13 +924,12 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
           reduce_bits<W>(r, L, D, adj_lds, bound, p.rules);
           const int32_t rr = bound - L.s;
           int vmax = 0;
-          int32_t degsum = 0;
-          if (rr >= 0) bits_max_degree<W>(L, D, vmax, degsum);
-          const int32_t edges = degsum / 2;
+          int32_t dmax = 0;
+          if (rr >= 0) bits_max_degree<W>(L, D, vmax, dmax);
           if (rr < 0 || ((p.rules & kPruneEdges) && (p.rules & kRuleHigh) && rr < cur_n &&
-                         edges > rr * rr)) {
+                         bits_more_edges<W>(L, D, dmax, rr * rr))) {
             reached = false;
-          } else if (edges == 0) {  // a cover: recorded once, on the owning path
+          } else if (dmax == 0) {  // a cover: recorded once, on the owning path
             if (owner) {
               int won = 0;
               if (tid == 0) won = bits_claim<PVC>(p, cur, L.s);
@@ -965,6 +985,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
             atomicMax(ctr_i32(p, kError), 2);
             store_relaxed(ctr_i32(p, kAbort), 1);
           }
+          rejoin();
           break;
         }
         // a root's input check and the instance's header are loaded now, while the instance is
@@ -1014,6 +1035,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
           const int rejected = __builtin_amdgcn_readfirstlane(err_row != kNoRow);
           if (rejected) {  // rejected input: no search (PVC: the instance is settled)
             if (PVC && tid == 0) fetch_add(ctr_i32(p, kOpen), -1);
+            rejoin();
             continue;
           }
           root_bits<W>(L, cur_n);
@@ -1112,21 +1134,22 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       continue;
     }
     int vmax;
-    int32_t degsum;
-    bits_max_degree<W>(L, D, vmax, degsum);
+    int32_t dmax;
+    bits_max_degree<W>(L, D, vmax, dmax);
     clk.charge(kActBranch);
     // (rr >= n - |S| leaves no room for the prune: |E| < (n - |S|)^2 / 2)
-    const int32_t edges = degsum / 2;
-    if ((rules & kPruneEdges) && (rules & kRuleHigh) && rr < cur_n && edges > rr * rr) {
+    if ((rules & kPruneEdges) && (rules & kRuleHigh) && rr < cur_n &&
+        bits_more_edges<W>(L, D, dmax, rr * rr)) {
       have = false;
       continue;
     }
-    if (edges == 0) {  // a vertex cover of size |S|
+    if (dmax == 0) {  // a vertex cover of size |S|
       if (!PVC && L.s < seen_best) {
         seen_best = L.s;
         if (lane == 0)
           __hip_atomic_fetch_min(&team.best, static_cast<uint32_t>(L.s), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        rejoin();
       }
       const Params& p = cold_params();
       int won = 0;
@@ -1135,6 +1158,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
         write_cover<W>(p.covers + cur_vtx, L, cur_n);
         __threadfence();
         if (lane == 0) bits_publish<PVC>(p, cur, L.s);
+        rejoin();
       }
       // PVC: a cover of size <= k is recorded now, by this wavefront or another one
       if (PVC) inst_done = true;
@@ -1152,6 +1176,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
         atomicMax(ctr_i32(p, kError), 1);
         store_relaxed(ctr_i32(p, kAbort), 1);
       }
+      rejoin();
       if constexpr (SO) break;
       stop = 1;
       have = false;
@@ -1178,6 +1203,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       if (bits_enqueue<W>(p, c, cur, m, lstack, stack_lds ? nullptr : gstack(), stack_lds, bot_slot)) {
         given = m;
         if (lane == 0) add_tally(&tally.enqueues, m);
+        rejoin();
       }
       quiet = 0;
     }

@@ -62,7 +62,7 @@ __device__ __forceinline__ unsigned long long fetch_add(unsigned long long* a,
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t x) {
   return static_cast<uint32_t>(
-      __builtin_amdgcn_update_dpp(static_cast<int>(x), static_cast<int>(x), CTRL, 0xF, 0xF, false));
+      __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 __device__ __forceinline__ uint64_t dpp64(uint64_t x) {
