@@ -67,6 +67,7 @@ struct vc_ctx {
     size_t bytes = 0;
     size_t used = 0;
     bool host_heap = true;
+    bool narrow = false;  // the plan that needs least memory (run_in_workspace)
   };
   Workspace* ws = nullptr;
   std::vector<char> host_heap;
@@ -319,7 +320,8 @@ int choose_words(vc_ctx* ctx, int32_t n, bool pvc, const vc_options* o, int32_t*
   const bool force_arrays = flags & (VC_OPT_DEGREE_ARRAYS | VC_OPT_GLOBAL_NODES);
   if (force_bits && n > vc::kMaxBitsetN)
     return fail(ctx, VC_ERR_INVALID_ARG, "VC_OPT_BITSETS needs n <= 512");
-  const bool plain = pvc && !(o && o->wg_size) && !(flags & (VC_OPT_CSR_GLOBAL | VC_OPT_STACK_ONLY));
+  const bool plain = pvc && !(ctx->ws && ctx->ws->narrow) && !(o && o->wg_size) &&
+                     !(flags & (VC_OPT_CSR_GLOBAL | VC_OPT_STACK_ONLY));
   const int32_t most = plain ? vc::kAutoBitsetNPvc : vc::kAutoBitsetN;
   const bool bits = force_bits || (!force_arrays && n <= most);
   *words = bits ? (std::max(n, 1) + 63) / 64 : 0;
@@ -362,16 +364,18 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
     // registers) as long as their stack rings fit in LDS beside the adjacency matrix with room for
     // a second workgroup on the CU, and there is a workgroup for every instance: an instance
     // occupies one workgroup, so with more instances than workgroups smaller teams leave fewer
-    // wavefronts idle. One wavefront where the caller asks for 64-thread workgroups, for no donations (each
-    // workgroup then walks its whole sub-tree in depth-first order), or for StackOnly.
+    // wavefronts idle. One wavefront where the caller asks for 64-thread workgroups, for no
+    // donations (each workgroup then walks its whole sub-tree in depth-first order), or for
+    // StackOnly; and where a caller's workspace is too small for teams.
     const size_t lds_most = static_cast<size_t>(ctx->prop.maxSharedMemoryPerMultiProcessor) / 2 - 2048;
     if (!ctx->bitset_lds_set.count(std::make_tuple(words, pvc, prof))) {
       const bool so = o && (o->flags & VC_OPT_STACK_ONLY);
       VC_HIP(ctx, vc::bitset_lds_limit(words, pvc, prof, so, lds_most));
       if (!so) ctx->bitset_lds_set.insert(std::make_tuple(words, pvc, prof));
     }
-    const bool alone = o && (o->wg_size == 64 || o->wl_threshold == -1 ||
-                             (o->flags & VC_OPT_STACK_ONLY));
+    const bool alone = (ctx->ws && ctx->ws->narrow) ||
+                       (o && (o->wg_size == 64 || o->wl_threshold == -1 ||
+                              (o->flags & VC_OPT_STACK_ONLY)));
     int32_t team = alone ? 1 : sh.team ? sh.team : std::min(8, vc::bitset_max_team(words));
     if (!alone && !sh.team)
       while (team > 1 && bitset_team_lds(sh, team) > lds_most) team /= 2;
@@ -383,7 +387,10 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
       if ((rc = occupancy(ctx, words, pvc, prof, best_ws, pl.lds, n_max, &best_occ))) return rc;
       pl.num_wg = best_occ * cus;
       // Untuned, at most 16 wavefronts per CU in teams, and eight in workgroups of one: idle
-      // workgroups beyond that only add polling on the worklist counters in small searches.
+      // workgroups beyond that only add polling on the worklist counters in small searches. A
+      // smaller grid suits trees that spread over few workgroups (G(200, 0.5) PVC no, 87,000
+      // nodes: 1.8 ms on 512, 1.1 on 128) but not the long searches (G(240, 7/240), 10^8 nodes:
+      // 350 ms on 512, 528 on 256).
       if (!(o && o->num_wg > 0) && !sh.team)
         pl.num_wg = std::min(pl.num_wg, cus * (team > 1 ? std::max(1, 16 / team) : 8));
       if (o && o->grid_share > 0) pl.num_wg = std::max(1, pl.num_wg / o->grid_share);
@@ -499,7 +506,7 @@ void size_worklist(Plan& pl, const vc_options* o, uint64_t min_cap) {
   const uint64_t producers = static_cast<uint64_t>(pl.num_wg) * pl.team;
   uint64_t cap = o && o->wl_capacity ? static_cast<uint64_t>(o->wl_capacity)
                                      : std::max<uint64_t>(8ull * pl.num_wg, min_cap);
-  cap = std::max<uint64_t>(cap, 2ull * (pl.donate + 1) * producers);
+  cap = std::max<uint64_t>(cap, (pl.team > 1 ? 2ull * (pl.donate + 1) : pl.donate + 2ull) * producers);
   pl.cap = next_pow2(cap);
   uint64_t thr;
   if (o && o->wl_threshold == -1) thr = 0;
@@ -1233,11 +1240,12 @@ int32_t abort_mark(const vc_ctx* ctx) {
 // nothing of the workspace stays referenced (per-workgroup statistics included).
 class WorkspaceScope {
  public:
-  WorkspaceScope(vc_ctx* ctx, void* base, size_t bytes, bool host_heap) : ctx_(ctx) {
+  WorkspaceScope(vc_ctx* ctx, void* base, size_t bytes, bool host_heap, bool narrow) : ctx_(ctx) {
     if (!base) return;
     ws_.base = static_cast<char*>(base);
     ws_.bytes = bytes;
     ws_.host_heap = host_heap;
+    ws_.narrow = narrow;
     for (size_t i = 0; i < kBufs; ++i) {
       saved_[i] = *buf(i);
       *buf(i) = DevBuf{};
@@ -1275,6 +1283,24 @@ struct WsArgs {
   size_t bytes = 0;
   bool host_heap = true;   // host staging may grow beyond the pinned buffer
 };
+
+// run_batch, in the caller's workspace if there is one. Teams need more stacks and worklist slots
+// than workgroups of one wavefront, and PVC graphs above kAutoBitsetN as bitsets adjacency rows and
+// a worklist for each word count that degree arrays do not: a workspace too small for them is tried
+// again without either.
+int run_in_workspace(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, BatchOut& out,
+                     std::chrono::steady_clock::time_point t0, int32_t abort_base,
+                     const WsArgs& wsa) {
+  int rc;
+  {
+    WorkspaceScope scope(ctx, wsa.base, wsa.bytes, wsa.host_heap, false);
+    rc = run_batch(ctx, b, pvc, o, out, t0, abort_base);
+  }
+  if (rc != VC_ERR_NO_MEMORY || !wsa.base) return rc;
+  VC_HIP(ctx, hipStreamSynchronize(ctx->stream));  // launches of the families that did fit
+  WorkspaceScope scope(ctx, wsa.base, wsa.bytes, wsa.host_heap, true);
+  return run_batch(ctx, b, pvc, o, out, t0, abort_base);
+}
 
 // One graph: a batch of one.
 int solve(vc_ctx* ctx, const vc_graph* g, bool device_graph, bool pvc, int32_t k,
@@ -1315,10 +1341,7 @@ int solve(vc_ctx* ctx, const vc_graph* g, bool device_graph, bool pvc, int32_t k
   out.cover_dev = cover_dev;
   out.stats = stats;
   out.single = true;
-  {
-    WorkspaceScope scope(ctx, wsa.base, wsa.bytes, wsa.host_heap);
-    if ((rc = run_batch(ctx, b, pvc, o, out, t0, abort_base))) return rc;
-  }
+  if ((rc = run_in_workspace(ctx, b, pvc, o, out, t0, abort_base, wsa))) return rc;
   *size_out = size;
   if (yes_out) *yes_out = yes;
   return VC_OK;
@@ -1359,8 +1382,7 @@ int solve_batch(vc_ctx* ctx, const vc_batch* batch, bool device_graph, bool pvc,
   out.cover_host = cover_host;
   out.cover_dev = cover_dev;
   out.stats = stats;
-  WorkspaceScope scope(ctx, wsa.base, wsa.bytes, wsa.host_heap);
-  return run_batch(ctx, b, pvc, o, out, t0, abort_base);
+  return run_in_workspace(ctx, b, pvc, o, out, t0, abort_base, wsa);
 }
 
 // Device bytes a caller-workspace call on these graphs needs (an upper bound): the buffers

@@ -43,11 +43,14 @@ struct Request {
 
 // Bytes of node stacks a request adds to a batch: its workgroups (at most one per CU's worth,
 // 256, since a batch's grid is capped by its share of the device) times the depth bound times
-// the stored node size of its kernel family.
+// the stored node size of its kernel family, for each wavefront of a bitset team (a PVC request
+// above kAutoBitsetN, whose team's nodes take less, counts as a degree array).
 int64_t footprint(int32_t n, int32_t problem, int32_t k, int32_t wg_per_request) {
   const int64_t depth = problem == VC_PROBLEM_PVC ? std::min<int64_t>(k, n) + 1 : n;
-  const int64_t node = n <= vc::kAutoBitsetN ? vc::bitset_stride((std::max(n, 1) + 63) / 64) * 4
-                                            : static_cast<int64_t>(vc::array_stride(n)) * 4;
+  const int words = (std::max(n, 1) + 63) / 64;
+  const int64_t node = n <= vc::kAutoBitsetN
+                           ? vc::bitset_stride(words) * 4 * std::min(8, vc::bitset_max_team(words))
+                           : static_cast<int64_t>(vc::array_stride(n)) * 4;
   return std::min<int64_t>(wg_per_request, 256) * depth * node;
 }
 

@@ -141,6 +141,45 @@ def test_workspace_too_small_and_smaller_grid(solver, oracle_lib, torch_cuda):
     assert small.stats["num_wg"] < full.stats["num_wg"]
 
 
+@pytest.mark.parametrize("problem", ["mvc", "pvc"])
+@pytest.mark.parametrize("n", [120, 200, 265, 400, 512])
+def test_least_workspace_of_one_wavefront_or_degree_arrays_is_enough(solver, oracle_lib,
+                                                                     torch_cuda, problem, n):
+    """The smallest workspace that workgroups of one wavefront (bitsets) or degree arrays accept
+    also serves the call without options: teams and, for PVC graphs above 256 vertices, bitsets are
+    left where they do not fit. For PVC, a batch of eight such graphs as well."""
+    import paper_2204_10402_amd as vc
+    plain = vc.Options(flags=vc.OPT_DEGREE_ARRAYS) if n > 256 else vc.Options(wg_size=64)
+    gs = [G.erdos_renyi(n - 8 * (i % 2), 2.5 / n, i) for i in range(8)]
+    taus = [oracle.mvc(g).size for g in gs]
+    rp, ci, cover = dev(torch_cuda, gs[0])
+    nb, nnz, rpb, cib = vc.pack_batch(gs)
+    rpb, cib = torch_cuda.from_numpy(rpb).to("cuda:0"), torch_cuda.from_numpy(cib).to("cuda:0")
+
+    def one(ws, o):
+        if problem == "mvc":
+            return solver.mvc_device_ws(rp, ci, ws, cover, o).size == taus[0]
+        return not solver.pvc_device_ws(rp, ci, taus[0] - 1, ws, cover, o).yes
+
+    def batch(ws, o):
+        res = solver.pvc_batch_device_ws(nb, nnz, rpb, cib, [t - 1 for t in taus], ws, None, o)
+        return not any(res.yes) and not any(res.status)
+
+    for call in [one] + ([batch] if problem == "pvc" else []):
+        lo, hi = 0, 1 << 18  # units of 256 bytes: 0 is refused, 64 MiB is enough
+        full = workspace(torch_cuda, hi * 256)
+        assert call(full, plain)
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            try:
+                assert call(full[:mid * 256], plain)
+                hi = mid
+            except vc.VCError as e:
+                assert e.code == vc.ERR_NO_MEMORY
+                lo = mid
+        assert call(full[:hi * 256], None), hi
+
+
 def hard_batch(torch, count):
     """`count` G(150, 0.08) graphs: MVC searches of millions of nodes each."""
     import paper_2204_10402_amd as vc
