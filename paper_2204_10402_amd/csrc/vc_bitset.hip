@@ -9,7 +9,8 @@
 // self-contained, given the read-only adjacency, and W*8 + 8 bytes instead of 4(n+2). A degree
 // is recomputed as popcount(adj[v] & L).
 //
-// One wavefront per node. Lane l holds vertices l, 64+l, ..., (W-1)*64+l and their W
+// One wavefront per node, several to a workgroup (a team, which shares the adjacency matrix and
+// hands sub-trees over inside the workgroup; see Team). Lane l holds vertices l, 64+l, ..., (W-1)*64+l and their W
 // adjacency words each in vector registers; the whole adjacency matrix also sits in LDS for
 // random access (the triangle test). A rule pass is a handful of ballots and bit operations;
 // the main loop has no barriers except inside the worklist protocol.
@@ -788,7 +789,8 @@ constexpr uint32_t kPollNodes = 16;
 // time of a few nodes. Up to kDonateMost entries go out at once, so that a tree whose side
 // branches are small still spreads. Measured (one 5-regular graph of 120 vertices / a G(200, 0.5)
 // search of 85,000 nodes), entries x interval: 1 x 8: 5.4 / 5.1 ms, 2 x 8: 4.4 / 3.7,
-// 4 x 8: 3.9 / 2.4, 4 x 2: 4.1 / 3.9, 4 x 32: 4.2 / 4.0.
+// 4 x 8: 3.9 / 2.4, 4 x 2: 4.1 / 3.9, 4 x 32: 4.2 / 4.0 (with the node in scalar registers 4 x 8
+// takes 3.4 / 1.7).
 constexpr uint32_t kDonateNodes = 8;
 
 // The hybrid traversal (§IV-A, Fig. 4; termination §IV-C) on bitset nodes, over every instance
