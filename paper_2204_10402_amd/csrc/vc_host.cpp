@@ -53,7 +53,8 @@ struct vc_ctx {
   // A second context (own stream, worklist, counters, stacks) on which a batch's degree-array
   // launch runs while its bitset launches run on this one; created on first use.
   vc_ctx* aux = nullptr;
-  bool aux_busy = false;  // work was queued on it that no call has waited for (an error return)
+  // the running call has queued work on `stream` (or aux's) that the host has not waited for
+  bool queued = false;
   vc_ctx* stats_src = nullptr;  // the context holding the last traversal's per-workgroup stats
   // vc_abort: a host-pinned word, mapped for the device; vc_abort increments it and a launch
   // stops when it differs from its value at the start of the call
@@ -227,6 +228,27 @@ int ensure_events(vc_ctx* ctx, size_t count) {
   }
   return VC_OK;
 }
+
+// Before a call that has queued work may return early (or try again in another way): stop its
+// launches, as vc_abort does, and wait for everything on its streams. What it queued reads and
+// writes the pinned staging, the context's buffers, and the caller's graph, covers and workspace:
+// all of it is the next call's, or the caller's, once this one has returned. Returns how far the
+// stop word was moved on.
+int32_t settle(vc_ctx* ctx) {
+  if (!ctx->queued) return 0;
+  if (ctx->abort_host) __atomic_fetch_add(ctx->abort_host, 1, __ATOMIC_RELEASE);
+  if (ctx->aux) (void)hipStreamSynchronize(ctx->aux->stream);
+  (void)hipStreamSynchronize(ctx->stream);
+  ctx->queued = false;
+  return ctx->abort_host ? 1 : 0;
+}
+
+// Settles what is still queued when a call returns: after an error (a call that succeeds has
+// waited for its work itself).
+struct SettleOnReturn {
+  vc_ctx* ctx;
+  ~SettleOnReturn() { settle(ctx); }
+};
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
@@ -766,20 +788,16 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
   if (m > 0) {
     if ((rc = ensure(ctx, ctx->ctr, vc::kNumCounters * vc::kCounterStride * sizeof(int32_t)))) return rc;
     if ((rc = ensure_events(ctx, 4 * static_cast<size_t>(ng) + 4))) return rc;
-    if (ctx->aux && ctx->aux_busy) {
-      // whatever an earlier call left on the auxiliary stream (an error return does not wait
-      // for it) finishes before this call's table overwrites the meta buffer
-      VC_HIP(ctx, hipEventRecord(ctx->ev[2 * ng + 3], ctx->aux->stream));
-      VC_HIP(ctx, hipStreamWaitEvent(st, ctx->ev[2 * ng + 3], 0));
-    }
     if (use_aux &&
         (rc = ensure(ctx, ctx->aux->ctr, vc::kNumCounters * vc::kCounterStride * sizeof(int32_t))))
       return rc;
     // one copy in: instance table, fresh per-instance state and work counters (a small single
     // graph's are written by its validation kernel)
-    if (!small) VC_HIP(ctx, hipMemcpyAsync(dev, host, L.res, hipMemcpyHostToDevice, st));
+    if (!small) {
+      ctx->queued = true;
+      VC_HIP(ctx, hipMemcpyAsync(dev, host, L.res, hipMemcpyHostToDevice, st));
+    }
     if (use_aux) {
-      ctx->aux_busy = true;
       VC_HIP(ctx, hipEventRecord(ctx->ev[2 * ng + 2], st));
       VC_HIP(ctx, hipStreamWaitEvent(ctx->aux->stream, ctx->ev[2 * ng + 2], 0));
     }
@@ -905,6 +923,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       p.timeout_ticks = std::max<uint64_t>(1, static_cast<uint64_t>(left_ms * ctx->clock_khz));
     }
 
+    ctx->queued = true;
     if (small) VC_HIP(ctx, vc::launch_prepare_small(p, dres, h_inst[0], gst));
     else VC_HIP(ctx, vc::launch_prepare(p, dres, g.vertices, g.entries, gst));
     if (!pvc) {
@@ -1071,7 +1090,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
   if (out.cover_host && total_n > 0)
     VC_HIP(ctx, hipMemcpyAsync(h_cover, covers, static_cast<size_t>(total_n), hipMemcpyDeviceToHost, st));
   VC_HIP(ctx, hipStreamSynchronize(st));
-  if (use_aux) ctx->aux_busy = false;
+  ctx->queued = false;
   // The greedy's time, and the traversal's: from its first workgroup's start to the cover check,
   // added up over the launches, or with the auxiliary context the span from the first launch's
   // start until the last one's end.
@@ -1212,6 +1231,7 @@ int upload(vc_ctx* ctx, const int32_t* rp, int64_t rp_count, const int32_t* ci, 
   int rc;
   if ((rc = ensure(ctx, ctx->rp, static_cast<size_t>(std::max<int64_t>(rp_count, 1)) * sizeof(int32_t)))) return rc;
   if ((rc = ensure(ctx, ctx->ci, static_cast<size_t>(std::max<int64_t>(ci_count, 1)) * sizeof(int32_t)))) return rc;
+  ctx->queued = true;
   if (rp_count > 0)
     VC_HIP(ctx, hipMemcpyAsync(ctx->rp.ptr, rp, static_cast<size_t>(rp_count) * sizeof(int32_t),
                                hipMemcpyHostToDevice, ctx->stream));
@@ -1297,7 +1317,8 @@ int run_in_workspace(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* 
     rc = run_batch(ctx, b, pvc, o, out, t0, abort_base);
   }
   if (rc != VC_ERR_NO_MEMORY || !wsa.base) return rc;
-  VC_HIP(ctx, hipStreamSynchronize(ctx->stream));  // launches of the families that did fit
+  // the launches of the families that did fit; their stop is not the second try's
+  abort_base += settle(ctx);
   WorkspaceScope scope(ctx, wsa.base, wsa.bytes, wsa.host_heap, true);
   return run_batch(ctx, b, pvc, o, out, t0, abort_base);
 }
@@ -1320,6 +1341,7 @@ int solve(vc_ctx* ctx, const vc_graph* g, bool device_graph, bool pvc, int32_t k
     if (stats) std::memset(stats, 0, sizeof *stats), stats->total_ms = ms_since(t0);
     return VC_OK;
   }
+  SettleOnReturn settle_on_return{ctx};
   BatchIn b;
   b.count = 1;
   b.n = &g->n;
@@ -1359,6 +1381,7 @@ int solve_batch(vc_ctx* ctx, const vc_batch* batch, bool device_graph, bool pvc,
   if (!status_out || !size_out || (pvc && !yes_out))
     return fail(ctx, VC_ERR_INVALID_ARG, "output pointer is NULL");
   if ((rc = check_options(ctx, o))) return rc;
+  SettleOnReturn settle_on_return{ctx};
   BatchIn b;
   b.count = batch->count;
   b.n = batch->n;
@@ -1488,6 +1511,7 @@ int setup_single(vc_ctx* ctx, const vc_graph* g, int rules, int32_t flags, uint8
   in.n = g->n;
   in.nnz = g->nnz;
   init_state(reinterpret_cast<InstState*>(host + L.ist), reinterpret_cast<int32_t*>(host + L.work), 1);
+  ctx->queued = true;
   VC_HIP(ctx, hipMemcpyAsync(dev, host, L.res, hipMemcpyHostToDevice, ctx->stream));
   p = Params{};
   p.num_inst = 1;
@@ -1779,6 +1803,7 @@ int vc_greedy_device(vc_ctx* ctx, const vc_graph* g, int32_t* size_out, uint8_t*
     *size_out = 0;
     return VC_OK;
   }
+  SettleOnReturn settle_on_return{ctx};
   Params p{};
   int32_t ws = 0;
   if ((rc = setup_single(ctx, g, vc::kRulesAll, 0, nullptr, p, &ws))) return rc;
@@ -1789,6 +1814,7 @@ int vc_greedy_device(vc_ctx* ctx, const vc_graph* g, int32_t* size_out, uint8_t*
       reinterpret_cast<InstState*>(static_cast<char*>(ctx->pinned) + meta_layout(1, 1, 0).ist);
   VC_HIP(ctx, hipMemcpyAsync(h_is, p.ist, sizeof(InstState), hipMemcpyDeviceToHost, s));
   VC_HIP(ctx, hipStreamSynchronize(s));
+  ctx->queued = false;
   const InstState is = *h_is;
   if (is.err_row != vc::kNoRow) return fail(ctx, VC_ERR_INVALID_GRAPH, bad_row_message(is.err_row));
   if (cover_dev) {
@@ -1810,6 +1836,7 @@ int vc_reduce_device(vc_ctx* ctx, const vc_graph* g, int32_t* deg_dev, int32_t* 
   o.flags = flags;
   if ((rc = check_options(ctx, &o))) return rc;
   if (g->n == 0) return VC_OK;
+  SettleOnReturn settle_on_return{ctx};
   Params p{};
   int32_t ws = 0;
   if ((rc = setup_single(ctx, g, rules_from_flags(flags), flags, nullptr, p, &ws))) return rc;
@@ -1825,6 +1852,7 @@ int vc_reduce_device(vc_ctx* ctx, const vc_graph* g, int32_t* deg_dev, int32_t* 
   VC_HIP(ctx, hipMemcpyAsync(h_is, p.ist, sizeof(InstState), hipMemcpyDeviceToHost, s));
   VC_HIP(ctx, hipMemcpyAsync(&s_new, sdev, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   VC_HIP(ctx, hipStreamSynchronize(s));
+  ctx->queued = false;
   const InstState is = *h_is;
   if (is.err_row != vc::kNoRow) return fail(ctx, VC_ERR_INVALID_GRAPH, bad_row_message(is.err_row));
   *s_inout = s_new;

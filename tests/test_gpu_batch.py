@@ -7,6 +7,8 @@ depend on the schedule (one workgroup that never donates; PVC graphs whose answe
 launch configuration). A graph's answer must not depend on the graphs it is batched with.
 """
 
+import time
+
 import numpy as np
 import pytest
 
@@ -317,3 +319,39 @@ def test_results_of_batches_around_the_direct_limit(solver, oracle_lib, count):
         assert no.yes.tolist() == [x.yes for x in o]
         assert [int(no.nodes[i]) for i in range(count) if not o[i].yes] == \
             [x.nodes for x in o if not x.yes]
+
+
+@pytest.mark.parametrize("way", ["option", "workspace"])
+def test_failed_batch_leaves_nothing_running(oracle_lib, torch_cuda, way):
+    """A batch that fails after some of its launches are queued (the graph above 256 vertices runs
+    first, then the bitset group refuses a workgroup size; or a workspace that only holds the first
+    kernel family) has stopped them when it returns: at once, although one of the searches would
+    take far longer, and the next batch, staged in the same host memory, gets its own answers."""
+    import paper_2204_10402_amd as vc
+    hard = G.erdos_renyi(300, 0.06, 1)
+    small = [G.erdos_renyi(60, 0.1, i) for i in range(3)]
+    other = [G.erdos_renyi(30 + 7 * i, 0.12, 70 + i) for i in range(7)]
+    with vc.Solver(0) as s:
+        for _ in range(3):
+            t = time.perf_counter()
+            with pytest.raises(vc.VCError) as e:
+                if way == "option":
+                    s.mvc_batch(small + [hard], vc.Options(wg_size=128, timeout_ms=30000))
+                else:
+                    large = G.planted_cover(20000, 800, 60000, 0.75, 1)
+                    n, nnz, rp, ci = vc.pack_batch(small + [large])
+                    s.mvc_batch_device_ws(
+                        n, nnz, torch_cuda.from_numpy(rp).to("cuda:0"),
+                        torch_cuda.from_numpy(ci).to("cuda:0"),
+                        torch_cuda.empty(4 << 20, dtype=torch_cuda.uint8, device="cuda:0"))
+            assert e.value.code == (vc.ERR_INVALID_ARG if way == "option" else vc.ERR_NO_MEMORY)
+            assert time.perf_counter() - t < 5.0
+            res = s.mvc_batch(other)
+            for i, g in enumerate(other):
+                want = oracle.mvc(g)
+                assert (res.status[i], res.size[i]) == (0, want.size), i
+                check_cover(g, res.cover_of(i), want.size)
+            res = s.pvc_batch(other, [oracle.mvc(g).size - 1 for g in other])
+            for i, g in enumerate(other):
+                o = oracle.pvc(g, oracle.mvc(g).size - 1)
+                assert (res.status[i], bool(res.yes[i]), res.nodes[i]) == (0, False, o.nodes), i
