@@ -350,6 +350,30 @@ int choose_words(vc_ctx* ctx, int32_t n, bool pvc, const vc_options* o, int32_t*
   return VC_OK;
 }
 
+// The same for every graph of a batch (0 for graphs without vertices). Graphs above kAutoBitsetN
+// that take the bitset kernels share one launch, as wide as the widest of them needs: a launch lasts
+// as long as its slowest search, and one launch for each of five to eight words runs these searches
+// in turn, which costs a batch more than the words a smaller graph does without (PVC no, graphs of
+// 257-512 vertices, average degree 2.6, 8 / 128 / 2,000 a call: 469 / 953 / 1,740 us with a launch
+// for each width, 290 / 390 / 1,480 with one; degree arrays, one launch for all: 420 / 670 / 2,370).
+// The plan that needs least memory keeps a launch for each width (no padded adjacency rows).
+int choose_batch_words(vc_ctx* ctx, int32_t count, const int32_t* n, bool pvc, const vc_options* o,
+                       std::vector<int32_t>* words) {
+  words->assign(static_cast<size_t>(count), 0);
+  constexpr int32_t kNarrow = vc::kAutoBitsetN / 64;
+  int32_t widest = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    if (n[i] == 0) continue;
+    int rc = choose_words(ctx, n[i], pvc, o, &(*words)[i]);
+    if (rc) return rc;
+    widest = std::max(widest, (*words)[i]);
+  }
+  if (widest > kNarrow && !(ctx->ws && ctx->ws->narrow))
+    for (int32_t& w : *words)
+      if (w > kNarrow) w = widest;
+  return VC_OK;
+}
+
 void size_worklist(Plan& pl, const vc_options* o, uint64_t min_cap);
 
 // What a launch plan depends on.
@@ -682,7 +706,8 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
   const bool stack_only = flags & VC_OPT_STACK_ONLY;
 
   // instance table, sorted by kernel family; graphs without vertices are answered here
-  std::vector<int32_t> words(b.count, 0), order;
+  std::vector<int32_t> words, order;
+  if ((rc = choose_batch_words(ctx, b.count, b.n, pvc, o, &words))) return rc;
   order.reserve(b.count);
   for (int32_t i = 0; i < b.count; ++i) {
     if (b.n[i] == 0) {
@@ -691,7 +716,6 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       }
       continue;
     }
-    if ((rc = choose_words(ctx, b.n[i], pvc, o, &words[i]))) return rc;
     order.push_back(i);
   }
   // by bitset words, degree arrays last, in the caller's order within a family (counting sort)
@@ -1420,17 +1444,18 @@ int workspace_need(vc_ctx* ctx, int32_t count, const int32_t* n, const int32_t* 
     int64_t vertices = 0;
   };
   size_t most = 0;
+  for (int32_t i = 0; i < count; ++i)
+    if (n[i] < 0 || nnz[i] < 0) return fail(ctx, VC_ERR_INVALID_ARG, "negative n or nnz");
   for (bool pvc : {false, true}) {
     std::map<int32_t, Fam> fams;  // by bitset words (0: degree arrays)
     int64_t total_n = 0;
     int32_t m = 0;
+    std::vector<int32_t> words;
+    int rc = choose_batch_words(ctx, count, n, pvc, o, &words);
+    if (rc) return rc;
     for (int32_t i = 0; i < count; ++i) {
-      if (n[i] < 0 || nnz[i] < 0) return fail(ctx, VC_ERR_INVALID_ARG, "negative n or nnz");
       if (n[i] == 0) continue;
-      int32_t words = 0;
-      int rc = choose_words(ctx, n[i], pvc, o, &words);
-      if (rc) return rc;
-      Fam& f = fams[words];
+      Fam& f = fams[words[i]];
       f.n_max = std::max(f.n_max, n[i]);
       f.nnz_max = std::max(f.nnz_max, nnz[i]);
       f.count += 1;
@@ -1453,8 +1478,7 @@ int workspace_need(vc_ctx* ctx, int32_t count, const int32_t* n, const int32_t* 
       sh.words = words;
       sh.count = f.count;
       sh.depth = static_cast<int32_t>(d);
-      int rc = plan_launch(ctx, pvc, sh, o, pl);
-      if (rc) return rc;
+      if ((rc = plan_launch(ctx, pvc, sh, o, pl))) return rc;
       const size_t stride_b = static_cast<size_t>(pl.stride) * sizeof(int32_t);
       size_t need = al(pl.cap * stride_b) + al(pl.cap * sizeof(uint32_t)) +
                     al(static_cast<size_t>(pl.num_wg) * sizeof(vc::WgStats)) +

@@ -355,3 +355,32 @@ def test_failed_batch_leaves_nothing_running(oracle_lib, torch_cuda, way):
             for i, g in enumerate(other):
                 o = oracle.pvc(g, oracle.mvc(g).size - 1)
                 assert (res.status[i], bool(res.yes[i]), res.nodes[i]) == (0, False, o.nodes), i
+
+
+@pytest.mark.parametrize("sizes", [(257, 320, 321, 384), (257, 384, 385, 448, 300), (300, 449, 512, 257, 385)])
+def test_wide_bitset_graphs_share_a_launch(solver, oracle_lib, torch_cuda, sizes):
+    """The graphs of 257 to 512 vertices of a PVC batch run in one bitset launch, as wide as the
+    widest of them needs (a launch for each word count would run their searches in turn), beside
+    the launches of the smaller ones. Node counts of no-answers are the oracle's, in a workspace
+    of the stated size as well. Whole numbers: no tolerance."""
+    import paper_2204_10402_amd as vc
+    gs = [G.erdos_renyi(n, 2.6 / n, 60 + i) for i, n in enumerate(sizes)]
+    for extra, launches in ([], 1), ([G.erdos_renyi(50, 0.08, 1), G.erdos_renyi(200, 0.015, 2)], 3):
+        batch = gs + extra
+        taus = [oracle.mvc(g, node_cap=200000).size for g in batch]
+        no = solver.pvc_batch(batch, [t - 1 for t in taus])
+        assert no.stats["launches"] == launches
+        assert no.stats["bitset_words"] == (max(sizes) + 63) // 64
+        want = [oracle.pvc(g, t - 1, node_cap=200000).nodes for g, t in zip(batch, taus)]
+        assert not no.yes.any() and no.nodes.tolist() == want
+        yes = solver.pvc_batch(batch, taus)
+        for i, g in enumerate(batch):
+            assert yes.yes[i] and yes.size[i] <= taus[i], i
+            check_cover(g, yes.cover_of(i), int(yes.size[i]))
+        n, nnz, rp, ci = vc.pack_batch(batch)
+        ws = torch_cuda.empty(solver.batch_workspace_bytes(n, nnz), dtype=torch_cuda.uint8, device="cuda:0")
+        r = solver.pvc_batch_device_ws(n, nnz, torch_cuda.from_numpy(rp).to("cuda:0"),
+                                       torch_cuda.from_numpy(ci).to("cuda:0"), [t - 1 for t in taus], ws)
+        assert r.stats["launches"] == launches and r.nodes.tolist() == want
+        mv = solver.mvc_batch(gs, vc.Options(flags=vc.OPT_BITSETS))
+        assert mv.stats["launches"] == 1 and mv.size.tolist() == taus[:len(gs)]
