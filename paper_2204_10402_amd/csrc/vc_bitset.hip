@@ -790,8 +790,13 @@ constexpr uint32_t kPollNodes = 16;
 // branches are small still spreads. Measured (one 5-regular graph of 120 vertices / a G(200, 0.5)
 // search of 85,000 nodes), entries x interval: 1 x 8: 5.4 / 5.1 ms, 2 x 8: 4.4 / 3.7,
 // 4 x 8: 3.9 / 2.4, 4 x 2: 4.1 / 3.9, 4 x 32: 4.2 / 4.0 (with the node in scalar registers 4 x 8
-// takes 3.4 / 1.7).
-constexpr uint32_t kDonateNodes = 8;
+// takes 3.4 / 1.7). A node of five words or more takes several times as long, so that a donation
+// costs less of one and a small tree waits longer for its nodes to spread: every 4 nodes there (PVC
+// no, one G(500, 3.1/500) / one G(400, 3.1/400) / eight graphs of 257-512 vertices, average degree
+// 2.6: 8 nodes 532 / 280 / 295 us, 4 nodes 384 / 228 / 228, 2 nodes 333 / 199 / 208; but 16 graphs
+// G(390, 3.5/390), 750,000 nodes: 1.71, 1.73 and 1.80 ms).
+template <int W>
+constexpr uint32_t kDonateNodes = W >= 5 ? 4 : 8;
 
 // The hybrid traversal (§IV-A, Fig. 4; termination §IV-C) on bitset nodes, over every instance
 // of the launch (as traverse_kernel). Each wavefront of a workgroup walks its own sub-trees with
@@ -1198,7 +1203,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       given = team_give<W>(team, idle, top - bot, lstack, stack_lds ? nullptr : gstack(), stack_lds,
                            bot_slot, cap);
     } else if (seen_count < threshold &&
-               (waves == 1 || (top - bot > 1 && quiet >= kDonateNodes))) {
+               (waves == 1 || (top - bot > 1 && quiet >= kDonateNodes<W>))) {
       const int m = min(kDonateMost, (top - bot + 1) / 2);
       if (!stack_lds) __threadfence_block();
       const Params& p = cold_params();
