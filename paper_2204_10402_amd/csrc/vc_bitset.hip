@@ -782,6 +782,11 @@ __device__ __forceinline__ int bits_report_nodes(const Params& p, int j, uint32_
   return 0;
 }
 
+// Without a node budget a wavefront reports its nodes to the instance every kFlushNodes of them, so
+// that what all wavefronts of a team have not reported (at most this many each) fits in Team::nodes.
+constexpr uint32_t kFlushNodes = 1u << 27;
+static_assert(uint64_t{kMaxWaves} * kFlushNodes <= 0xFFFFFFFFu, "a team's unreported nodes wrap");
+
 // Nodes between two reads of the node header (a power of two).
 constexpr uint32_t kPollNodes = 16;
 // In a team of more than one, nodes a wavefront visits between two donations to the worklist:
@@ -860,9 +865,9 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
   int cur = -1, cur_n = 0;
   int32_t cur_k = 0, cur_vtx = 0;
   // Statistics: nodes and stack traffic are counted in 32 bits since the last flush (instance
-  // switch, budget report, or every 2^30 nodes) and folded into `tally` there.
+  // switch, budget report, or every kFlushNodes nodes) and folded into `tally` there.
   uint32_t unreported = 0, pushes32 = 0, pops32 = 0;  // since the last flush
-  const uint32_t flush_at = args.node_budget > 0 ? static_cast<uint32_t>(args.budget_chunk) : (1u << 30);
+  const uint32_t flush_at = args.node_budget > 0 ? static_cast<uint32_t>(args.budget_chunk) : kFlushNodes;
   int max_depth = 0;
   uint32_t headers = 0;  // nodes since the last header, and so on (see kPollNodes)
   uint32_t so_path = 0;  // StackOnly: the current path index
@@ -1124,9 +1129,7 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       int spent = 0;
       if (lane == 0) {
         const Params& p = cold_params();
-        if (p.node_budget > 0) spent = bits_report_nodes(p, cur, unreported);
-        else __hip_atomic_fetch_add(&team.nodes, unreported, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+        spent = bits_report_nodes(p, cur, unreported);
         add_tally(&tally.nodes, unreported);
         add_tally(&tally.pushes, pushes32);
         add_tally(&tally.pops, pops32);

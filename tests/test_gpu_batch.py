@@ -384,3 +384,17 @@ def test_wide_bitset_graphs_share_a_launch(solver, oracle_lib, torch_cuda, sizes
         assert r.stats["launches"] == launches and r.nodes.tolist() == want
         mv = solver.mvc_batch(gs, vc.Options(flags=vc.OPT_BITSETS))
         assert mv.stats["launches"] == 1 and mv.size.tolist() == taus[:len(gs)]
+
+
+@pytest.mark.parametrize("budget", [0, 10 ** 5, 10 ** 12])
+def test_node_counts_reported_on_the_way(solver, oracle_lib, budget):
+    """A graph's node count is the oracle's whether its wavefronts report it when they leave the
+    graph (no budget) or every few nodes (a budget that the tree does not use up)."""
+    import paper_2204_10402_amd as vc
+    g = G.erdos_renyi(90, 0.07, 5)
+    k = oracle.mvc(g).size - 1
+    want = oracle.pvc(g, k).nodes
+    assert 200 < want < 10 ** 5
+    for flags in (vc.OPT_BITSETS, vc.OPT_DEGREE_ARRAYS):
+        r = solver.pvc(g, k, vc.Options(node_budget=budget, flags=flags))
+        assert not r.yes and r.stats["nodes"] == want
