@@ -46,8 +46,9 @@ struct vc_ctx {
   std::string last_error;
   // occupancy-API answers: (kernel family, pvc, profiled, workgroup size, words, LDS bytes)
   std::map<std::tuple<int, int, int, int, int, size_t>, int> occupancy;
-  // bitset traversal kernels (words, pvc, profiled) allowed more than the default dynamic LDS
-  std::set<std::tuple<int, bool, bool>> bitset_lds_set;
+  // bitset traversal kernels (words, pvc, profiled, StackOnly) allowed more than the default
+  // dynamic LDS
+  std::set<std::tuple<int, bool, bool, bool>> bitset_lds_set;
   // autotuner choices: (bitset words, pvc, flags, log2 n_max, log2 instances) -> knobs
   std::map<std::tuple<int, int, int, int, int>, std::tuple<int, int, int>> tuned;
   // A second context (own stream, worklist, counters, stacks) on which a batch's degree-array
@@ -414,10 +415,11 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
     // donations (each workgroup then walks its whole sub-tree in depth-first order), or for
     // StackOnly; and where a caller's workspace is too small for teams.
     const size_t lds_most = static_cast<size_t>(ctx->prop.maxSharedMemoryPerMultiProcessor) / 2 - 2048;
-    if (!ctx->bitset_lds_set.count(std::make_tuple(words, pvc, prof))) {
-      const bool so = o && (o->flags & VC_OPT_STACK_ONLY);
+    const bool so = o && (o->flags & VC_OPT_STACK_ONLY);
+    const auto kernel = std::make_tuple(words, pvc, prof, so);
+    if (!ctx->bitset_lds_set.count(kernel)) {
       VC_HIP(ctx, vc::bitset_lds_limit(words, pvc, prof, so, lds_most));
-      if (!so) ctx->bitset_lds_set.insert(std::make_tuple(words, pvc, prof));
+      ctx->bitset_lds_set.insert(kernel);
     }
     const bool alone = (ctx->ws && ctx->ws->narrow) ||
                        (o && (o->wg_size == 64 || o->wl_threshold == -1 ||

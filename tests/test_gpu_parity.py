@@ -738,3 +738,17 @@ def test_graph_beyond_lds(solver, oracle_lib):
     with pytest.raises(vc.VCError) as ei:
         solver.mvc(g, vc.Options(flags=vc.OPT_GLOBAL_NODES | vc.OPT_BITSETS))
     assert ei.value.code == vc.ERR_INVALID_ARG
+
+
+def test_stack_only_after_a_hybrid_call_on_the_widest_bitsets(oracle_lib):
+    """MVC of 512 vertices as bitsets: the matrix and one stack ring take 74 KB of LDS, more than a
+    kernel may use by default, in the hybrid kernel and in the StackOnly one after it."""
+    import paper_2204_10402_amd as vc
+    g = G.erdos_renyi(512, 2.2 / 512, 7)
+    want = oracle.mvc(g)
+    with vc.Solver(0) as s:
+        for flags, depth in ((vc.OPT_BITSETS, 0), (vc.OPT_BITSETS | vc.OPT_STACK_ONLY, 4),
+                             (vc.OPT_BITSETS | vc.OPT_STACK_ONLY | vc.OPT_PROFILE, 4)):
+            r = s.mvc(g, vc.Options(flags=flags, start_depth=depth))
+            assert r.size == want.size and oracle.is_cover(g, r.cover)
+            assert r.stats["stack_lds"] == 1 and r.stats["bitset_words"] == 8
