@@ -1647,8 +1647,9 @@ hipError_t traverse_occupancy(bool pvc, bool prof, bool global_node, int32_t rp_
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, wg_size, lds_bytes);
 }
 
+// Every degree-array kernel: with the node in device memory too, the lists alone take up to 96 KB.
 hipError_t set_lds_limit(size_t lds_bytes) {
-  for (int mem = kMemLds; mem <= kMemLdsCsr; ++mem) {
+  for (int mem = kMemGlobal; mem <= kMemLdsCsr; ++mem) {
     const void* fns[] = {traverse_fn(true, false, mem), traverse_fn(false, false, mem),
                          traverse_fn(true, true, mem), traverse_fn(false, true, mem),
                          traverse_fn(true, false, mem, true), traverse_fn(false, false, mem, true),
@@ -1660,9 +1661,11 @@ hipError_t set_lds_limit(size_t lds_bytes) {
     }
   }
   const void* others[] = {
+      reinterpret_cast<const void*>(&greedy_kernel<kMemGlobal>),
       reinterpret_cast<const void*>(&greedy_kernel<kMemLds>),
       reinterpret_cast<const void*>(&greedy_kernel<kMemLdsRp>),
       reinterpret_cast<const void*>(&greedy_kernel<kMemLdsCsr>),
+      reinterpret_cast<const void*>(&reduce_kernel<kMemGlobal>),
       reinterpret_cast<const void*>(&reduce_kernel<kMemLds>),
       reinterpret_cast<const void*>(&reduce_kernel<kMemLdsRp>),
       reinterpret_cast<const void*>(&reduce_kernel<kMemLdsCsr>)};

@@ -752,3 +752,26 @@ def test_stack_only_after_a_hybrid_call_on_the_widest_bitsets(oracle_lib):
             r = s.mvc(g, vc.Options(flags=flags, start_depth=depth))
             assert r.size == want.size and oracle.is_cover(g, r.cover)
             assert r.stats["stack_lds"] == 1 and r.stats["bitset_words"] == 8
+
+
+def test_device_memory_node_with_the_longest_lists(oracle_lib):
+    """A node in device memory of more than 4,096 vertices: 1,024-thread workgroups whose candidate
+    lists take 96 KB of LDS, in the greedy, the traversal and the reduction, on a fresh context."""
+    import numpy as np
+    import torch
+    import paper_2204_10402_amd as vc
+    g = G.planted_cover(9000, 300, 27000, 0.75, 3)
+    with vc.Solver(0) as s:
+        o = vc.Options(flags=vc.OPT_GLOBAL_NODES, wg_size=1024)
+        for k in (300, 299):
+            want = oracle.pvc(g, k, node_cap=200000)
+            r = s.pvc(g, k, o)
+            assert r.yes == want.yes and (want.yes or r.stats["nodes"] == want.nodes)
+        r = s.mvc(g, o)
+        assert r.size == 300 and oracle.is_cover(g, r.cover)
+        rp, ci = torch.from_numpy(g.row_ptr).to("cuda:0"), torch.from_numpy(g.col_idx).to("cuda:0")
+        states = []
+        for flags in (vc.OPT_GLOBAL_NODES, 0):
+            deg = torch.from_numpy(np.diff(g.row_ptr).astype(np.int32)).to("cuda:0")
+            states.append((s.reduce_device(rp, ci, deg, 0, 300, flags), deg.cpu().tolist()))
+        assert states[0] == states[1]
