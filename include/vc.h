@@ -109,7 +109,9 @@ typedef struct {
                            (the occupancy rule of §IV-E). Bitset kernels: 0 (teams of up to 16
                            wavefronts, one node each) or 64 (one wavefront) */
   int32_t num_wg;       /* workgroups in the persistent grid; 0 = as many as are co-resident;
-                           larger values are clamped to the co-resident maximum */
+                           larger values are clamped to the co-resident maximum. 1: nodes are
+                           visited one after another, the same ones on every run (bitset kernels:
+                           one wavefront) */
   int32_t wl_capacity;  /* global worklist entries (rounded up to a power of two); 0 = auto */
   int32_t wl_threshold; /* a branch is donated to the worklist only while it holds fewer than
                            this many entries (§IV-A); 0 = auto; -1 = never donate (every

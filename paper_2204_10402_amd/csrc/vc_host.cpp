@@ -411,9 +411,10 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
     // registers) as long as their stack rings fit in LDS beside the adjacency matrix with room for
     // a second workgroup on the CU, and there is a workgroup for every instance: an instance
     // occupies one workgroup, so with more instances than workgroups smaller teams leave fewer
-    // wavefronts idle. One wavefront where the caller asks for 64-thread workgroups, for no
-    // donations (each workgroup then walks its whole sub-tree in depth-first order), or for
-    // StackOnly; and where a caller's workspace is too small for teams.
+    // wavefronts idle. One wavefront where the caller asks for 64-thread workgroups, for one
+    // workgroup (which visits the same nodes on every run), for no donations (each workgroup then
+    // walks its whole sub-tree in depth-first order), or for StackOnly; and where a caller's
+    // workspace is too small for teams.
     const size_t lds_most = static_cast<size_t>(ctx->prop.maxSharedMemoryPerMultiProcessor) / 2 - 2048;
     const bool so = o && (o->flags & VC_OPT_STACK_ONLY);
     const auto kernel = std::make_tuple(words, pvc, prof, so);
@@ -422,7 +423,7 @@ int plan_launch(vc_ctx* ctx, bool pvc, const Shape& sh, const vc_options* o, Pla
       ctx->bitset_lds_set.insert(kernel);
     }
     const bool alone = (ctx->ws && ctx->ws->narrow) ||
-                       (o && (o->wg_size == 64 || o->wl_threshold == -1 ||
+                       (o && (o->wg_size == 64 || o->num_wg == 1 || o->wl_threshold == -1 ||
                               (o->flags & VC_OPT_STACK_ONLY)));
     int32_t team = alone ? 1 : sh.team ? sh.team : std::min(8, vc::bitset_max_team(words));
     if (!alone && !sh.team)

@@ -398,3 +398,19 @@ def test_node_counts_reported_on_the_way(solver, oracle_lib, budget):
     for flags in (vc.OPT_BITSETS, vc.OPT_DEGREE_ARRAYS):
         r = solver.pvc(g, k, vc.Options(node_budget=budget, flags=flags))
         assert not r.yes and r.stats["nodes"] == want
+
+
+@pytest.mark.parametrize("n", [50, 100, 160, 230])
+def test_one_workgroup_visits_the_same_nodes_on_every_run(solver, oracle_lib, n):
+    """num_wg = 1 with the bitset kernels is one wavefront: the node counts of MVC and of a PVC yes
+    are the same on every run, and those of 64-thread workgroups."""
+    import paper_2204_10402_amd as vc
+    g = G.erdos_renyi(n, 4.6 / n, 11 + n)
+    tau = oracle.mvc(g).size
+    runs = []
+    for o in [vc.Options(num_wg=1)] * 3 + [vc.Options(num_wg=1, wg_size=64)]:
+        m, y, w = solver.mvc(g, o), solver.pvc(g, tau, o), solver.pvc(g, tau - 1, o)
+        assert (m.size, y.yes, w.yes) == (tau, True, False)
+        assert m.stats["wg_size"] == y.stats["wg_size"] == 64 and m.stats["num_wg"] == 1
+        runs.append((m.stats["nodes"], y.stats["nodes"], w.stats["nodes"]))
+    assert len(set(runs)) == 1 and runs[0][2] == oracle.pvc(g, tau - 1).nodes
