@@ -123,10 +123,11 @@ typedef struct {
                            run several launches side by side); 0 = all of it */
   int32_t start_depth;  /* with VC_OPT_STACK_ONLY: depth of the sub-trees handed out, 1..24;
                            0 = 12 */
-  int32_t stack_depth;  /* stack entries per workgroup; 0 = the depth bound of §IV-E (enough
-                           for any search). A smaller value is the caller's promise: a
-                           workgroup that would need more stops the call with
-                           VC_ERR_INTERNAL ("stack overflow") */
+  int32_t stack_depth;  /* stack entries per workgroup, with the bitset kernels per wavefront;
+                           0 = the depth bound of §IV-E (enough for any search). A smaller value
+                           is the caller's promise: a full stack hands its oldest entries over or
+                           donates them to the worklist, and where neither can be done the call
+                           stops with VC_ERR_INTERNAL ("stack overflow") */
   int32_t timeout_ms;   /* > 0: stop each traversal launch after about this many milliseconds
                            of the device clock (measured from the launch's start, checked every
                            few nodes and while idle); the call returns VC_ERR_BUDGET. 0: none */

@@ -1180,24 +1180,16 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     // branch on v_max: defer the N(v_max) child on this wavefront's stack, continue with the v_max
     // child. Idle wavefronts of the team take the oldest entries of the stack (the largest
     // sub-trees it holds) first; else, while the worklist is below its threshold, some are donated.
-    if (top - bot >= cap) {  // cannot happen: the depth bound of §IV-E holds
-      if (lane == 0) {
-        const Params& p = cold_params();
-        atomicMax(ctr_i32(p, kError), 1);
-        store_relaxed(ctr_i32(p, kAbort), 1);
-      }
-      rejoin();
-      if constexpr (SO) break;
-      stop = 1;
-      have = false;
-      top = bot;
-      top_slot = bot_slot;
-      continue;
-    }
-    if (stack_lds) bits_store<W>(lstack + top_slot * kStride, L, vmax, cur);
-    else bits_store<W>(gstack() + static_cast<size_t>(top_slot) * kStride, L, vmax, cur);
-    ++top;
-    top_slot = top_slot + 1 == cap ? 0 : top_slot + 1;
+    // A ring that is full (only one of the caller's size: the depth bound of §IV-E holds else) makes
+    // room that way before the child is deferred.
+    const bool full = top - bot >= cap;
+    const auto defer = [&]() {
+      if (stack_lds) bits_store<W>(lstack + top_slot * kStride, L, vmax, cur);
+      else bits_store<W>(gstack() + static_cast<size_t>(top_slot) * kStride, L, vmax, cur);
+      ++top;
+      top_slot = top_slot + 1 == cap ? 0 : top_slot + 1;
+    };
+    if (!full) defer();
     int given = 0;
     const uint32_t idle = waves > 1 ? __builtin_amdgcn_readfirstlane(idle_raw) : 0u;
     ++quiet;
@@ -1205,8 +1197,9 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
       if (!stack_lds) __threadfence_block();  // lane 0's entry, about to be read by other lanes
       given = team_give<W>(team, idle, top - bot, lstack, stack_lds ? nullptr : gstack(), stack_lds,
                            bot_slot, cap);
-    } else if (seen_count < threshold &&
-               (waves == 1 || (top - bot > 1 && quiet >= kDonateNodes<W>))) {
+    }
+    if (given == 0 && seen_count < threshold &&
+        (full || (!idle && (waves == 1 || (top - bot > 1 && quiet >= kDonateNodes<W>))))) {
       const int m = min(kDonateMost, (top - bot + 1) / 2);
       if (!stack_lds) __threadfence_block();
       const Params& p = cold_params();
@@ -1219,6 +1212,23 @@ __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     }
     bot += given;
     bot_slot = ring_slot(bot_slot, given, cap);
+    if (full) {
+      if (given == 0) {  // no room: the stack overflows
+        if (lane == 0) {
+          const Params& p = cold_params();
+          atomicMax(ctr_i32(p, kError), 1);
+          store_relaxed(ctr_i32(p, kAbort), 1);
+        }
+        rejoin();
+        if constexpr (SO) break;
+        stop = 1;
+        have = false;
+        top = bot;
+        top_slot = bot_slot;
+        continue;
+      }
+      defer();
+    }
     if (given == 0 || top > bot) ++pushes32;
     if (top - bot > max_depth) max_depth = top - bot;
     clk.charge(kActDonate);

@@ -245,3 +245,23 @@ def test_stack_deeper_than_promised_is_an_internal_error(solver, oracle_lib, fla
         solver.mvc(g, o)
     assert e.value.code == vc.ERR_INTERNAL and "stack overflow" in str(e.value)
     assert solver.mvc(g, vc.Options(flags=flags)).size == oracle.mvc(g).size
+
+
+@pytest.mark.parametrize("depth", [1, 2, 3, 8])
+@pytest.mark.parametrize("n", [60, 100, 200, 330])
+def test_small_stacks_are_enough_while_the_worklist_takes_nodes(solver, oracle_lib, n, depth):
+    """stack_depth below the depth of the search: a wavefront whose ring is full hands its oldest
+    entries to idle wavefronts or donates them to the worklist, which is never at its threshold in
+    these trees. MVC, PVC yes, and PVC no node for node, in workgroups of a team and of one."""
+    import paper_2204_10402_amd as vc
+    g = G.erdos_renyi(n, 5.0 / n if n < 200 else 3.3 / n, 3)
+    tau = oracle.mvc(g, node_cap=200000).size
+    want = oracle.pvc(g, tau - 1, node_cap=200000).nodes
+    for wg_size in (0, 64):
+        o = vc.Options(stack_depth=depth, flags=vc.OPT_BITSETS, wg_size=wg_size)
+        m = solver.mvc(g, o)
+        assert m.size == tau and oracle.is_cover(g, m.cover)
+        assert m.stats["max_stack_depth"] <= depth
+        no, yes = solver.pvc(g, tau - 1, o), solver.pvc(g, tau, o)
+        assert not no.yes and no.stats["nodes"] == want
+        assert yes.yes and yes.size <= tau and oracle.is_cover(g, yes.cover)
