@@ -1346,6 +1346,7 @@ int run_in_workspace(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* 
   if (rc != VC_ERR_NO_MEMORY || !wsa.base) return rc;
   // the launches of the families that did fit; their stop is not the second try's
   abort_base += settle(ctx);
+  ctx->last_error.clear();
   WorkspaceScope scope(ctx, wsa.base, wsa.bytes, wsa.host_heap, true);
   return run_batch(ctx, b, pvc, o, out, t0, abort_base);
 }

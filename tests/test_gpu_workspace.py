@@ -265,3 +265,22 @@ def test_small_stacks_are_enough_while_the_worklist_takes_nodes(solver, oracle_l
         no, yes = solver.pvc(g, tau - 1, o), solver.pvc(g, tau, o)
         assert not no.yes and no.stats["nodes"] == want
         assert yes.yes and yes.size <= tau and oracle.is_cover(g, yes.cover)
+
+
+def test_no_error_text_after_a_second_try(solver, oracle_lib, torch_cuda):
+    """A workspace that holds one-wavefront workgroups but not teams: the call succeeds with the
+    smaller plan and leaves no error text."""
+    import paper_2204_10402_amd as vc
+    g = G.erdos_renyi(120, 2.5 / 120, 0)
+    rp, ci, cover = dev(torch_cuda, g)
+    full = workspace(torch_cuda, 1 << 24)
+    lo, hi = 0, 1 << 16
+    while hi - lo > 1:  # the least workspace of 64-thread workgroups, in units of 256 bytes
+        mid = (lo + hi) // 2
+        try:
+            solver.mvc_device_ws(rp, ci, full[:mid * 256], cover, vc.Options(wg_size=64))
+            hi = mid
+        except vc.VCError:
+            lo = mid
+    assert solver.mvc_device_ws(rp, ci, full[:hi * 256], cover).stats["wg_size"] == 64
+    assert solver._lib.vc_last_error(solver._ctx) == b""
