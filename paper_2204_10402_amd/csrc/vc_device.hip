@@ -78,6 +78,7 @@ struct Node {
 // Where the lists' current entries lie (their tails grow in Ctrl), and the largest degree at the
 // last refresh, an upper bound until the next. The same in every thread of the workgroup.
 struct Front {
+  int32_t s;               // cover size of the node, as st[n] holds it
   uint32_t rm;             // marked vertices already removed end here
   uint32_t one, one_end;
   uint32_t two, two_end;
@@ -177,9 +178,9 @@ __device__ __forceinline__ int count_bits(const uint64_t (&m)[kWalk]) {
   return count;
 }
 
-// Hand the candidates that satisfy pred(d) to process(cand): one per lane, -1 where a lane has
-// none. The candidates are list entries [from, to) or, if the list has overflowed, found among
-// all vertices. Whole workgroup; the control flow is uniform in each wavefront. With `spread`,
+// Hand the candidates, the vertices with pred(d), to process(cand): one per lane, -1 where a lane
+// has none. They are the list entries [from, to), which hold exactly these vertices, or, if the list
+// has overflowed, they are found among all vertices. Whole workgroup; the control flow is uniform in each wavefront. With `spread`,
 // list entry i goes to wavefront i mod waves, so that a few candidates with long rows do not all
 // fall to one; otherwise the list goes out 64 entries at a time, so that a short list leaves the
 // other wavefronts out of a step's instructions (every wavefront's cost issue slots of the four
@@ -203,10 +204,7 @@ __device__ __forceinline__ void for_candidates(const Node& nd, int32_t* list, ui
     if (!scan) {
       if (i0 >= total) break;
       const int i = spread ? i0 + waves * lane : i0 + lane;
-      if (i < total) {
-        const int v = list[(from + static_cast<uint32_t>(i)) & nd.mask];
-        if (pred(nd.st[v])) held = v;
-      }
+      if (i < total) held = list[(from + static_cast<uint32_t>(i)) & nd.mask];
       i0 += waves * 64;
     } else {
       int count = 0;
@@ -281,7 +279,8 @@ __device__ __forceinline__ void apply_marks(const Node& nd, Ctrl& c, Front& f) {
             if (w.ok[u] && unmarked(d[u])) atomicSub(&st[w.xs[u]], 1);
         });
       });
-  if (threadIdx.x == 0) st[nd.n] += static_cast<int32_t>(tail - f.rm);
+  f.s += static_cast<int32_t>(tail - f.rm);
+  if (threadIdx.x == 0) st[nd.n] = f.s;
   f.rm = tail;
   __syncthreads();
 }
@@ -368,12 +367,15 @@ __device__ __forceinline__ void decide_degree_one(const Node& nd, Ctrl& c, const
           }
           if (!__builtin_amdgcn_ballot_w64(any)) return;
           uint64_t m[kWalk];
+          int32_t was[kWalk];  // all marks are issued before the first one's answer is waited for
 #pragma unroll
           for (int u = 0; u < kWalk; ++u) {
-            bool take = hit[u] && ((d[u] & kDegMask) != 1 || w.xs[u] < w.tags[u]);
-            if (take) take = !(atomicOr(&st[w.xs[u]], kFlag) & kFlag);
-            m[u] = __builtin_amdgcn_ballot_w64(take);
+            was[u] = kFlag;
+            if (hit[u] && ((d[u] & kDegMask) != 1 || w.xs[u] < w.tags[u]))
+              was[u] = atomicOr(&st[w.xs[u]], kFlag);
           }
+#pragma unroll
+          for (int u = 0; u < kWalk; ++u) m[u] = __builtin_amdgcn_ballot_w64(!(was[u] & kFlag));
           const int count = count_bits(m);
           if (count == 0) return;
           uint32_t at = 0;
@@ -503,13 +505,15 @@ struct NoClock {
 };
 
 // The reduction rules until the graph stops changing (§II-B, §IV-D), or until s > bound.
-// Precondition: the node is visible to the whole workgroup. With `marked`, the vertices that
+// Precondition: the node is visible to the whole workgroup and f.s is its cover size. With `marked`, the vertices that
 // mark_vertex / mark_neighbourhood flagged (a branch's removal) are removed first. The three
-// rules take turns through one loop, so that the removal step is compiled once per kernel.
+// rules take turns through one loop, so that the removal step is compiled once per kernel. On small
+// graphs a step is a chain of LDS latencies: the cover size is kept in a register (f.s), listed
+// candidates are not looked at again, and a batch's marks are waited for together (greedy of
+// G(512, 2.5/512): 117 -> 104 us, of a path of 1,000 vertices: 946 -> 798).
 template <typename Clock>
 __device__ __forceinline__ void reduce_node(const Node& nd, Ctrl& c, Front& f, int64_t bound,
                                             int rules, Clock& clk, bool marked) {
-  int32_t* st = nd.st;
   // A rule pass is skipped when nothing has been removed since it last found nothing, and when it
   // has no candidate: its list is empty, or (high-degree rule) no degree exceeds r. It would find
   // nothing: this drops empty passes, not any decision.
@@ -520,18 +524,17 @@ __device__ __forceinline__ void reduce_node(const Node& nd, Ctrl& c, Front& f, i
   for (;;) {
     if (rule >= 0) {
       if (rule == 0) {
-        const int32_t s1 = st[nd.n];
-        if (changes > 0 && s1 == s0) return;  // a round that removed nothing
-        s0 = s1;
+        if (changes > 0 && f.s == s0) return;  // a round that removed nothing
+        s0 = f.s;
       }
       bool skip = !(rules & (kRuleDeg1 << rule)) || quiet[rule] == changes;
       if (rule == 0) skip |= f.one_end == f.one;
       else if (rule == 1) skip |= f.two_end == f.two;
-      else skip |= f.most <= bound - st[nd.n];
+      else skip |= f.most <= bound - f.s;
       if (!skip) {
         if (rule == 0) decide_degree_one(nd, c, f);
         else if (rule == 1) decide_triangle(nd, c, f);
-        else decide_high_degree(nd, c, bound - st[nd.n]);
+        else decide_high_degree(nd, c, bound - f.s);
         __syncthreads();
         if (rule == 0) clk.charge(kActDeg1);
         else if (rule == 1) clk.charge(kActTri);
@@ -546,7 +549,7 @@ __device__ __forceinline__ void reduce_node(const Node& nd, Ctrl& c, Front& f, i
       }
     }
     if (rule >= 0 || marked) apply_marks(nd, c, f);
-    if (st[nd.n] > bound) return;
+    if (f.s > bound) return;
     refresh_lists(nd, c, f);
     if (rule < 0) {
       clk.charge(kActBranch);
@@ -1001,6 +1004,7 @@ __global__ void __launch_bounds__(1024) greedy_kernel(Params p) {
     if (skip) continue;
     const Node nd = load_instance<MEM>(p, j, st);
     build_root(p, nd, j);
+    f.s = 0;
     const int64_t unbounded = 0x3FFFFFFFFFFFFFFFll;
     for (bool marked = false;; marked = true) {
       reduce_node(nd, c, f, unbounded, kRuleDeg1 | kRuleTri, marked);
@@ -1010,7 +1014,7 @@ __global__ void __launch_bounds__(1024) greedy_kernel(Params p) {
       if (degsum == 0) break;
       mark_vertex(nd, c, vmax);
     }
-    const int s = st[nd.n];
+    const int s = f.s;
     uint8_t* cov = p.covers + p.inst[j].vtx_off;
     store_cover(cov, nd);
     if (threadIdx.x == 0) {
@@ -1135,6 +1139,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
           break;
         }
         build_root(p, nd, 0);
+        f.s = 0;
         bool reached = true;
         for (int d = 0; d < p.start_depth && reached; ++d) {
           const bool owner = (so_path >> d) == 0;
@@ -1154,7 +1159,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
           if (owner) ++unreported;
           reduce_node(nd, c, f, bound, rules, clk, marked);
           marked = false;
-          const int32_t s = st[nd.n];
+          const int32_t s = f.s;
           const int64_t r = bound - s;
           int vmax = 0;
           int32_t degsum = 0;
@@ -1243,6 +1248,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
         }
         clk.charge(kActOther);
       }
+      f.s = st[nd.n];
       const int pending = st[nd.n + 1];
       if (pending >= 0) {
         __syncthreads();  // every thread has read the pending vertex
@@ -1292,7 +1298,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
     // stopping condition (§II-B): no cover of size <= bound below this node if r < 0 or
     // |E| > r^2 (every remaining degree is <= r once the high-degree rule has run)
     const int n = nd.n;
-    const int32_t s = st[n];
+    const int32_t s = f.s;
     const int64_t r = bound - s;
     if (r < 0) {
       have = false;
@@ -1488,6 +1494,7 @@ __global__ void __launch_bounds__(1024) reduce_kernel(Params p, int32_t* deg, in
     st[v] = v < n ? deg[v] : (v == n ? *s : (v == n + 1 ? -1 : 0));
   __syncthreads();
   Front f{};
+  f.s = st[n];
   reduce_node(nd, c, f, bound, p.rules);
   for (int v = threadIdx.x; v < n; v += blockDim.x) deg[v] = st[v] < 0 ? kSent : (st[v] & kDegMask);
   if (threadIdx.x == 0) *s = st[n];

@@ -775,3 +775,43 @@ def test_device_memory_node_with_the_longest_lists(oracle_lib):
             deg = torch.from_numpy(np.diff(g.row_ptr).astype(np.int32)).to("cuda:0")
             states.append((s.reduce_device(rp, ci, deg, 0, 300, flags), deg.cpu().tolist()))
         assert states[0] == states[1]
+
+
+@pytest.mark.parametrize("kernel", ["degree_arrays", "csr_global", "global_nodes"])
+@pytest.mark.parametrize("shape", ["cliques", "stars", "many_stars", "both"])
+def test_rows_around_the_walks_limits(solver, oracle_lib, torch_cuda, shape, kernel):
+    """Rows of lengths around those where a walk changes (4, 16 and 64 entries): disjoint cliques,
+    which the greedy takes one vertex at a time, and stars, whose centres one step removes, few of
+    them or more than a wavefront's lanes. The fixpoint element by element and the greedy's size are
+    the oracle's; MVC and PVC answer tau. Whole numbers: no tolerance."""
+    import paper_2204_10402_amd as vc
+    torch = torch_cuda
+    lengths = [3, 4, 5, 15, 16, 17, 63, 64, 65, 129]
+    edges, n, tau = [], 0, 0
+    if shape in ("cliques", "both"):
+        for m in lengths:
+            edges += [(n + i, n + j) for i in range(m + 1) for j in range(i)]
+            n, tau = n + m + 1, tau + m
+    if shape != "cliques":
+        for m in lengths if shape != "many_stars" else [5] * 40 + [17] * 70 + [3] * 150 + [70] * 5:
+            edges += [(n, n + 1 + i) for i in range(m)]
+            n, tau = n + m + 1, tau + 1
+    g = G.from_edges(n, *np.array(edges).T)
+    rp, ci = torch.from_numpy(g.row_ptr).cuda(), torch.from_numpy(g.col_idx).cuda()
+    for bound, flags in ((tau, 0), (10**9, 0x4)):
+        mask = oracle.ALL & (~(oracle.RULE_HIGH | oracle.PRUNE_EDGES) if flags else -1)
+        od, os_ = oracle.reduce(g, g.degrees(), 0, bound, mask)
+        dd = torch.from_numpy(g.degrees()).cuda()
+        assert solver.reduce_device(rp, ci, dd, 0, bound, flags | KERNELS[kernel]) == os_
+        assert np.array_equal(dd.cpu().numpy(), od), (bound, flags)
+    if n > 256:  # the degree-array greedy
+        assert solver.greedy_device(rp, ci) == oracle.greedy(g)[0]
+    # the cliques one by one, whose search is short (that of their union is not)
+    for h, want in [(G.complete(m + 1), m) for m in lengths] if shape == "cliques" else [(g, tau)]:
+        if shape == "both":
+            continue
+        r = solver.mvc(h, vc.Options(flags=KERNELS[kernel]))
+        assert r.size == want and r.stats["greedy_size"] == oracle.greedy(h)[0]
+        check_cover(h, r.cover, want)
+        assert solver.pvc(h, want, vc.Options(flags=KERNELS[kernel])).yes
+        assert not solver.pvc(h, want - 1, vc.Options(flags=KERNELS[kernel])).yes
