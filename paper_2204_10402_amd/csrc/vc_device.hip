@@ -84,6 +84,11 @@ struct Front {
   uint32_t two, two_end;
   int32_t most;
   uint32_t turn;           // refreshes so far
+  // The instance has shown a degree above kLaneRow: removal steps spread their rows, also where the
+  // average degree is small. In a planted graph of average degree 6 the removed vertices' rows have
+  // 30 to 60 entries, and all fell to one or two wavefronts (greedy of 512 / 1,000 / 4,000 vertices
+  // 46 -> 40.5, 50 -> 42.5, 63 -> 52 us).
+  bool wide;
 };
 
 // Rows longer than this are walked in 64-entry pieces by the whole wavefront; shorter ones by
@@ -263,7 +268,7 @@ __device__ __forceinline__ void apply_marks(const Node& nd, Ctrl& c, Front& f) {
   int32_t* st = nd.st;
   const uint32_t tail = c.rm_tail;
   for_candidates(
-      nd, nd.rm, f.rm, tail, nd.spread, [](int32_t d) { return d >= 0 && (d & kFlag); },
+      nd, nd.rm, f.rm, tail, nd.spread || f.wide, [](int32_t d) { return d >= 0 && (d & kFlag); },
       [&](int v) {
         const bool mine = v >= 0;
         if (mine) st[v] = kSent;
@@ -343,6 +348,7 @@ __device__ __forceinline__ void refresh_lists(const Node& nd, Ctrl& c, Front& f)
   f.one_end = c.one_tail;
   f.two_end = c.two_tail;
   f.most = block_part_max(part);
+  f.wide |= f.most > kLaneRow;
 }
 
 // Degree-one rule (§II-B): v with one live neighbour u puts u in the cover; of two adjacent
@@ -1008,6 +1014,7 @@ __global__ void __launch_bounds__(1024) greedy_kernel(Params p) {
     const Node nd = load_instance<MEM>(p, j, st);
     build_root(p, nd, j);
     f.s = 0;
+    f.wide = false;
     const int64_t unbounded = 0x3FFFFFFFFFFFFFFFll;
     for (bool marked = false;; marked = true) {
       reduce_node(nd, c, f, unbounded, kRuleDeg1 | kRuleTri, marked);
@@ -1232,6 +1239,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
           if (tid == 0 && cur >= 0) report_nodes(p, cur, unreported);
           unreported = 0;
           nd = load_instance<MEM>(p, j, st);
+          f.wide = false;
           const Instance in = p.inst[j];
           cur = j;
           cur_k = in.k;
