@@ -254,6 +254,23 @@ __device__ __forceinline__ int32_t block_part_max(const int32_t* part) {
   return static_cast<int32_t>(wave_max32(static_cast<uint32_t>(x)));
 }
 
+// The neighbours in a batch of walked entries lose one degree each (see apply_marks).
+__device__ __forceinline__ void drop_degrees(const Node& nd, const Walked& w) {
+  int32_t* st = nd.st;
+  if (nd.far) {
+#pragma unroll
+    for (int u = 0; u < kWalk; ++u)
+      if (w.ok[u]) atomicSub(&st[w.xs[u]], 1);
+    return;
+  }
+  int32_t d[kWalk];
+#pragma unroll
+  for (int u = 0; u < kWalk; ++u) d[u] = st[w.xs[u]];
+#pragma unroll
+  for (int u = 0; u < kWalk; ++u)
+    if (w.ok[u] && unmarked(d[u])) atomicSub(&st[w.xs[u]], 1);
+}
+
 // Remove every marked vertex (paper §IV-B): marked vertices become kSent and s grows by their
 // number; each live unmarked neighbour of a marked vertex loses one degree per marked neighbour.
 // The walks only decrement entries that are live and unmarked (a marked vertex may turn kSent
@@ -272,20 +289,8 @@ __device__ __forceinline__ void apply_marks(const Node& nd, Ctrl& c, Front& f) {
       [&](int v) {
         const bool mine = v >= 0;
         if (mine) st[v] = kSent;
-        walk_rows(nd.ci, mine ? nd.rp[v] : 0, mine ? nd.rp[v + 1] : 0, v, [&](const Walked& w) {
-          if (nd.far) {
-#pragma unroll
-            for (int u = 0; u < kWalk; ++u)
-              if (w.ok[u]) atomicSub(&st[w.xs[u]], 1);
-            return;
-          }
-          int32_t d[kWalk];
-#pragma unroll
-          for (int u = 0; u < kWalk; ++u) d[u] = st[w.xs[u]];
-#pragma unroll
-          for (int u = 0; u < kWalk; ++u)
-            if (w.ok[u] && unmarked(d[u])) atomicSub(&st[w.xs[u]], 1);
-        });
+        walk_rows(nd.ci, mine ? nd.rp[v] : 0, mine ? nd.rp[v + 1] : 0, v,
+                  [&](const Walked& w) { drop_degrees(nd, w); });
       });
   f.s += static_cast<int32_t>(tail - f.rm);
   if (threadIdx.x == 0) st[nd.n] = f.s;
@@ -515,7 +520,7 @@ struct NoClock {
 
 // The reduction rules until the graph stops changing (§II-B, §IV-D), or until s > bound.
 // Precondition: the node is visible to the whole workgroup and f.s is its cover size. With `marked`, the vertices that
-// mark_vertex / mark_neighbourhood flagged (a branch's removal) are removed first. The three
+// mark_neighbourhood flagged (a branch's removal) are removed first. The three
 // rules take turns through one loop, so that the removal step is compiled once per kernel. On small
 // graphs a step is a chain of LDS latencies: the cover size is kept in a register (f.s), listed
 // candidates are not looked at again, and a batch's marks are waited for together (greedy of
@@ -648,12 +653,19 @@ __device__ __forceinline__ void mark_neighbourhood(const Node& nd, Ctrl& c, int 
   __syncthreads();
 }
 
-// Flag v alone (the "v in the cover" child, §II-B); the next reduce_node (marked = true)
-// removes it. Ends with a barrier.
-__device__ __forceinline__ void mark_vertex(const Node& nd, Ctrl& c, int v) {
-  if (threadIdx.x == 0) {
-    nd.st[v] |= kFlag;
-    nd.rm[c.rm_tail++ & nd.mask] = v;
+// Remove v alone, a live vertex that every thread names, from a node with nothing marked (the "v in
+// the cover" child, §II-B). One wavefront walks its row: no list to go through, and one barrier, at
+// the end (greedy of G(1000, 8/1000), a vertex a step: 2,201 -> 2,053 us).
+__device__ __forceinline__ void remove_vertex(const Node& nd, Front& f, int v) {
+  f.s += 1;
+  if (wave_id() == 0) {
+    const bool mine = lane_id() == 0;
+    if (mine) {
+      nd.st[v] = kSent;
+      nd.st[nd.n] = f.s;
+    }
+    walk_rows(nd.ci, mine ? nd.rp[v] : 0, mine ? nd.rp[v + 1] : 0, v,
+              [&](const Walked& w) { drop_degrees(nd, w); });
   }
   __syncthreads();
 }
@@ -1016,13 +1028,13 @@ __global__ void __launch_bounds__(1024) greedy_kernel(Params p) {
     f.s = 0;
     f.wide = false;
     const int64_t unbounded = 0x3FFFFFFFFFFFFFFFll;
-    for (bool marked = false;; marked = true) {
-      reduce_node(nd, c, f, unbounded, kRuleDeg1 | kRuleTri, marked);
+    for (;;) {
+      reduce_node(nd, c, f, unbounded, kRuleDeg1 | kRuleTri);
       int vmax;
       int32_t degsum;
       max_degree_and_sum(nd, c, f, vmax, degsum);
       if (degsum == 0) break;
-      mark_vertex(nd, c, vmax);
+      remove_vertex(nd, f, vmax);
     }
     const int s = f.s;
     uint8_t* cov = p.covers + p.inst[j].vtx_off;
@@ -1191,9 +1203,9 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
             }
             reached = false;
           } else {
-            if ((so_path >> d) & 1u) mark_neighbourhood(nd, c, vmax);
-            else mark_vertex(nd, c, vmax);
-            marked = true;
+            marked = (so_path >> d) & 1u;
+            if (marked) mark_neighbourhood(nd, c, vmax);
+            else remove_vertex(nd, f, vmax);
           }
           __syncthreads();  // every thread has read c.* before thread 0 writes it again
         }
@@ -1369,8 +1381,7 @@ __global__ void __launch_bounds__(1024) traverse_kernel(Params args) {
       __syncthreads();  // the copy has read the node before it changes below
     }
     clk.charge(kActDonate);
-    mark_vertex(nd, c, vmax);
-    marked = true;
+    remove_vertex(nd, f, vmax);
     clk.charge(kActBranch);
   }
   clk.end();
