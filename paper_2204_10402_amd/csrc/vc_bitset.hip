@@ -660,7 +660,8 @@ __device__ __forceinline__ int team_give(Team<W>& t, uint32_t idle, int avail,
   const uint32_t bit = lane < 32 ? 1u << lane : 0u;
   bool claim = (idle & bit) && __popc(idle & (bit - 1u)) < avail;
   if (claim)
-    claim = __hip_atomic_fetch_and(&t.idle, ~bit, __ATOMIC_RELAXED,
+    // (acquire: the receiver's reads of its box's last content come before the writes below)
+    claim = __hip_atomic_fetch_and(&t.idle, ~bit, __ATOMIC_ACQUIRE,
                                    __HIP_MEMORY_SCOPE_WORKGROUP) & bit;
   const uint64_t mask = ballot(claim);
   const int given = __popcll(mask);
