@@ -168,8 +168,8 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
                                    __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0));
 }
 
-// Append this lane's values v[u], where its bit of m[u] is set, to a list at `at` (the result of
-// list_reserve). Uniform control flow.
+// Append this lane's values v[u], where its bit of m[u] is set, to a list at `at` (its tail before
+// the wavefront raised it by count_bits(m)). Uniform control flow.
 __device__ __forceinline__ void list_write(int32_t* list, uint32_t mask, uint32_t at,
                                            const uint64_t (&m)[kWalk], const int (&v)[kWalk]) {
 #pragma unroll

@@ -1,6 +1,6 @@
 // vc_device_common.h -- device building blocks shared by the degree-array kernels
 // (vc_device.hip) and the bitset kernels (vc_bitset.hip): scoped atomics on the control
-// words, wavefront-64 DPP reductions and scans, the worklist protocol, the activity clock.
+// words, wavefront-64 DPP reductions, the worklist protocol, the activity clock.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -146,55 +146,10 @@ struct Ctrl {
   int32_t red_sum[kMaxWaves];
 };
 
-// ---- wavefront building blocks ---------------------------------------------------------------
-
-// Inclusive prefix sum over the 64 lanes: DPP row shifts inside each 16-lane row, then row
-// broadcasts (row_bcast:15 to rows 1 and 3, row_bcast:31 to rows 2 and 3).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int32_t dpp_or_zero(int32_t x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xF, false);
-}
-__device__ __forceinline__ int32_t wave_incl_scan(int32_t x) {
-  x += dpp_or_zero<0x111, 0xF>(x);  // row_shr:1
-  x += dpp_or_zero<0x112, 0xF>(x);  // row_shr:2
-  x += dpp_or_zero<0x114, 0xF>(x);  // row_shr:4
-  x += dpp_or_zero<0x118, 0xF>(x);  // row_shr:8
-  x += dpp_or_zero<0x142, 0xA>(x);  // row_bcast:15
-  x += dpp_or_zero<0x143, 0xC>(x);  // row_bcast:31
-  return x;
-}
-
-__device__ __forceinline__ int shfl(int x, int src_lane) {
-  return __builtin_amdgcn_ds_bpermute(src_lane << 2, x);
-}
-
-// Index of the k-th (from 0) set bit of m; m must have more than k set bits.
-__device__ __forceinline__ int kth_set_bit(uint64_t m, int k) {
-  int pos = 0;
-  uint32_t w = static_cast<uint32_t>(m);
-  int c = __popc(w);
-  if (k >= c) {
-    k -= c;
-    pos = 32;
-    w = static_cast<uint32_t>(m >> 32);
-  }
-#pragma unroll
-  for (int half = 16; half > 0; half >>= 1) {
-    c = __popc(w & ((1u << half) - 1u));
-    if (k >= c) {
-      k -= c;
-      pos += half;
-      w >>= half;
-    }
-  }
-  return pos;
-}
-
 __device__ __forceinline__ void backoff(int& spins) {
   if (spins < 8) ++spins;
   for (int i = 0; i < spins; ++i) __builtin_amdgcn_s_sleep(8);
 }
-
 
 // An instance's best size (low half) and state flags (high half), read as one word.
 __device__ __forceinline__ uint64_t inst_header(const Params& p, int j) {
