@@ -33,9 +33,9 @@
  * vc_last_error() describes the failure.
  *
  * Batches: vc_mvc_batch / vc_pvc_batch solve many independent graphs in one persistent
- * launch per kernel family (bitset kernels by words per row, degree-array kernels): every
- * graph's root is handed out to the workgroups in turn, and the sub-trees of all graphs share
- * one worklist. A single-graph call is a batch of one.
+ * launch per kernel family (bitset kernels by words per row, one launch for all graphs above 256
+ * vertices; degree-array kernels): every graph's root is handed out to the workgroups in turn, and
+ * the sub-trees of a launch's graphs share one worklist. A single-graph call is a batch of one.
  */
 #ifndef VC_H
 #define VC_H
@@ -71,8 +71,9 @@ extern "C" {
                                      VC_OPT_CSR_GLOBAL and VC_OPT_STACK_ONLY select them above
                                      256): a node is an int32 degree array in LDS */
 #define VC_OPT_BITSETS 0x40       /* use the bitset kernels (the default up to 256 vertices, for
-                                     PVC up to 512; available up to 512, VC_ERR_INVALID_ARG above): a node is
-                                     the set of live vertices, held in registers */
+                                     PVC up to 512; available up to 512, VC_ERR_INVALID_ARG
+                                     above): a node is the set of live vertices, held in
+                                     registers */
 #define VC_OPT_STACK_ONLY 0x100   /* ablation: the StackOnly method the paper compares with
                                      (§V-A): no worklist; workgroup w takes the sub-trees at
                                      depth start_depth numbered w, w + grid, ..., walks down
@@ -117,7 +118,9 @@ typedef struct {
                            this many entries (§IV-A); 0 = auto; -1 = never donate (every
                            workgroup keeps its whole sub-tree on its own stack) */
   int64_t node_budget;  /* stop with VC_ERR_BUDGET after about this many nodes (per graph
-                           of a batch); 0 = none */
+                           of a batch); 0 = none. Nodes are reported now and then, so up to about
+                           half as many more may be visited, and a few by each wavefront of the
+                           grid where the budget is small */
   int32_t flags;        /* VC_OPT_* */
   int32_t grid_share;   /* > 0: use at most 1/grid_share of the co-resident grid (callers that
                            run several launches side by side); 0 = all of it */

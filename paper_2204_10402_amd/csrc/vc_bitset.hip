@@ -10,10 +10,10 @@
 // is recomputed as popcount(adj[v] & L).
 //
 // One wavefront per node, several to a workgroup (a team, which shares the adjacency matrix and
-// hands sub-trees over inside the workgroup; see Team). Lane l holds vertices l, 64+l, ..., (W-1)*64+l and their W
-// adjacency words each in vector registers; the whole adjacency matrix also sits in LDS for
-// random access (the triangle test). A rule pass is a handful of ballots and bit operations;
-// the main loop has no barriers except inside the worklist protocol.
+// hands sub-trees over inside the workgroup; see Team). Lane l holds vertices l, 64+l, ...,
+// (W-1)*64+l and their W adjacency words each in vector registers; the whole adjacency matrix also
+// sits in LDS for random access (the triangle test). A rule pass is a handful of ballots and bit
+// operations; the main loop has no barriers except where a team looks for work.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -809,6 +809,11 @@ constexpr uint32_t kDonateNodes = W >= 5 ? 4 : 8;
 // its own stack; the wavefronts of a workgroup (a team) share the instance's adjacency matrix and
 // pass sub-trees to each other in LDS, and the workgroup as a whole takes nodes and roots from
 // the launch's worklist when all of its wavefronts have run out.
+// Registers: a lane's adjacency rows take 2 W^2 of them. Up to seven words the kernel is held to two
+// wavefronts per SIMD; at seven that spills about 40 registers to scratch, which costs less than half
+// the wavefronts do (16 graphs G(390, 3.5/390): 1.76 ms, with one wavefront per SIMD and no spill
+// 2.37; planted batch of 40-400 vertices level). Eight words take about 400 registers and one
+// wavefront per SIMD.
 template <int W, bool PVC, bool PROF, bool SO>
 __global__ void __launch_bounds__(64 * bitset_max_team(W), W <= 7 ? 2 : 1)
     bitset_traverse_kernel(Params args) {

@@ -13,9 +13,9 @@
 //    pointers, and the column indices too when they fit, are staged in LDS after it. Where
 //    each of them lives is a template parameter of the kernels, so every access compiles to
 //    an LDS or a device-memory instruction, never a generic one;
-//  - vertices are processed in 64-vertex chunks, one chunk per wavefront at a time; a
-//    ballot over the chunk yields the candidates; a candidate's CSR row is walked by its own
-//    lane when it is short, and in 64-entry pieces by the whole wavefront when it is long;
+//  - after each removal step one scan lists the vertices of degree one and two and finds the
+//    largest degree; the rule passes work on those lists. A candidate's CSR row is walked by its
+//    own lane when it is short, and in 64-entry pieces by the whole wavefront when it is long;
 //  - the maximum-degree vertex and the degree sum come from one pass reduced with DPP row
 //    operations inside each wavefront and one LDS step across wavefronts;
 //  - a deferred child is stored as its parent's reduced degree array plus the vertex whose
@@ -188,12 +188,12 @@ __device__ __forceinline__ int count_bits(const uint64_t (&m)[kWalk]) {
 
 // Hand the candidates, the vertices with pred(d), to process(cand): one per lane, -1 where a lane
 // has none. They are the list entries [from, to), which hold exactly these vertices, or, if the list
-// has overflowed, they are found among all vertices. Whole workgroup; the control flow is uniform in each wavefront. With `spread`,
-// list entry i goes to wavefront i mod waves, so that a few candidates with long rows do not all
-// fall to one; otherwise the list goes out 64 entries at a time, so that a short list leaves the
-// other wavefronts out of a step's instructions (every wavefront's cost issue slots of the four
-// SIMDs, whether or not its lanes hold a candidate). The scan stages its finds in the wavefront's
-// share of the overflowed list; a chunk with more finds than that goes out as it is.
+// has overflowed, they are found among all vertices. Whole workgroup; the control flow is uniform in
+// each wavefront. With `spread`, list entry i goes to wavefront i mod waves, so that a few candidates
+// with long rows do not all fall to one; otherwise the list goes out 64 entries at a time, so that a
+// short list leaves the other wavefronts out of a step's instructions (every wavefront's cost issue
+// slots of the four SIMDs, whether or not its lanes hold a candidate). The scan stages its finds in
+// the wavefront's share of the overflowed list; a chunk with more finds than that goes out as it is.
 template <typename Pred, typename Proc>
 __device__ __forceinline__ void for_candidates(const Node& nd, int32_t* list, uint32_t from,
                                                uint32_t to, bool spread, Pred pred,
@@ -519,11 +519,11 @@ struct NoClock {
 };
 
 // The reduction rules until the graph stops changing (§II-B, §IV-D), or until s > bound.
-// Precondition: the node is visible to the whole workgroup and f.s is its cover size. With `marked`, the vertices that
-// mark_neighbourhood flagged (a branch's removal) are removed first. The three
-// rules take turns through one loop, so that the removal step is compiled once per kernel. On small
-// graphs a step is a chain of LDS latencies: the cover size is kept in a register (f.s), listed
-// candidates are not looked at again, and a batch's marks are waited for together (greedy of
+// Precondition: the node is visible to the whole workgroup and f.s is its cover size. With `marked`,
+// the vertices that mark_neighbourhood flagged (a stored child's pending removal) are removed first.
+// The three rules take turns through one loop, so that the removal step is compiled once per kernel.
+// On small graphs a step is a chain of LDS latencies: the cover size is kept in a register (f.s),
+// listed candidates are not looked at again, and a batch's marks are waited for together (greedy of
 // G(512, 2.5/512): 117 -> 104 us, of a path of 1,000 vertices: 946 -> 798).
 template <typename Clock>
 __device__ __forceinline__ void reduce_node(const Node& nd, Ctrl& c, Front& f, int64_t bound,

@@ -333,7 +333,7 @@ int occupancy(vc_ctx* ctx, int words, bool pvc, bool prof, int ws, size_t lds, i
   return VC_OK;
 }
 
-// Kernel family of a graph: bitset kernels with ceil(n/64) words up to kAutoBitsetN vertices
+// Kernel family of a graph by itself: bitset kernels with ceil(n/64) words up to kAutoBitsetN vertices
 // (kAutoBitsetNPvc for PVC, up to kMaxBitsetN when the caller asks for them), else degree arrays
 // (0). Above kAutoBitsetN an option that only the degree-array kernels know keeps them: a
 // workgroup size, how they read the CSR, or StackOnly's walk.
@@ -787,7 +787,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     g.entries += in.nnz;
   }
   hipStream_t st = ctx->stream;
-  // A batch that mixes graphs of up to four bitset words with larger ones (wider bitsets, degree
+  // A batch that mixes graphs of up to four bitset words with larger ones (wide bitsets, degree
   // arrays) runs the larger ones' launches on the auxiliary context (first, as the longest) while
   // the others follow on this one: the persistent launches share the device instead of queueing
   // behind each other. Not when the caller already runs launches side by side on shares of the
@@ -869,10 +869,9 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
       // Two launches side by side. A degree-array launch, which holds its CUs to the end, takes a
       // third of the co-resident grid and leaves half to the bitset launches beside it; the rest
       // stays free for the short validation and check kernels of the other stream (full grids
-      // starved them). Bitset launches are short: the wider ones take a third and the others the
-      // whole grid (4,096 planted graphs of 40-400 / 860 of 99-363 vertices, shares wider : other
-      // 1 : 1 1.86 / 0.70 ms, half : half 2.06 / 0.56, half : 1 2.00 / 0.55, third : half 1.93 /
-      // 0.60, quarter : 1 1.74 / 0.62, all on one stream 2.03 / 0.79).
+      // starved them). Bitset launches are short: the wide one takes a third and the others the whole
+      // grid (4,096 planted graphs of 40-400 / 3,662 of 65-262 vertices, share of the wide launch 1:
+      // 1.58 / 0.89 ms, half: 1.43 / 0.93, third: 1.34 / 0.95, quarter: 1.42 / 0.95).
       const bool arrays = groups.back().words == 0;
       shared.grid_share = std::max(shared.grid_share, 1) * (large(gi) ? 3 : arrays ? 2 : 1);
       go = &shared;
@@ -918,7 +917,8 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
     p.covers = covers;
     p.wg_stats = static_cast<vc::WgStats*>(lc->wg_stats.ptr);
     p.node_budget = o ? o->node_budget : 0;
-    // report often enough that the whole grid overshoots a budget by at most about half
+    // report often enough that all wavefronts of the grid together overshoot a budget by at most
+    // about half
     p.budget_chunk = std::max<int64_t>(1, std::min<int64_t>(1024, p.node_budget / (2ll * pl.num_wg * pl.team)));
     p.q_cap = pl.cap;
     p.q_threshold = pl.threshold;
@@ -1045,7 +1045,7 @@ int run_batch(vc_ctx* ctx, const BatchIn& b, bool pvc, const vc_options* o, Batc
         std::vector<std::tuple<int, int, int>> cand;
         cand.emplace_back(0, 0, 0);
         if (g.words) {
-          // 8 to 32 wavefronts per CU in teams of up to 16, and workgroups of one wavefront
+          // 8 to 24 wavefronts per CU in teams of up to 16, and workgroups of one wavefront
           for (const auto& tw : {std::make_pair(16, 1), std::make_pair(8, 1), std::make_pair(8, 2),
                                  std::make_pair(8, 3), std::make_pair(4, 4), std::make_pair(1, 8),
                                  std::make_pair(1, 16)})

@@ -132,12 +132,13 @@ struct Params {
   int32_t* payload;     // worklist node storage: q_cap * stride
   uint32_t* seq;        // worklist slot tickets: q_cap
   int32_t* ctr;         // control lines: kNumCounters * kCounterStride
-  int32_t* stacks;      // per-workgroup stacks: num_wg * depth_cap * stride
+  int32_t* stacks;      // stacks: num_wg * depth_cap * stride, a bitset team's times `team`
   uint8_t* covers;      // packed covers, one n_i-byte cover per instance
   WgStats* wg_stats;    // num_wg
   DevResult* res;       // launch result block: every workgroup adds its statistics at exit
   int64_t node_budget;  // per instance; 0 = none
-  int64_t budget_chunk; // nodes a workgroup visits between two reports to its instance
+  int64_t budget_chunk; // nodes a workgroup (bitsets: a wavefront) visits between two reports to its
+                        // instance
   uint32_t q_cap;       // power of two, >= q_threshold + (kDonateMost + 1) * (wavefronts)
   uint32_t q_threshold; // donate while count < threshold (0 = never)
   int32_t depth_cap;
@@ -151,7 +152,7 @@ struct Params {
   int32_t list_cap;     // degree-array kernels: entries of each candidate list (a power of two)
   int32_t* gnodes;      // degree-array kernels with the node in device memory: one stride-word
                         // slot per workgroup (nullptr: the node lives in LDS)
-  int32_t stack_lds;    // bitset kernels: 1 = each workgroup's stack ring lives in LDS after the
+  int32_t stack_lds;    // bitset kernels: 1 = each wavefront's stack ring lives in LDS after the
                         // adjacency matrix (depth_cap nodes), 0 = in `stacks`
   int32_t pvc;          // 1: PVC (instances stop once answered), 0: MVC
   int32_t start_depth;  // > 0: StackOnly traversal of instance 0 from this depth; 0: hybrid
@@ -254,11 +255,12 @@ hipError_t launch_max_greedy(const Params& p, int32_t* out, hipStream_t stream);
 constexpr int kMaxBitsetN = 512;
 constexpr int kMaxBitsetWords = 8;  // ceil(kMaxBitsetN / 64)
 // Largest n that takes the bitset kernels by default: 256 for MVC, 512 for PVC. One wavefront per
-// node and the teams' handovers suit the searches and roots of 257 to 512 vertices (PVC, planted
-// graphs of 257-320 / 385-448 vertices, 1,024 a call: 2.80 -> 0.46 ms / 4.84 -> 0.99 ms; 16 graphs
-// G(390, 3.5/390), 750,000 nodes: 9.5 -> 4.8 ms; one planted root of 300 / 500 vertices: 132 ->
-// 102 us / 152 -> 125 us). MVC calls keep the degree arrays above 256, the family that
-// vc_stats.bitset_words has always reported for them.
+// node and the teams' handovers suit the searches and roots of 257 to 512 vertices (PVC, degree
+// arrays -> bitsets: planted graphs of 257-320 / 385-448 vertices, 1,024 a call, 2.80 -> 0.46 ms /
+// 4.84 -> 0.99 ms; 16 graphs G(390, 3.5/390), 750,000 nodes, 7.0 -> 1.8 ms). MVC calls above 256 vertices
+// stay on degree arrays, which is the documented default that vc_stats.bitset_words reports, and not
+// the faster side: one G(300, 3.5/300) / G(400, 3.1/400) / G(500, 3.1/500) takes 1,526 / 619 / 831 us,
+// with VC_OPT_BITSETS 345 / 326 / 477.
 constexpr int kAutoBitsetN = 256;
 constexpr int kAutoBitsetNPvc = 512;
 hipError_t launch_bitset_greedy(const Params& p, hipStream_t stream);
